@@ -540,9 +540,11 @@ int create_factor(spc_symbolic sym, int precision, spc_factor *out, int nstatus 
     f->device = dev;
     f->nstatus = nstatus;
     size_t esz = precision == SPC_FP64 ? sizeof(double) : sizeof(float);
-    size_t bytes = std::max<size_t>(1, (size_t)sym->S.panel_entries()) * esz;
+    // kLoadSlack entries past the end: wide loads may reach beyond the last
+    // panel or inverse (masked by their callers)
+    size_t bytes = ((size_t)sym->S.panel_entries() + spc::kLoadSlack) * esz;
     hipError_t e = hipMalloc(&f->Lx, bytes);
-    size_t inv_bytes = std::max<size_t>(1, (size_t)sym->S.inv_off.back()) * esz;
+    size_t inv_bytes = ((size_t)sym->S.inv_off.back() + spc::kLoadSlack) * esz;
     if (e == hipSuccess) e = hipMalloc(&f->Linv, inv_bytes);
     f->nflags = spc::kFlagsPerBlock * (int)sym->S.sblocks.size();  // panel flags and claim of each block
     // status words, the device-error word and the raised-pivot count,

@@ -79,6 +79,10 @@ inline SolveSync make_solve_sync(int32_t *base, int64_t nblocks, WaitCtl wc) {
     return SolveSync{base, base + nblocks, base + 2 * nblocks, base + 3 * nblocks, wc.err, wc.spin};
 }
 
+// Entries that wide loads may read past the end of the panel and inverse
+// stores; both are allocated with them.
+constexpr int kLoadSlack = 4;
+
 enum { kTilesTrailing = 0, kTilesScatter = 1, kTilesTrsm = 2 };
 
 // Bytes of the per-device scratch array that spc_solve_noalloc works in.

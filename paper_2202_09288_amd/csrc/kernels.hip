@@ -1903,9 +1903,10 @@ __global__ __launch_bounds__(256, 2) void k_solve_fwd_multi(const SolveTask *tas
     }
 }
 
-// Backward, one task = rows r0..r1-1 below block q: thread (k, g) sums
-// L[r][c0+k] X[rows[r]] over the rows r of group g (64 rows each); the four
-// groups are added through LDS.  A block with one task finishes itself:
+// Backward, one task = rows r0..r1-1 below block q, one right-hand side:
+// thread (k, g) sums L[r][c0+k] X[rows[r]] over the rows r of group g (64
+// rows each); the four groups are added through LDS.  A block with one task
+// finishes itself:
 //   t = X_q - sum,  x_q = Linv_q^T t.
 // A block split over several tasks adds its sums into Acc.  In a level
 // launch the last task to arrive (sy.cnt) finishes the block.  In the
@@ -1918,28 +1919,22 @@ __global__ __launch_bounds__(256, 2) void k_solve_fwd_multi(const SolveTask *tas
 // sweep).  Persistent sweep, inside a supernode: the task finishing block
 // q also puts x_q into XB, and the first task of block q - 1 (whose first
 // rows are q's) polls XB for those rows instead of q's done flag (hand bits).
-template <typename T, int NR, bool PERSIST>
+template <typename T, bool PERSIST>
 __global__ __launch_bounds__(256) void k_solve_bwd(const SolveTask *tasks, int64_t ntasks, const int32_t *order,
                                                    const int32_t *rows, const T *Lx, const T *Linv, T *X, T *Acc,
-                                                   T *XB, int64_t n, int nrhs, const int64_t *tgt_ptr,
-                                                   const int32_t *tgt, SolveSync sy) {
+                                                   T *XB, int64_t n, const int64_t *tgt_ptr, const int32_t *tgt,
+                                                   SolveSync sy) {
     constexpr int NB = kNB, QW = 16, RG = 64;
-    constexpr int XR = 256 * (NR + 1), SM = 4 * NB * NR, VT = NR == 1 ? 0 : NB * (NB + 1);
-    constexpr int SH = XR > SM ? (XR > VT ? XR : VT) : (SM > VT ? SM : VT);
-    __shared__ T sh[SH];
-    __shared__ T tq[NB][NR];
-    __shared__ T ao[NB][NR];  // persistent finisher: the other tasks' sums
+    __shared__ T xr[256];      // x of the task's rows
+    __shared__ T Sm[4][NB];    // sums of the 4 groups
+    __shared__ T tq[NB];
+    __shared__ T ao[NB];       // persistent finisher: the other tasks' sums
     __shared__ int last;
     __shared__ int32_t slot;
-    T(*xr)[NR + 1] = reinterpret_cast<T(*)[NR + 1]>(sh);   // x of the task's rows
-    T(*Sm)[NB][NR] = reinterpret_cast<T(*)[NB][NR]>(sh);    // sums of the 4 groups
-    T(*Vt)[NB + 1] = reinterpret_cast<T(*)[NB + 1]>(sh);    // block inverse (several RHS)
     const int tid = threadIdx.x, k = tid & 63, g = tid >> 6;
-    // x_q = Linv^T t, with (Linv^T)[c][i] = Linv[i][c] nonzero for i >= c.
-    // One right-hand side: four threads per output c, 16 rows i each, that
-    // part of Linv held in registers.  Several: Linv is loaded coalesced and
-    // staged in LDS, then 16x16x4 MFMA, wave g the outputs 16 g .. 16 g + 15,
-    // lane bringing A[c][i] for c = 16 g + lane % 16, i = 4 s + lane / 16.
+    // x_q = Linv^T t, with (Linv^T)[c][i] = Linv[i][c] nonzero for i >= c:
+    // four threads per output c, 16 rows i each, that part of Linv held in
+    // registers.
     const int oc = tid >> 2;
     auto inv_row = [&](int s2) { return QW * (tid & 3) + s2; };
     for (int pass = 0;; ++pass) {
@@ -1956,16 +1951,11 @@ __global__ __launch_bounds__(256) void k_solve_bwd(const SolveTask *tasks, int64
 #pragma unroll
         for (int u = 0; u < RG; ++u)
             pv[u] = P[(int64_t)(tk.c0 + min(k, nb - 1)) * m + min<int64_t>(tk.r0 + g * RG + u, m - 1)];
-        if constexpr (NR == 1) {
 #pragma unroll
-            for (int s2 = 0; s2 < QW; ++s2) {
-                const int i = inv_row(s2);
-                const T v = Q[min(i, nb - 1) + (int64_t)min(oc, nb - 1) * nb];
-                qv[s2] = (i >= oc && i < nb && oc < nb) ? v : T(0);
-            }
-        } else {
-#pragma unroll
-            for (int u = 0; u < QW; ++u) qv[u] = Q[min(tid + 256 * u, nb * nb - 1)];
+        for (int s2 = 0; s2 < QW; ++s2) {
+            const int i = inv_row(s2);
+            const T v = Q[min(i, nb - 1) + (int64_t)min(oc, nb - 1) * nb];
+            qv[s2] = (i >= oc && i < nb && oc < nb) ? v : T(0);
         }
         int32_t my_tgt = -1;
         if (PERSIST) {
@@ -1976,27 +1966,16 @@ __global__ __launch_bounds__(256) void k_solve_bwd(const SolveTask *tasks, int64
         // the block's own forward values: final since the forward sweep, and
         // overwritten only by the task that finishes this block, so a task
         // known to finish it loads them before it waits
-        constexpr int XPT = NB * NR / 256 > 0 ? NB * NR / 256 : 1;
-        T xb[XPT];
-        auto load_xb = [&]() {
-#pragma unroll
-            for (int u = 0; u < XPT; ++u) {
-                const int e = tid + 256 * u, i = min(e / nrhs, nb - 1), q = min(e % nrhs, nrhs - 1);
-                xb[u] = X[(tk.g0 + i) * nrhs + q];
-            }
-        };
-        if (tk.ntasks == 1 || (PERSIST && tk.first)) load_xb();
+        T xb = T(0);
+        if (tk.ntasks == 1 || (PERSIST && tk.first)) xb = X[tk.g0 + min(tid, nb - 1)];
         const bool finisher = PERSIST && tk.first && tk.ntasks > 1;
         if (finisher) {
             // every other task of the block was dequeued before this one
             if (tid == 0) wait_value(&sy.cnt[tk.blk], tk.ntasks - 1, sy.err, sy.spin);
             __syncthreads();
             acquire_after_wait();
-            for (int e = tid; e < nb * nrhs; e += 256) {
-                const int i = e / nrhs, q = e % nrhs;
-                ao[i][q] = __hip_atomic_exchange(&Acc[(tk.g0 + i) * nrhs + q], T(0), __ATOMIC_RELAXED,
-                                                 __HIP_MEMORY_SCOPE_AGENT);
-            }
+            if (tid < nb)
+                ao[tid] = __hip_atomic_exchange(&Acc[tk.g0 + tid], T(0), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
         // rows of the next block of the supernode: their x come through XB
         const bool handed = PERSIST && (tk.hand & kHandOut) && tid < (tk.hand >> 8);
@@ -2006,174 +1985,330 @@ __global__ __launch_bounds__(256) void k_solve_bwd(const SolveTask *tasks, int64
             __syncthreads();
             acquire_after_wait();
         }
-        T xv[NR];
-#pragma unroll
-        for (int q = 0; q < NR; ++q) {
-            const int64_t e = gr * nrhs + min(q, nrhs - 1);
-            xv[q] = handed ? (q < nrhs ? wait_handed(&XB[e], sy.err, sy.spin) : T(0))
-                           : (PERSIST ? shared_load(&X[e]) : X[e]);
-        }
-#pragma unroll
-        for (int q = 0; q < NR; ++q) xr[tid][q] = (rown < tk.r1 && q < nrhs) ? xv[q] : T(0);
+        const T xv = handed ? wait_handed(&XB[gr], sy.err, sy.spin) : (PERSIST ? shared_load(&X[gr]) : X[gr]);
+        xr[tid] = rown < tk.r1 ? xv : T(0);
         __syncthreads();
-        T acc[NR];
-        if constexpr (NR == 1) {
+        {
             T a0 = T(0), a1 = T(0), a2 = T(0), a3 = T(0);
 #pragma unroll
             for (int u = 0; u < RG; u += 4) {
-                a0 += pv[u] * xr[g * RG + u][0];
-                a1 += pv[u + 1] * xr[g * RG + u + 1][0];
-                a2 += pv[u + 2] * xr[g * RG + u + 2][0];
-                a3 += pv[u + 3] * xr[g * RG + u + 3][0];
+                a0 += pv[u] * xr[g * RG + u];
+                a1 += pv[u + 1] * xr[g * RG + u + 1];
+                a2 += pv[u + 2] * xr[g * RG + u + 2];
+                a3 += pv[u + 3] * xr[g * RG + u + 3];
             }
-            acc[0] = (a0 + a1) + (a2 + a3);
-        } else {
-#pragma unroll
-            for (int q = 0; q < NR; ++q) acc[q] = T(0);
-#pragma unroll
-            for (int u = 0; u < RG; ++u) {
-                const T l = pv[u];
-#pragma unroll
-                for (int q = 0; q < NR; ++q) acc[q] += l * xr[g * RG + u][q];
-            }
+            Sm[g][k] = (a0 + a1) + (a2 + a3);
         }
         __syncthreads();
-#pragma unroll
-        for (int q = 0; q < NR; ++q) Sm[g][k][q] = acc[q];
-        __syncthreads();
-        for (int e = tid; e < NB * NR; e += 256) {
-            const int i = e % NB, q = e / NB;
-            tq[i][q] = Sm[0][i][q] + Sm[1][i][q] + Sm[2][i][q] + Sm[3][i][q];
-        }
+        if (tid < NB) tq[tid] = Sm[0][tid] + Sm[1][tid] + Sm[2][tid] + Sm[3][tid];
         __syncthreads();
         bool fin = true;
         if (tk.ntasks == 1) {
-#pragma unroll
-            for (int u = 0; u < XPT; ++u) {
-                const int e = tid + 256 * u, i = e / nrhs, q = e % nrhs;
-                if (e < nb * nrhs) tq[i][q] = xb[u] - tq[i][q];
-            }
+            if (tid < nb) tq[tid] = xb - tq[tid];
         } else if (finisher) {
-#pragma unroll
-            for (int u = 0; u < XPT; ++u) {
-                const int e = tid + 256 * u, i = e / nrhs, q = e % nrhs;
-                if (e < nb * nrhs) tq[i][q] = xb[u] - (tq[i][q] + ao[i][q]);
-            }
+            if (tid < nb) tq[tid] = xb - (tq[tid] + ao[tid]);
             if (tid == 0) sy.cnt[tk.blk] = 0;
-        } else if (PERSIST) {
-            for (int e = tid; e < nb * nrhs; e += 256) {
-                const int i = e / nrhs, q = e % nrhs;
-                atomicAdd(&Acc[(tk.g0 + i) * nrhs + q], tq[i][q]);
-            }
-            release_own();
-            __syncthreads();
-            if (tid == 0) atomicAdd(&sy.cnt[tk.blk], 1);
-            fin = false;
         } else {
-            if (tk.r1 > tk.r0)
-                for (int e = tid; e < nb * nrhs; e += 256) {
-                    const int i = e / nrhs, q = e % nrhs;
-                    atomicAdd(&Acc[(tk.g0 + i) * nrhs + q], tq[i][q]);
-                }
-            // the partial sums are device-scope atomics and the last task
-            // reads them back with atomic exchanges: each thread only waits
-            // for its own atomics to be performed before the count goes up
+            // the partial sums are device-scope atomics and the finishing
+            // task reads them back with atomic exchanges: each thread only
+            // waits for its own atomics to be performed before the count
+            // goes up
+            if (tid < nb && tk.r1 > tk.r0) atomicAdd(&Acc[tk.g0 + tid], tq[tid]);
             release_own();
             __syncthreads();
-            if (tid == 0) last = (atomicAdd(&sy.cnt[tk.blk], 1) == tk.ntasks - 1);
-            __syncthreads();
-            fin = last;
-            if (fin) {
-                load_xb();
-#pragma unroll
-                for (int u = 0; u < XPT; ++u) {
-                    const int e = tid + 256 * u, i = e / nrhs, q = e % nrhs;
-                    if (e < nb * nrhs) {
-                        const T a = __hip_atomic_exchange(&Acc[(tk.g0 + i) * nrhs + q], T(0), __ATOMIC_RELAXED,
-                                                          __HIP_MEMORY_SCOPE_AGENT);
-                        tq[i][q] = xb[u] - a;
-                    }
+            if (PERSIST) {
+                if (tid == 0) atomicAdd(&sy.cnt[tk.blk], 1);
+                fin = false;
+            } else {
+                if (tid == 0) last = (atomicAdd(&sy.cnt[tk.blk], 1) == tk.ntasks - 1);
+                __syncthreads();
+                fin = last;
+                if (fin) {
+                    if (tid < nb)
+                        tq[tid] = X[tk.g0 + tid] - __hip_atomic_exchange(&Acc[tk.g0 + tid], T(0), __ATOMIC_RELAXED,
+                                                                         __HIP_MEMORY_SCOPE_AGENT);
+                    if (tid == 0) sy.cnt[tk.blk] = 0;
                 }
-                if (tid == 0) sy.cnt[tk.blk] = 0;
             }
         }
         if (fin) {
             // x_q = Linv^T t (rows of t beyond nb meet zero entries of qv)
             __syncthreads();
-            if constexpr (NR == 1) {
-                T a0 = T(0), a1 = T(0);
+            T a0 = T(0), a1 = T(0);
 #pragma unroll
-                for (int s2 = 0; s2 < QW; s2 += 2) {
-                    a0 += qv[s2] * tq[inv_row(s2)][0];
-                    a1 += qv[s2 + 1] * tq[inv_row(s2 + 1)][0];
+            for (int s2 = 0; s2 < QW; s2 += 2) {
+                a0 += qv[s2] * tq[inv_row(s2)];
+                a1 += qv[s2 + 1] * tq[inv_row(s2 + 1)];
+            }
+            T a = a0 + a1;
+            a += __shfl_xor(a, 1);
+            a += __shfl_xor(a, 2);
+            if ((tid & 3) == 0 && oc < nb) {
+                if (PERSIST) {
+                    shared_store(&X[tk.g0 + oc], a);
+                    if (tk.hand & kHandIn) shared_store(&XB[tk.g0 + oc], a);
+                } else {
+                    X[tk.g0 + oc] = a;
                 }
-                T a = a0 + a1;
-                a += __shfl_xor(a, 1);
-                a += __shfl_xor(a, 2);
-                if ((tid & 3) == 0 && oc < nb) {
-                    if (PERSIST) {
-                        shared_store(&X[tk.g0 + oc], a);
-                        if (tk.hand & kHandIn) shared_store(&XB[tk.g0 + oc], a);
-                    } else {
-                        X[tk.g0 + oc] = a;
-                    }
-                }
-            } else if constexpr (NR < kMaxRhs) {
-                // a few right-hand sides: the inverse staged in LDS, each
-                // thread one or two outputs (c, q) as a dot product over the
-                // rows i >= c of the inverse's column c
-#pragma unroll
-                for (int u = 0; u < QW; ++u) {
-                    const int e = tid + 256 * u;
-                    if (e < nb * nb) Vt[e % nb][e / nb] = qv[u];
-                }
+            }
+            if (PERSIST) {
+                release_own();
                 __syncthreads();
+                if (tid == 0) atomicExch(&sy.done[tk.blk], 1);
+            }
+        }
+        __syncthreads();
+    }
+}
+
+// Four consecutive entries from an address aligned to one entry; they may
+// reach up to three entries past what the caller uses (the panel and the
+// inverse stores are allocated with that slack), and the caller masks them.
+template <typename T>
+struct Quad {
+    T v[4];
+};
+template <typename T>
+__device__ __forceinline__ Quad<T> load_quad(const T *p) {
+    Quad<T> q;
+    __builtin_memcpy(&q, p, sizeof(q));
+    return q;
+}
+
+// Backward, several right-hand sides (up to kMaxRhs): the steps of
+// k_solve_bwd, with both products on 16x16x4 MFMA blocks.
+//   sums: S[c][q] = sum_r L[r][c0+c] X[rows[r]][q].  Wave w takes rows
+//     64 u + 16 w .. + 15 of the task (u = 0 .. 3) for all 64 columns; lane
+//     l brings four consecutive rows 4 (l / 16) .. + 3 of column l % 16 with
+//     one wide load, and the x of the same four rows for right-hand side
+//     l % 16 straight from X (the order of k inside a product is free as
+//     long as both operands use the same).  The rows handed over by the
+//     next block (u = 0) are multiplied last and are spread over all four
+//     waves, so the chain from block to block sees a quarter of their
+//     products; the panel, the inverse and the other rows' products are
+//     done before.
+//   x_q = Linv^T t: wave w the outputs 16 w .. 16 w + 15, the inverse's
+//     columns in registers, t from LDS.
+// Bound by latency: the chain of blocks at the top of the tree, one block
+// waiting for the x of the next.  Polling a lane's four values together
+// (rather than one right-hand side after the other) and wide panel loads (16
+// columns x 128 bytes per instruction rather than 64 columns x 8) took the
+// 16-column FP64 solve of the 30x29x27 elasticity operator from 3331 to 1118
+// us and the refined FP32 8-column re-solve of a 50^3 grid from 5170 to 3235,
+// against the vector-FMA form with x in LDS that this replaced for all counts
+// (at 4 right-hand sides, FP64: 48^3 elasticity step 65.7 to 65.1 ms).
+template <typename T, bool PERSIST>
+__global__ __launch_bounds__(256, 2) void k_solve_bwd_multi(const SolveTask *tasks, int64_t ntasks,
+                                                            const int32_t *order, const int32_t *rows, const T *Lx,
+                                                            const T *Linv, T *X, T *Acc, T *XB, int64_t n, int nrhs,
+                                                            const int64_t *tgt_ptr, const int32_t *tgt,
+                                                            SolveSync sy) {
+    constexpr int NB = kNB, NR = kMaxRhs, NT = NB / 16, EPT = NB * NR / 256;
+    using M = Mfma<T>;
+    using acc_t = typename M::acc;
+    __shared__ T Sm[4][NB][NR + 1];  // each wave's sums
+    __shared__ T tq[NB][NR + 1];
+    __shared__ int32_t grs[256];
+    __shared__ int last;
+    __shared__ int32_t slot;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int kq = lane & 15, kg = lane >> 4;
+    const int64_t q = min(kq, nrhs - 1);  // columns beyond nrhs repeat the last and are not stored
+    for (int pass = 0;; ++pass) {
+        const int64_t t = next_task<PERSIST>(pass, order, sy.queue + 1, ntasks, &slot);
+        if (t < 0) return;
+        const SolveTask tk = tasks[t];
+        const int nb = tk.nb;
+        const int64_t m = tk.m;
+        const T *P = Lx + tk.loff;
+        const T *Q = Linv + tk.ioff;
+        const int nrows = tk.r1 - tk.r0;
+        const int ntile = (nb + 15) >> 4;  // column tiles that hold columns of the block
+        // Level launches skip the tiles beyond the block's columns and the
+        // task's rows (the same for every lane of a wave); the persistent
+        // sweep, of mostly full blocks, keeps the unconditional form.
+        auto row_tile = [&](int u) { return PERSIST || 64 * u + 16 * wave < nrows; };
+        auto col_tile = [&](int ct) { return PERSIST || ct < ntile; };
+        Quad<T> av[4][NT], qv[NT];
+        grs[tid] = rows[tk.roff + min<int64_t>(tk.r0 + tid, m - 1)];
 #pragma unroll
-                for (int u = 0; u < (NB * NR + 255) / 256; ++u) {
-                    const int e = tid + 256 * u, c = e / NR, q = e % NR;
-                    if (c < nb && q < nrhs) {
-                        T a0 = T(0), a1 = T(0);
-                        int i = c;
-                        for (; i + 1 < nb; i += 2) {
-                            a0 += Vt[i][c] * tq[i][q];
-                            a1 += Vt[i + 1][c] * tq[i + 1][q];
-                        }
-                        if (i < nb) a0 += Vt[i][c] * tq[i][q];
-                        const T a = a0 + a1;
-                        if (PERSIST) {
-                            shared_store(&X[(tk.g0 + c) * nrhs + q], a);
-                            if (tk.hand & kHandIn) shared_store(&XB[(tk.g0 + c) * nrhs + q], a);
-                        } else {
-                            X[(tk.g0 + c) * nrhs + q] = a;
-                        }
-                    }
+        for (int u = 0; u < 4; ++u) {
+            const int64_t r = min<int64_t>(tk.r0 + 64 * u + 16 * wave + 4 * kg, m - 1);
+#pragma unroll
+            for (int ct = 0; ct < NT; ++ct) {
+                if (row_tile(u) && col_tile(ct))
+                    av[u][ct] = load_quad(P + (int64_t)(tk.c0 + min(16 * ct + kq, nb - 1)) * m + r);
+                else
+                    av[u][ct] = Quad<T>{};
+            }
+        }
+        // the inverse's column c = 16 wave + kq, rows 16 s + 4 kg ..
+        const int c = 16 * wave + kq;
+#pragma unroll
+        for (int s = 0; s < NT; ++s)
+            qv[s] = col_tile(s) ? load_quad(Q + (int64_t)min(c, nb - 1) * nb + min(16 * s + 4 * kg, nb - 1))
+                                : Quad<T>{};
+        int32_t my_tgt = -1;
+        if (PERSIST) {
+            // at most one target block per row of the task
+            const int64_t tb = tgt_ptr[t], te = tgt_ptr[t + 1];
+            if (tid < te - tb) my_tgt = tgt[tb + tid];
+        }
+        // the block's own forward values (as in k_solve_bwd); thread's
+        // entries (row ei(v), right-hand side kq)
+        auto ei = [&](int v) { return (tid >> 4) + 16 * v; };
+        T xb[EPT];
+        auto load_xb = [&]() {
+#pragma unroll
+            for (int v = 0; v < EPT; ++v) xb[v] = X[(int64_t)(tk.g0 + min(ei(v), nb - 1)) * nrhs + q];
+        };
+#pragma unroll
+        for (int v = 0; v < EPT; ++v) xb[v] = T(0);
+        if (tk.ntasks == 1 || (PERSIST && tk.first)) load_xb();
+        const bool finisher = PERSIST && tk.first && tk.ntasks > 1;
+        auto take_acc = [&]() {
+#pragma unroll
+            for (int v = 0; v < EPT; ++v)
+                if (ei(v) < nb && kq < nrhs)
+                    xb[v] -= __hip_atomic_exchange(&Acc[(int64_t)(tk.g0 + ei(v)) * nrhs + kq], T(0),
+                                                   __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        };
+        if (finisher) {
+            // every other task of the block was dequeued before this one
+            if (tid == 0) wait_value(&sy.cnt[tk.blk], tk.ntasks - 1, sy.err, sy.spin);
+            __syncthreads();
+            acquire_after_wait();
+            take_acc();
+        }
+        const int nhand = (PERSIST && (tk.hand & kHandOut)) ? tk.hand >> 8 : 0;  // rows that come through XB
+        if (PERSIST) {
+            if (my_tgt >= 0 && !(nhand && my_tgt == tk.blk + 1)) wait_value(&sy.done[my_tgt], 1, sy.err, sy.spin);
+            acquire_after_wait();
+        }
+        __syncthreads();
+        if (nrows < 256) {
+            // a ragged task: what the wide loads took beyond its rows
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    const bool in = 64 * u + 16 * wave + 4 * kg + j < nrows;
+#pragma unroll
+                    for (int ct = 0; ct < NT; ++ct) av[u][ct].v[j] = in ? av[u][ct].v[j] : T(0);
                 }
+        }
+        acc_t acc[NT];
+#pragma unroll
+        for (int ct = 0; ct < NT; ++ct) acc[ct] = acc_t{0, 0, 0, 0};
+        T xv[4];  // x of the lane's four rows of one u
+        auto at = [&](int u, int j) { return 64 * u + 16 * wave + 4 * kg + j; };
+        auto product = [&](int u) {
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+#pragma unroll
+                for (int ct = 0; ct < NT; ++ct)
+                    if (col_tile(ct)) acc[ct] = M::run(av[u][ct].v[j], xv[j], acc[ct]);
+        };
+#pragma unroll
+        for (int u = 3; u >= (PERSIST ? 1 : 0); --u) {
+            if (!row_tile(u)) continue;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const T *px = &X[(int64_t)grs[at(u, j)] * nrhs + q];
+                const T v = PERSIST ? shared_load(px) : *px;
+                xv[j] = at(u, j) < nrows ? v : T(0);
+            }
+            product(u);
+        }
+        if (PERSIST) {
+            // the rows nearest the block: four values a lane, polled together
+            const T *px[4];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) px[j] = (at(0, j) < nhand ? XB : X) + (int64_t)grs[at(0, j)] * nrhs + q;
+            bool ready = false;
+            for (int it = 0; it < sy.spin; ++it) {
+                bool unset = false;
+#pragma unroll
+                for (int j = 0; j < 4; ++j) xv[j] = shared_load(px[j]);
+#pragma unroll
+                for (int j = 0; j < 4; ++j) unset = unset || (at(0, j) < nhand && is_unset(xv[j]));
+                if (!__any(unset)) {
+                    ready = true;
+                    break;
+                }
+                if ((it & 255) == 255 && __hip_atomic_load(sy.err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) break;
+                __builtin_amdgcn_s_sleep(1);
+            }
+            if (!ready && lane == 0) flag_device_error(sy.err);
+#pragma unroll
+            for (int j = 0; j < 4; ++j) xv[j] = at(0, j) < nrows && ready ? xv[j] : T(0);
+            product(0);
+        }
+#pragma unroll
+        for (int ct = 0; ct < NT; ++ct)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) Sm[wave][16 * ct + M::row(lane, v)][kq] = acc[ct][v];
+        __syncthreads();
+        T sum[EPT];
+#pragma unroll
+        for (int v = 0; v < EPT; ++v)
+            sum[v] = (Sm[0][ei(v)][kq] + Sm[1][ei(v)][kq]) + (Sm[2][ei(v)][kq] + Sm[3][ei(v)][kq]);
+        bool fin = true;
+        if (tk.ntasks > 1 && !finisher) {
+            // the partial sums are device-scope atomics and the finishing
+            // task reads them back with atomic exchanges: each thread only
+            // waits for its own atomics to be performed before the count
+            // goes up
+            if (nrows > 0)
+#pragma unroll
+                for (int v = 0; v < EPT; ++v)
+                    if (ei(v) < nb && kq < nrhs) atomicAdd(&Acc[(int64_t)(tk.g0 + ei(v)) * nrhs + kq], sum[v]);
+            release_own();
+            __syncthreads();
+            if (PERSIST) {
+                if (tid == 0) atomicAdd(&sy.cnt[tk.blk], 1);
+                fin = false;
             } else {
-                using acc_t = typename Mfma<T>::acc;
-#pragma unroll
-                for (int u = 0; u < QW; ++u) {
-                    const int e = tid + 256 * u;
-                    if (e < nb * nb) Vt[e % nb][e / nb] = qv[u];
-                }
+                if (tid == 0) last = (atomicAdd(&sy.cnt[tk.blk], 1) == tk.ntasks - 1);
                 __syncthreads();
-                const int c0 = 16 * g + (k & 15);
-                acc_t xa = {0, 0, 0, 0};
+                fin = last;
+                if (fin) {
+                    load_xb();
+                    take_acc();
 #pragma unroll
-                for (int s2 = 0; s2 < QW; ++s2) {
-                    const int i = 4 * s2 + (k >> 4);
-                    const T a = (i >= c0 && i < nb && c0 < nb) ? Vt[min(i, nb - 1)][min(c0, nb - 1)] : T(0);
-                    xa = Mfma<T>::run(a, tq[i][k & 15], xa);
+                    for (int v = 0; v < EPT; ++v) sum[v] = T(0);
                 }
+            }
+        }
+        if (fin) {
+            if (tid == 0 && tk.ntasks > 1) sy.cnt[tk.blk] = 0;
 #pragma unroll
-                for (int v = 0; v < 4; ++v) {
-                    const int c = 16 * g + Mfma<T>::row(k, v), q = k & 15;
-                    if (c < nb && q < nrhs) {
-                        if (PERSIST) {
-                            shared_store(&X[(tk.g0 + c) * nrhs + q], xa[v]);
-                            if (tk.hand & kHandIn) shared_store(&XB[(tk.g0 + c) * nrhs + q], xa[v]);
-                        } else {
-                            X[(tk.g0 + c) * nrhs + q] = xa[v];
-                        }
+            for (int v = 0; v < EPT; ++v) tq[ei(v)][kq] = ei(v) < nb ? xb[v] - sum[v] : T(0);
+            __syncthreads();
+            // x_q = Linv^T t; the inverse is zero above row c and has no row
+            // beyond nb
+            acc_t xa[2] = {acc_t{0, 0, 0, 0}, acc_t{0, 0, 0, 0}};
+#pragma unroll
+            for (int s = 0; s < NT; ++s)
+                if (s >= wave && col_tile(s))
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) {
+                        const int i = 16 * s + 4 * kg + j;
+                        const T a = (i >= c && i < nb) ? qv[s].v[j] : T(0);
+                        xa[j & 1] = M::run(a, tq[i][kq], xa[j & 1]);
+                    }
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const int co = 16 * wave + M::row(lane, v);
+                const T xo = xa[0][v] + xa[1][v];
+                if (co < nb && kq < nrhs) {
+                    const int64_t e = (int64_t)(tk.g0 + co) * nrhs + kq;
+                    if (PERSIST) {
+                        if (tk.hand & kHandIn) shared_store(&XB[e], xo);
+                        shared_store(&X[e], xo);
+                    } else {
+                        X[e] = xo;
                     }
                 }
             }
@@ -2903,26 +3038,21 @@ void launch_solve_bwd(const DevPlan &P, int64_t t0, int64_t t1, const T *Lx, con
     const SolveTask *tk = persist ? P.stasks : P.stasks + t0;
     const int64_t *tp = persist ? P.stgt_ptr : P.stgt_ptr + t0;
     const int32_t *ord = persist ? P.bwd_order : nullptr;
-    // the instantiation for the fewest right-hand sides that holds nrhs
-#define SPC_BWD(NRV)                                                                                          \
-    do {                                                                                                      \
-        if (persist)                                                                                          \
-            hipLaunchKernelGGL((k_solve_bwd<T, NRV, true>), g, b, 0, st, tk, nt, ord, P.rows, Lx, Linv, X, Acc, \
-                               XB, n, nrhs, tp, P.stgt, sy);                                                  \
-        else                                                                                                  \
-            hipLaunchKernelGGL((k_solve_bwd<T, NRV, false>), g, b, 0, st, tk, nt, ord, P.rows, Lx, Linv, X,    \
-                               Acc, XB, n, nrhs, tp, P.stgt, sy);                                             \
-    } while (0)
     if (nrhs == 1) {
-        SPC_BWD(1);
-    } else if (nrhs <= 4) {
-        SPC_BWD(4);
-    } else if (nrhs <= 8) {
-        SPC_BWD(8);
+        if (persist)
+            hipLaunchKernelGGL((k_solve_bwd<T, true>), g, b, 0, st, tk, nt, ord, P.rows, Lx, Linv, X, Acc, XB, n, tp,
+                               P.stgt, sy);
+        else
+            hipLaunchKernelGGL((k_solve_bwd<T, false>), g, b, 0, st, tk, nt, ord, P.rows, Lx, Linv, X, Acc, XB, n, tp,
+                               P.stgt, sy);
     } else {
-        SPC_BWD(kMaxRhs);
+        if (persist)
+            hipLaunchKernelGGL((k_solve_bwd_multi<T, true>), g, b, 0, st, tk, nt, ord, P.rows, Lx, Linv, X, Acc, XB,
+                               n, nrhs, tp, P.stgt, sy);
+        else
+            hipLaunchKernelGGL((k_solve_bwd_multi<T, false>), g, b, 0, st, tk, nt, ord, P.rows, Lx, Linv, X, Acc, XB,
+                               n, nrhs, tp, P.stgt, sy);
     }
-#undef SPC_BWD
 }
 
 void launch_spmv(const int64_t *rowptr, const int32_t *colidx, const int64_t *valmap, const double *values,

@@ -1,0 +1,83 @@
+"""GPU kernels at the edges of their tiles, against the CPU oracle: panels and
+blocks of 1 to a few columns and rows, one row or column past a tile, every
+level launched on its own and every level persistent.
+
+Tolerances: solves are held to the normwise backward error 1e-12 (FP64) and
+1e-5 (FP32), factors to 1e-10 (FP64, each supernode on its own), the bars of
+the other parity tests.
+"""
+import numpy as np
+import pytest
+
+import oracle
+from paper_2202_09288_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+BAR = {"fp64": 1e-12, "fp32": 1e-5}
+
+
+@pytest.fixture(scope="module")
+def lib():
+    import torch
+    assert torch.cuda.is_available(), "GPU tests need a HIP device"
+    from paper_2202_09288_amd import spchol
+    return spchol
+
+
+def spd(n, pattern, seed=0):
+    """Diagonally dominant matrix with the given strictly lower entries."""
+    rng = np.random.default_rng(seed)
+    r, c = pattern
+    v = -(0.5 + rng.random(r.size))
+    d = 1.0 + np.bincount(r, -v, n) + np.bincount(c, -v, n)
+    colptr, rowidx, values = W.lower_csc(n, np.concatenate([np.arange(n), r]), np.concatenate([np.arange(n), c]),
+                                         np.concatenate([d, v]))
+    return colptr, rowidx, values, np.arange(n, dtype=np.int32)
+
+
+def dense(n):
+    return spd(n, np.tril_indices(n, -1))
+
+
+def wide(w, m):
+    """One supernode of w columns and m rows, over a dense trailing block."""
+    return spd(m, np.tril_indices(m, -1)) if w == m else spd(
+        m, tuple(np.concatenate(a) for a in zip(np.tril_indices(w, -1),
+                                                (np.repeat(np.arange(w, m), w), np.tile(np.arange(w), m - w)))))
+
+
+def tridiag(n):
+    return spd(n, (np.arange(1, n), np.arange(n - 1)))
+
+
+MATRICES = {
+    "one": lambda: dense(1), "pair": lambda: dense(2), "triple": lambda: dense(3), "tridiag-5": lambda: tridiag(5),
+    "dense-63": lambda: dense(63), "dense-65": lambda: dense(65), "dense-130": lambda: dense(130),
+    "wide-17x18": lambda: wide(17, 18), "wide-64x321": lambda: wide(64, 321), "wide-66x323": lambda: wide(66, 323),
+}
+# every supernode on the blocked paths
+BLOCKED = {"tiny_w": -1, "tiny_m": -1, "small_w": -1, "small_m": -1}
+
+
+@pytest.mark.parametrize("precision", ["fp64", "fp32"])
+@pytest.mark.parametrize("name", list(MATRICES))
+def test_solve_sweeps_on_ragged_blocks(lib, name, precision):
+    """The block sweeps' wide loads, row and column tiles and right-hand-side
+    padding on blocks and tasks that fill them only in part."""
+    import torch
+    colptr, rowidx, values, perm = MATRICES[name]()
+    n = colptr.size - 1
+    B = np.random.default_rng(3).uniform(-1, 1, (n, 17))
+    dv = torch.from_numpy(values).cuda()
+    for persist in (-1, 1 << 30):
+        F = lib.factorize(lib.Symbolic(colptr, rowidx, perm, 0.05, dict(BLOCKED, solve_persist_max=persist)), dv,
+                          precision)
+        F.sync()
+        for q in (1, 2, 4, 9, 16, 17):
+            X = torch.from_numpy(np.ascontiguousarray(B[:, :q].T)).cuda()
+            F.solve(X)
+            F.sync()
+            eta = oracle.backward_error(n, colptr, rowidx, values, X.cpu().numpy().T, B[:, :q])
+            print(f"{name} {precision} persist={persist} nrhs={q}: eta={eta:.2e}", flush=True)
+            assert eta <= BAR[precision]
