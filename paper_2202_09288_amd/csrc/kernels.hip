@@ -823,22 +823,39 @@ __global__ __launch_bounds__(256) void k_tiny(const SmallTask *tasks, int64_t n1
 // ---------------------------------------------------------------------------
 // k_small: one workgroup per small supernode (w <= kSmallW, m <= kSmallM),
 // the whole m x w panel in LDS:
-//   1. column Cholesky of the panel, right-looking: l_jj = sqrt(d_j),
-//      l_ij = a_ij / l_jj, then a_ik -= l_ij l_kj for the columns right of j
-//      (POTRF of the diagonal block and TRSM of the rows below at once);
-//   2. the inverse of the diagonal triangle, one column per thread by
-//      forward substitution (kept for the solves);
-//   3. the update C = P P^T of the rows below the block, scatter-added into
-//      the ancestors: C[i][k] goes to cbase[k] + rel[crel[k] + i].
+//   1. column Cholesky by panels of 16 columns: each wave holds the panel's
+//      16 diagonal rows in lanes 0..15 and 48 rows below in the others, 16
+//      columns of a row in registers, pivots and multipliers read from their
+//      lanes as in k_tiny (POTRF of the diagonal block and TRSM of the rows
+//      below at once); every wave factors the diagonal rows for itself, so
+//      the pivot chain crosses no barrier.  Waves 0..2 cover all the rows.
+//      The second panel's columns are brought up to date in 16x16 MFMA tiles
+//      in between;
+//   2. the inverse of the diagonal triangle (kept for the solves) by wave 3:
+//      each 16x16 triangle by forward substitution, lane = column, then
+//      inv [L11 0; L21 L22] = [X11 0; -X22 L21 X11  X22];
+//   3. the update C = P P^T of the rows below the block in 16x16 MFMA tiles,
+//      taken by the waves from a counter and scatter-added into the
+//      ancestors: C[i][k] goes to cbase[k] + rel[crel[k] + i].  The tile is
+//      formed transposed, so 16 lanes add to 16 rows of one target column.
 // Pivots that are not positive and finite lower the status word.
+// Bound by latency (a chain of w pivots in a launch of few workgroups, or
+// the atomics of the scatter in a wide one): a column at a time with
+// three barriers each and a division per entry took 55 us a launch over the
+// levels of the 64^2 grid (FP64) and 67 us over those of a batch of 32
+// systems (FP32), this form 16 and 32 us.
 // ---------------------------------------------------------------------------
 // LDS of one small supernode: A[c][i] = panel entry (row i, column c), the
 // inverse Vt[c][a] = (L^{-1})_ac, and the scatter addresses of its rows.
+// (A's row stride puts the four k of a 16x16x4 operand in different banks.)
 template <typename T>
 struct SmallLds {
-    T A[kSmallW][kSmallM + 1];
+    T A[kSmallW][kSmallM + 16];
     T Vt[kSmallW][kSmallW + 1];
+    T U[16][17];
+    T rdg[kSmallW];
     int64_t cb[kSmallM], cr[kSmallM];
+    int tile;
 };
 
 // One workgroup's small supernode (the body of k_small and of the
@@ -848,102 +865,194 @@ __device__ __forceinline__ void small_body(const SmallTask &tk, SmallLds<T> &L, 
                                            const int64_t *crel, const int32_t *rel, T *Lx, T *Linv,
                                            unsigned long long *status, const int32_t *status_slot,
                                            PivotFloor<T> pfl) {
-    constexpr int MS = kSmallM, WS = kSmallW, LPT = WS * MS / 256, SB = 8;
+    constexpr int MS = kSmallM, PW = 16, RW = 64 - PW;  // RW: rows below per wave
+    static_assert(kSmallW == 2 * PW && 3 * RW >= kSmallM, "two panels; three waves cover the rows");
+    using M = Mfma<T>;
+    using acc_t = typename M::acc;
     auto &A = L.A;
     auto &Vt = L.Vt;
-    auto &cb = L.cb;
-    auto &cr = L.cr;
     const int m = tk.m, w = tk.w;
     T *P = Lx + tk.loff;
-    const int tid = threadIdx.x;
-    {
-        T ld[LPT];
+    const int tid = threadIdx.x, lane = tid & 63, l16 = lane & 15, lg = lane >> 4;
+    const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int npan = w > PW ? 2 : 1;
+    // columns in pairs (128 threads a column); columns w.. of a panel are zero
+    auto fill = [&](auto count) {
+        constexpr int N = decltype(count)::value;
+        T ld[N];
 #pragma unroll
-        for (int q = 0; q < LPT; ++q) {
+        for (int q = 0; q < N; ++q) {
             const int e = tid + 256 * q, i = e % MS, c = e / MS;
             const T *src = &P[(int64_t)min(c, w - 1) * m + min(i, m - 1)];
             ld[q] = COH ? dev_load(src) : *src;
         }
         if (tid < MS) {
             const int64_t k = tk.roff + min(max(tid, w), m - 1);
-            cb[tid] = cbase[k];
-            cr[tid] = crel[k];
+            L.cb[tid] = cbase[k];
+            L.cr[tid] = crel[k];
         }
+        if (tid == 0) L.tile = 0;
 #pragma unroll
-        for (int q = 0; q < LPT; ++q) {
+        for (int q = 0; q < N; ++q) {
             const int e = tid + 256 * q, i = e % MS, c = e / MS;
             A[c][i] = (i < m && c < w) ? ld[q] : T(0);
         }
-    }
+    };
+    if (npan == 1) fill(std::integral_constant<int, PW / 2>{});
+    else fill(std::integral_constant<int, PW>{});
     __syncthreads();
-    int bad = -1, boosted = 0;
-    for (int j = 0; j < w; ++j) {
-        T d = A[j][j];
-        if (pfl.v) {
-            const T fj = pfl.v[tk.g0 + j];
-            if (d < fj) {
-                d = fj;
-                ++boosted;
+    // inverse of the diagonal triangle at p0 (wave 3; lane = column): v holds
+    // the right-hand side from row k on, shifted up one row a step, so the
+    // step's code is the same for every k
+    auto invert16 = [&](int p0) {
+        const int w1 = min(w, p0 + PW);
+        T v[PW];
+#pragma unroll
+        for (int a = 0; a < PW; ++a) v[a] = a == l16 ? T(1) : T(0);
+#pragma unroll 1
+        for (int k = p0; k < w1; ++k) {
+            const T y = v[0] * L.rdg[k];
+            if (lane < PW) Vt[p0 + l16][k] = y;
+#pragma unroll
+            for (int a = 1; a < PW; ++a) {
+                const T l = A[k][k + a];
+                v[a - 1] = v[a] - (k + a < w1 ? l : T(0)) * y;
             }
+            v[PW - 1] = T(0);
         }
-        if (bad < 0 && !finite_pos(d)) bad = j;
-        const T ljj = sqrt(d);
-        __syncthreads();  // every thread has read d
-        for (int i = j + tid; i < m; i += 256) A[j][i] = (i == j) ? ljj : A[j][i] / ljj;
-        __syncthreads();
-        const int rem = w - j - 1;
-        for (int e = tid; e < rem * m; e += 256) {
-            const int k = j + 1 + e / m, i = e % m;
-            if (i >= k) A[k][i] -= A[j][i] * A[j][k];
+    };
+    int bad = -1, boosted = 0;
+#pragma unroll 1
+    for (int p = 0; p < npan; ++p) {
+        const int p0 = PW * p, b0 = min(w, p0 + PW);
+        if (p == 1) {
+            // the second panel's columns less the first panel's product:
+            // rows 16.. in tiles of 16, tile = (columns) x (rows)
+            for (int i0 = PW + 16 * wv; i0 < m; i0 += 64) {
+                acc_t acc = {0, 0, 0, 0};
+#pragma unroll
+                for (int kk = 0; kk < PW; kk += 4) acc = M::run(A[kk + lg][PW + l16], A[kk + lg][i0 + l16], acc);
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                    const int c = PW + M::row(lane, v);
+                    if (c < w) A[c][i0 + l16] -= acc[v];
+                }
+            }
+            __syncthreads();
+        }
+        // lanes 0..15: the diagonal rows (identity beyond w); the others: rows b0 + RW wv ..
+        const bool dg = lane < PW;
+        const int i = dg ? p0 + lane : b0 + RW * wv + lane - PW;
+        const bool real = dg ? i < w : i < m;
+        T r[PW];
+#pragma unroll
+        for (int c = 0; c < PW; ++c) {
+            const T a = A[p0 + c][min(i, m - 1)];
+            r[c] = real ? a : (c == lane ? T(1) : T(0));
+        }
+        __syncthreads();  // every wave has read the diagonal rows that wave 0 stores below
+        if (wv < 3 && (wv == 0 || b0 + RW * wv < m)) {
+            T mine = T(0);
+            const T flo = pfl.v ? pfl.v[tk.g0 + min(p0 + l16, w - 1)] : T(0);
+#pragma unroll
+            for (int c = 0; c < PW; ++c) {
+                if ((c & 3) == 0 && p0 + c >= w) break;
+                T d = lane_read(r[c], c);
+                if (pfl.v) {
+                    const T fc = lane_read(flo, c);
+                    if (d < fc && p0 + c < w) {
+                        d = fc;
+                        ++boosted;
+                    }
+                }
+                if (bad < 0 && p0 + c < w && !finite_pos(d)) bad = p0 + c;
+                // l_cc, 1 / l_cc and l_ic with a correction step each, which
+                // leaves the rounding of a square root and a division
+                const T rs = rsqrt_nr(d);
+                T ld = d * rs;
+                ld = fma(fma(-ld, ld, d), T(0.5) * rs, ld);
+                if (lane == c) mine = fma(fma(-rs, ld, T(1)), rs, rs);
+                const T q = r[c] * rs;
+                const T lic = (lane == c) ? ld : fma(fma(-q, ld, r[c]), rs, q);
+                r[c] = lic;
+#pragma unroll
+                for (int c2 = c + 1; c2 < PW; ++c2) r[c2] -= lic * lane_read(lic, c2);
+            }
+            if (wv == 0 && dg) L.rdg[p0 + lane] = mine;
+            if (real && (wv == 0 || !dg))
+#pragma unroll
+                for (int c = 0; c < PW; ++c) {
+                    if (dg && c > lane) continue;
+                    A[p0 + c][i] = r[c];
+                    if (p0 + c < w) P[(int64_t)(p0 + c) * m + i] = r[c];
+                }
+        } else if (wv == 3 && p == 1) {
+            invert16(0);
         }
         __syncthreads();
     }
     if (tid == 0 && bad >= 0)
         atomicMin(status + (status_slot ? status_slot[tk.s] : 0), (unsigned long long)(tk.g0 + bad));
     if (tid == 0 && boosted) atomicAdd(pfl.count, boosted);
-    for (int e = tid; e < w * MS; e += 256) {
-        const int i = e % MS, c = e / MS;
-        if (i < m && i >= c) P[(int64_t)c * m + i] = A[c][i];
-    }
-    // inverse of the diagonal triangle: thread c owns column c
-    if (tid < w) {
-        const int c = tid;
-        for (int a = 0; a < w; ++a) {
-            T v = (a == c) ? T(1) : T(0);
-            for (int k = c; k < a; ++k) v -= A[k][a] * Vt[c][k];
-            Vt[c][a] = (a < c) ? T(0) : v / A[a][a];
+    if (wv == 3) {
+        invert16(PW * (npan - 1));
+        wave_lds_sync();
+        if (npan == 2) {
+            acc_t acc = {0, 0, 0, 0};  // L21 X11
+#pragma unroll
+            for (int kk = 0; kk < PW; kk += 4) {
+                const int k = kk + lg;
+                acc = M::run(PW + l16 < w ? A[k][PW + l16] : T(0), Vt[l16][k], acc);
+            }
+#pragma unroll
+            for (int v = 0; v < 4; ++v) L.U[M::row(lane, v)][l16] = acc[v];
+            wave_lds_sync();
+            acc = acc_t{0, 0, 0, 0};  // X22 (L21 X11)
+#pragma unroll
+            for (int kk = 0; kk < PW; kk += 4)
+                acc = M::run(PW + kk + lg < w ? Vt[PW + kk + lg][PW + l16] : T(0), L.U[kk + lg][l16], acc);
+#pragma unroll
+            for (int v = 0; v < 4; ++v) Vt[l16][PW + M::row(lane, v)] = -acc[v];
+            wave_lds_sync();
+        }
+        T *Vi = Linv + tk.ioff;
+        for (int e = lane; e < w * w; e += 64) {
+            const int c = e / w, a = e % w;
+            Vi[e] = a >= c ? Vt[c][a] : T(0);
         }
     }
-    __syncthreads();
-    T *Vi = Linv + tk.ioff;
-    for (int e = tid; e < w * w; e += 256) Vi[e] = Vt[e / w][e % w];
     // update of the rows below, scatter-added into the ancestors
-    const int mb = m - w, ne = mb * mb;
-    for (int e0 = 0; e0 < ne; e0 += 256 * SB) {
-        int32_t rr[SB];
-        int cc_[SB];
-        T vv[SB];
-        bool ok[SB];
+    const int mb = m - w, nt = (mb + 15) / 16, ntile = nt * (nt + 1) / 2;
+    for (;;) {
+        int x = 0;
+        if (lane == 0) x = atomicAdd(&L.tile, 1);
+        x = __builtin_amdgcn_readfirstlane(x);
+        if (x >= ntile) break;
+        int ti = 0;
+        while ((ti + 1) * (ti + 2) / 2 <= x) ++ti;
+        const int tj = x - ti * (ti + 1) / 2;
+        const int i = w + 16 * ti + l16, ic = min(i, m - 1);  // row of C
+        int64_t cbk[4];
+        int32_t rv[4];
+        bool ok[4];
 #pragma unroll
-        for (int u = 0; u < SB; ++u) {
-            const int e = e0 + tid + 256 * u;
-            const int r = w + e % mb, cc = w + e / mb;  // row, column (positions in R_s)
-            ok[u] = e < ne && cc <= r;
-            const int rc = ok[u] ? r : w, ccc = ok[u] ? cc : w;
-            cc_[u] = ccc;
-            rr[u] = rel[cr[ccc] + rc];
-            T acc = T(0);
-            for (int k = 0; k < w; ++k) acc += A[k][rc] * A[k][ccc];
-            vv[u] = acc;
+        for (int v = 0; v < 4; ++v) {
+            const int k = w + 16 * tj + M::row(lane, v), kc = min(k, ic);  // column of C
+            ok[v] = i < m && k <= i;
+            cbk[v] = L.cb[kc];
+            rv[v] = rel[L.cr[kc] + ic];
         }
+        acc_t acc = {0, 0, 0, 0};
+        for (int kk = 0; kk < w; kk += 4)
+            acc = M::run(A[kk + lg][w + 16 * tj + l16], A[kk + lg][w + 16 * ti + l16], acc);
 #pragma unroll
-        for (int u = 0; u < SB; ++u)
-            if (ok[u]) atomicAdd(&Lx[cb[cc_[u]] + rr[u]], -vv[u]);
+        for (int v = 0; v < 4; ++v)
+            if (ok[v]) atomicAdd(&Lx[cbk[v] + rv[v]], -acc[v]);
     }
 }
 
 template <typename T>
-__global__ __launch_bounds__(256) void k_small(const SmallTask *tasks, const int64_t *cbase, const int64_t *crel,
+__global__ __launch_bounds__(256, 3) void k_small(const SmallTask *tasks, const int64_t *cbase, const int64_t *crel,
                                                const int32_t *rel, T *Lx, T *Linv, unsigned long long *status,
                                                const int32_t *status_slot, PivotFloor<T> pfl) {
     __shared__ SmallLds<T> L;
@@ -970,11 +1079,8 @@ __global__ void k_persist_reset(const int32_t *pdep0, int64_t ns, int32_t *pdep,
     if (i == 0) *qctr = 0;
 }
 
-// (at least six waves per SIMD where the LDS allows it, i.e. in FP32: the
-// entries are latency-bound, and 4 -> 6 waves cut the 512-system batch's
-// launch from 13.3 to 10.4 ms)
 template <typename T>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(6, 8))) void k_persist_small(const PersistEntry *queue, const int32_t *chunk, int64_t nc,
+__global__ __launch_bounds__(256, 3) void k_persist_small(const PersistEntry *queue, const int32_t *chunk, int64_t nc,
                                                        const SmallTask *psmall,
                                                        const SmallTask *ptiny, const int64_t *ptgt_ptr,
                                                        const int32_t *ptgt, int32_t *pdep, int32_t *qctr,

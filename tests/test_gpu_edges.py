@@ -81,3 +81,44 @@ def test_solve_sweeps_on_ragged_blocks(lib, name, precision):
             eta = oracle.backward_error(n, colptr, rowidx, values, X.cpu().numpy().T, B[:, :q])
             print(f"{name} {precision} persist={persist} nrhs={q}: eta={eta:.2e}", flush=True)
             assert eta <= BAR[precision]
+
+
+def arrow(w, b, blocks=2):
+    """Dense blocks of w columns, each coupled to the same b last columns:
+    supernodes of w columns and w + b rows, and one of b columns."""
+    n = blocks * w + b
+    rows, cols = [], []
+    for k in range(blocks):
+        r, c = np.tril_indices(w, -1)
+        rows += [k * w + r, blocks * w + np.repeat(np.arange(b), w)]
+        cols += [k * w + c, k * w + np.tile(np.arange(w), b)]
+    return spd(n, (np.concatenate(rows), np.concatenate(cols)), seed=w)
+
+
+def factor_and_solve(lib, matrix, tuning, precision="fp64", nrhs=3, z=-1.0):
+    """Largest relative error of a supernode against the oracle, and the
+    solve's backward error."""
+    import torch
+    colptr, rowidx, values, perm = matrix
+    n = colptr.size - 1
+    S = oracle.Symbolic(colptr, rowidx, perm, z)
+    F = lib.factorize(lib.Symbolic(colptr, rowidx, perm, z, tuning), torch.from_numpy(values).cuda(), precision)
+    F.sync()
+    per = oracle.supernode_rel_errors(F.export(), S.factor(values), S.lptr, S.lower_mask())
+    B = np.random.default_rng(4).uniform(-1, 1, (n, nrhs))
+    X = torch.from_numpy(np.ascontiguousarray(B.T)).cuda()
+    F.solve(X)
+    F.sync()
+    return float(per.max()), oracle.backward_error(n, colptr, rowidx, values, X.cpu().numpy().T, B), S
+
+
+@pytest.mark.parametrize("precision", ["fp64", "fp32"])
+@pytest.mark.parametrize("persist", [-1, 1])
+@pytest.mark.parametrize("w,b", [(1, 127), (1, 1), (9, 40), (15, 113), (16, 112), (17, 111), (17, 1), (20, 33),
+                                 (31, 97), (32, 96), (32, 1), (30, 50)])
+def test_small_supernode_shapes(lib, w, b, persist, precision):
+    """The one-workgroup path at one and two 16-column panels, ragged ones
+    among them, and at the fewest and most rows below."""
+    err, eta, S = factor_and_solve(lib, arrow(w, b), {"tiny_w": -1, "persist": persist}, precision)
+    print(f"w={w} b={b} persist={persist} {precision}: worst supernode {err:.2e}, eta {eta:.2e}", flush=True)
+    assert S.nsuper == 3 and err <= (1e-10 if precision == "fp64" else 1e-4) and eta <= BAR[precision]
