@@ -376,7 +376,7 @@ void enqueue_factor(const spc::Symbolic &S, const spc::DevPlan &P, const double 
             const auto &stp = S.steps[k];
             if (stp.f1 > stp.f0)
                 prof.run(SPC_K_POTRF, stp.potrf_flops, st,
-                         [&] { spc::launch_potrf<T>(P, stp.f0, stp.f1, Lx, Linv, status, wc.err, pfl, st); });
+                         [&] { spc::launch_potrf<T>(P, stp.f0, stp.f1, Lx, Linv, status, pfl, st); });
             if (stp.p1 > stp.p0)
                 prof.run(SPC_K_TRSM, stp.trsm_flops, st, [&] {
                     spc::launch_tiles<T>(P, spc::kTilesTrsm, stp.p0, stp.p1, Lx, Linv, status, nullptr, wc, false, pfl,

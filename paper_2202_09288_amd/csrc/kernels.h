@@ -106,7 +106,7 @@ template <typename T>
 void launch_pivot_floor(const DevPlan &P, int64_t n, const double *values, double theta, T *floor, hipStream_t st);
 template <typename T>
 void launch_potrf(const DevPlan &P, int64_t t0, int64_t t1, T *Lx, T *Linv, unsigned long long *status,
-                  int32_t *deverr, PivotFloor<T> pfl, hipStream_t st);
+                  PivotFloor<T> pfl, hipStream_t st);
 template <typename T>
 void launch_small(const DevPlan &P, int64_t t0, int64_t t1, T *Lx, T *Linv, unsigned long long *status,
                   PivotFloor<T> pfl, hipStream_t st);

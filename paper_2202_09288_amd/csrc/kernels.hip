@@ -143,26 +143,6 @@ __global__ void k_pivot_floor(const int64_t *dsrc, int64_t n, const double *valu
 // memory at the join, which serializes a loop of them.
 // ---------------------------------------------------------------------------
 
-// ---------------------------------------------------------------------------
-// k_potrf: one workgroup (4 waves) per diagonal block (nb <= kNB = 64), held
-// in LDS.  Blocked right-looking Cholesky with 16-column panels:
-//   - wave 0 factors the panel with lane = row and the panel's 16 columns in
-//     registers: for column j, d = a_jj (read from lane j), 1/l_jj from a
-//     reciprocal square root, l_ij = a_ij / l_jj, and the later panel
-//     columns k lose l_ij l_kj (l_kj read from lane k);
-//   - the four waves subtract the panel's product from the trailing lower
-//     part in 16x16 MFMA tiles.
-// Inverse: each wave inverts one 16x16 diagonal triangle by forward
-// substitution (lane = column; the diagonal of L^{-1} is the 1/l_jj of the
-// factorization), then the 2x2 block formula for a lower triangle,
-//   inv [L11 0; L21 L22] = [X11 0; -X22 L21 X11  X22],
-// on the 16-blocks inside each 32-block and then on the two 32-blocks, the
-// products on MFMA tiles.  L stays in the lower triangle of A; the strict
-// lower part of L^{-1} is kept transposed in the strict upper triangle
-// (A[c][a] = Linv[a][c]) and its diagonal in rdg.  A pivot that is not
-// positive and finite lowers the status word to its global column.
-// L^{-1} is stored column-major: Linv[ioff + k * nb + i] = (L^{-1})_ik.
-// ---------------------------------------------------------------------------
 template <typename T>
 __device__ __forceinline__ T lane_read(T v, int src);
 template <>
@@ -189,16 +169,6 @@ __device__ __forceinline__ float rsqrt_nr(float d) {
     return y * (1.5f - 0.5f * d * y * y);
 }
 
-// Bounded wait on an LDS word written by another wave of the workgroup
-// (all of whose waves are resident, so the wait ends unless the code is
-// wrong; the bound keeps even that from hanging the device).
-__device__ __forceinline__ bool lds_wait_geq(int *f, int v) {
-    for (int it = 0; it < (1 << 22); ++it) {
-        if (__hip_atomic_load(f, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP) >= v) return true;
-        __builtin_amdgcn_s_sleep(1);
-    }
-    return false;
-}
 // Completes a wave's own LDS operations (and keeps the compiler from moving
 // memory accesses across), so its later LDS reads of other lanes' data, and
 // other waves after a flag, see them.  Global memory operations in flight
@@ -208,324 +178,371 @@ __device__ __forceinline__ void wave_lds_sync() {
     __builtin_amdgcn_s_waitcnt(0xc07f);  // lgkmcnt(0)
     __asm__ volatile("" ::: "memory");
 }
-__device__ __forceinline__ void lds_flag_store(int *f, int v) {
-    wave_lds_sync();
-    __hip_atomic_store(f, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+// Value of lane C of each row of 16 lanes, in every lane of that row.
+template <int C>
+__device__ __forceinline__ double row_bcast(double v) {
+    return __longlong_as_double(
+        __builtin_amdgcn_update_dpp(0ll, __double_as_longlong(v), 0x150 + C, 0xf, 0xf, true));
 }
-__device__ __forceinline__ void lds_flag_add(int *f) {
-    wave_lds_sync();
-    __hip_atomic_fetch_add(f, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+template <int C>
+__device__ __forceinline__ float row_bcast(float v) {
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x150 + C, 0xf, 0xf, true));
 }
 
-// Factor the block in A (nb <= 64; rows and columns >= nb hold the identity,
-// the upper triangle is zero), write L into P (columns c0.., leading
-// dimension m, lower triangle only) and the inverse into Vi; a failed pivot
-// lowers *status to g0 + its column.  LDS scratch from the caller: rdg (64
-// entries), Tf and T32 (32 x 33 each), flags (8 ints).  Called by all 256
-// threads of the workgroup.  With pflags (a full block, nb = 64), each
-// panel p is also handed to workgroups of the same launch: its L and the
-// inverse of its 16x16 diagonal triangle go out with device-scope atomic
-// stores, and each of waves 1-3 adds 1 to pflags[p] once its part has
-// completed (3 when the panel is out).
+// 1/d: hardware estimate and one correction step (of third order in double,
+// whose estimate is good to about 1e-8).
+__device__ __forceinline__ double rcp_nr(double d) {
+    const double y = __builtin_amdgcn_rcp(d), e = fma(-d, y, 1.0);
+    return fma(y, fma(e, e, e), y);
+}
+__device__ __forceinline__ float rcp_nr(float d) {
+    const float y = __builtin_amdgcn_rcpf(d);
+    return fmaf(y, fmaf(-d, y, 1.0f), y);
+}
+// Diagonals above `big` are scaled by `down` before an elimination that
+// takes 1/d, which would be subnormal near the top of the range.
+template <typename T>
+struct PivotRange;
+template <>
+struct PivotRange<double> {
+    static constexpr double big = 0x1p1000, down = 0x1p-512, root = 0x1p-256;
+};
+template <>
+struct PivotRange<float> {
+    static constexpr float big = 0x1p100f, down = 0x1p-64f, root = 0x1p-32f;
+};
+
+// Elimination steps C.. of a 16x16 diagonal tile, by one wave.  Every row of
+// 16 lanes holds the whole symmetric tile: t[k] of lane c is entry (k, c).
+// Step C: w = u_Cc / d_C for the lanes c > C, and every row k > C loses
+// u_kC w, u_kC broadcast inside the row of lanes; lane C keeps its column.
+// The same w updates NX row tiles below (x[4 u + v], in the layout of an
+// MFMA result: column = lane, so u_iC is a broadcast too), or, with INV, the
+// rows z of an identity, which end as the inverse of the unit triangle.
+// dl of lane C receives d_C.  The chain from pivot to pivot is a
+// reciprocal and four dependent multiply-adds; there is no square root in
+// it (the columns are scaled afterwards, all at once).
+template <typename T, int NX, bool INV, bool BOOST, int C>
+__device__ __forceinline__ void eliminate16(T (&t)[16], T (&x)[NX > 0 ? 4 * NX : 1], T (&z)[INV ? 16 : 1], T flo,
+                                            T &dl, int &boosted, int l16) {
+    if constexpr (C < 16) {
+        T d = row_bcast<C>(t[C]);
+        if constexpr (BOOST) {
+            const T f = row_bcast<C>(flo);
+            if (d < f) {  // a NaN compares false and fails the pivot check
+                d = f;
+                ++boosted;
+            }
+            t[C] = l16 == C ? d : t[C];
+        }
+        dl = l16 == C ? d : dl;
+        const T y = rcp_nr(d);
+        const T w = l16 > C ? t[C] * y : T(0);
+#pragma unroll
+        for (int k = C + 1; k < 16; ++k) t[k] -= row_bcast<C>(t[k]) * w;
+#pragma unroll
+        for (int e = 0; e < 4 * NX; ++e) x[e] -= row_bcast<C>(x[e]) * w;
+        if constexpr (INV) {
+            const T wz = z[C] * y;
+#pragma unroll
+            for (int k = C + 1; k < 16; ++k) z[k] -= row_bcast<C>(t[k]) * wz;
+            // z is off the chain: without this its updates are put off (into
+            // the block that stores z) and their broadcasts kept meanwhile,
+            // in more registers than there are
+#pragma unroll
+            for (int k = C + 1; k < 16; ++k) __asm__ volatile("" : "+v"(z[k]));
+        }
+        eliminate16<T, NX, INV, BOOST, C + 1>(t, x, z, flo, dl, boosted, l16);
+    }
+}
+template <typename T, int K>
+__device__ __forceinline__ void scale_rows16(T (&z)[16], T rs) {
+    if constexpr (K < 16) {
+        z[K] *= row_bcast<K>(rs);
+        scale_rows16<T, K + 1>(z, rs);
+    }
+}
+
+// LDS scratch of potrf_lds beside the block itself: the inverses of the four
+// 16x16 diagonal triangles, a tile for each wave but the second, and the
+// diagonal of L.
+template <typename T>
+struct PotrfLds {
+    T xd[4][16][17];
+    T tile[3][16][17];
+    T dg[kNB];
+};
+
+// Workgroups handing out one panel of a block: waves 2 and 3 add 1 each to
+// its flag once their part is out.
+constexpr int kPanelParts = 2;
+
+// Factor the block in A (nb <= 64; rows and columns >= nb hold the identity;
+// only the lower triangle is read, what is above the diagonal is scratch), write L into P (columns c0.., leading dimension m, lower triangle
+// only) and the inverse into Vi; a failed pivot lowers *status to g0 + its
+// column.  Called by all 256 threads of the workgroup.  With pflags (a full
+// block, nb = 64), each panel p is also handed to workgroups of the same
+// launch: its L and the inverse of its 16x16 diagonal triangle go out with
+// device-scope atomic stores, and each of waves 2 and 3 adds 1 to pflags[p]
+// once its part has completed (kPanelParts when the panel is out).
 //
-// Blocked by 16-column panels with lookahead: wave 0 factors panel p (lane
-// = row, pivots broadcast by readlane) right after bringing its columns up
-// to date with panel p-1 itself (16x16x4 MFMA), while waves 1-3 apply panel
-// p-1 to the columns two panels on and beyond; then wave 1 inverts its 16x16
-// diagonal triangle (and merges the second 32-column block's inverse after
-// the last panel), wave 2 merges the first 32-column block's inverse once
-// its two triangles are inverted, and waves 2-3 store L, so that the
-// inverses keep pace with the panels.  The waves hand over through LDS flags, so
-// the panel chain never waits for a whole-workgroup barrier.  Each trailing
-// tile belongs to one wave for all panels, so no tile is updated by two
-// waves at once.
+// Four 16-column panels, one workgroup barrier each.  In step p each of the
+// panel's tiles below the diagonal (at most three) has a wave of its own (0,
+// 2, 3): it brings the diagonal tile and its own up to date with panel p-1
+// (16x16x4 MFMA, its own tile staying in registers), eliminates both
+// (eliminate16; the diagonal tile by every such wave for itself, so nothing
+// crosses between waves inside a panel) and scales the columns.  Wave 1 does
+// the same for the diagonal tile with the identity beside it, which gives
+// the inverse of its triangle.  Waves 2 and 3 also hand out panel q = p-1,
+// apply it to the columns beyond panel p, and carry the block inverse on:
+//   X_qj = -X_qq S_qj,  then  S_ij += L_iq X_qj  for i > q  (j <= q),
+// with S_ij, later X_ij, in the tile (j, i) of A.  Only the last row's three
+// products remain after the last panel.
+// L^{-1} is stored column-major: Vi[k * nb + i] = (L^{-1})_ik.
+// Bound by the chain of 64 pivots.  The form before kept a panel's 16
+// columns in the registers of lane = row of one wave, its multipliers read
+// lane by lane into scalar registers, had a reciprocal square root in the
+// chain and the inverse after it; one block alone took 19.6 us (FP64) and
+// 16.9 (FP32) a launch, this one 12.6 and 11.3; the trailing launches of a
+// 34^3 grid's top levels (FP32) 21.7 and 18.4 on average.
 template <typename T, bool BOOST = false>
-__device__ __forceinline__ void potrf_lds(T (*A)[kNB + 1], T *rdg, T (*Tf)[33], T (*T32)[33], int *flags, int nb,
-                                          T *P, int64_t m, int c0, T *Vi, unsigned long long *status, int32_t *deverr,
-                                          int64_t g0, int32_t *pflags, PivotFloor<T> pfl = {}) {
-    constexpr int NB = kNB, PW = 16;
+__device__ __forceinline__ void potrf_lds(T (*A)[kNB + 1], PotrfLds<T> &W, int nb, T *P, int64_t m, int c0, T *Vi,
+                                          unsigned long long *status, int64_t g0, int32_t *pflags,
+                                          PivotFloor<T> pfl = {}) {
+    constexpr int PW = 16;
     using M = Mfma<T>;
     using acc_t = typename M::acc;
-    int &flag_panel = flags[0];   // panels 0 .. flag_panel - 1 are factored in A
-    int *flag_trail = flags + 1;  // [4] trailing waves done with panel p (0..3)
-    int &flag_err = flags[5];
-    int &flag_x11 = flags[6];     // inverse of the first 32-column block done
-    int &flag_dinv = flags[7];    // diagonal 16x16 triangles 0 .. flag_dinv - 1 inverted
-    // T32: L21 X11 of the two 32-column blocks
-    const int t = threadIdx.x, lane = t & 63;
+    using R = PivotRange<T>;
+    const int t = threadIdx.x;
+    int lane = t & 63, l16 = lane & 15, lg = lane >> 4;
+    // hides the lane's indices from the optimizer, so that the addresses of
+    // one wave's role are not computed ahead of the loop by all of them
+    auto fresh = [&] { __asm__ volatile("" : "+v"(lane), "+v"(l16), "+v"(lg)); };
     const int wv = __builtin_amdgcn_readfirstlane(t >> 6);
     const int npan = (nb + PW - 1) / PW;
-    if (t == 0) {
-        flag_panel = 0;
-        flag_trail[0] = flag_trail[1] = flag_trail[2] = flag_trail[3] = 0;
-        flag_err = 0;
-        flag_x11 = 0;
-        flag_dinv = 0;
-    }
-    if (t >= PW * npan && t < NB) rdg[t] = T(1);  // identity rows past the last panel
-    __syncthreads();
-#define SPC_INV(a, c) ((c) < (a) ? A[c][a] : ((c) == (a) ? rdg[a] : T(0)))
-    auto vi_put = [&](int64_t e, T v) { Vi[e] = v; };
-    // one wave's part of a panel is out: its stores have completed
-    auto panel_out = [&](int pb) {
-        __builtin_amdgcn_s_waitcnt(0);
-        if (lane == 0) __hip_atomic_fetch_add(pflags + pb, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    };
-    // inverse of the 32-column block at o from its two 16-block inverses
-    // (one wave): X21 = -X22 L21 X11, kept transposed in the upper triangle
-    auto inv16 = [&](int o) {
-        const int tr = o >> 1;  // Tf rows tr .. tr + 15
-        acc_t acc = {0, 0, 0, 0};  // L21 X11
-#pragma unroll
-        for (int kk = 0; kk < 16; kk += 4)
-            acc = M::run(A[o + 16 + (lane & 15)][o + kk + (lane >> 4)], SPC_INV(o + kk + (lane >> 4), o + (lane & 15)),
-                         acc);
-#pragma unroll
-        for (int v = 0; v < 4; ++v) Tf[tr + M::row(lane, v)][lane & 15] = acc[v];
-        wave_lds_sync();
-        acc = acc_t{0, 0, 0, 0};  // X22 (L21 X11)
-#pragma unroll
-        for (int kk = 0; kk < 16; kk += 4)
-            acc = M::run(SPC_INV(o + 16 + (lane & 15), o + 16 + kk + (lane >> 4)), Tf[tr + kk + (lane >> 4)][lane & 15],
-                         acc);
-#pragma unroll
-        for (int v = 0; v < 4; ++v) A[o + (lane & 15)][o + 16 + M::row(lane, v)] = -acc[v];
-        wave_lds_sync();
-    };
     int bad = -1;  // wave 0: first pivot (block column) that failed
     int boosted = 0;
-    if (wv == 0) {
-        const int i = lane;
-        // pivot floors of this block's columns (lane = column), read off the chain
-        const T flo = BOOST ? pfl.v[g0 + min(lane, nb - 1)] : T(0);
-        for (int pb = 0; pb < npan; ++pb) {
-            const int p0 = PW * pb;
-            if (pb >= 2 && !lds_wait_geq(&flag_trail[pb - 2], 3)) flag_err = 1;
-            if (pb >= 1) {
-                // this panel's columns (rows >= p0) minus panel pb-1's
-                // product: up to three 16-row tiles, their loads, products
-                // and updates each issued together
-                const int q0 = p0 - PW;
-                T bop[4], aop[3][4], cold[3][4];
-                acc_t acc[3];
+    // rows 16 ti.. and columns 16 tj.. of L L^T over panel q (as a result
+    // tile: this lane's column 16 tj + l16)
+    auto outer = [&](int ti, int tj, int q) {
+        acc_t acc[2] = {acc_t{0, 0, 0, 0}, acc_t{0, 0, 0, 0}};
 #pragma unroll
-                for (int kk = 0; kk < 4; ++kk) bop[kk] = A[p0 + (lane & 15)][q0 + 4 * kk + (lane >> 4)];
+        for (int kk = 0; kk < PW; kk += 4)
+            acc[kk >> 3] =
+                M::run(A[16 * ti + l16][PW * q + kk + lg], A[16 * tj + l16][PW * q + kk + lg], acc[kk >> 3]);
+        return acc[0] + acc[1];
+    };
+    // panel p: the diagonal tile, with the identity (wave 1) or with the tile
+    // of rows 16 ti .. (ti > p; ti = p: none)
+    auto panel = [&](int p, int ti, auto nxc, auto invc) {
+        constexpr int NX = decltype(nxc)::value;
+        constexpr bool INV = decltype(invc)::value;
+        const int p0 = PW * p;
+        T tt[16], x[NX > 0 ? 4 * NX : 1], z[INV ? 16 : 1], dl = T(1);
+        // (xd[p] is written by wave 1 alone)
+        T(*D)[17] = INV ? W.xd[p] : W.tile[wv == 0 ? 0 : wv - 1];
+        T dmax;
+        if (p > 0) {
+            const acc_t a0 = outer(p, p, p - 1);
+            T cold[4];
 #pragma unroll
-                for (int x = 0; x < 3; ++x) {
-                    const int tt = min(pb + x, 3);
-#pragma unroll
-                    for (int kk = 0; kk < 4; ++kk) aop[x][kk] = A[16 * tt + (lane & 15)][q0 + 4 * kk + (lane >> 4)];
-#pragma unroll
-                    for (int v = 0; v < 4; ++v) cold[x][v] = A[16 * tt + M::row(lane, v)][p0 + (lane & 15)];
-                }
-#pragma unroll
-                for (int x = 0; x < 3; ++x) {
-                    acc[x] = acc_t{0, 0, 0, 0};
-#pragma unroll
-                    for (int kk = 0; kk < 4; ++kk) acc[x] = M::run(aop[x][kk], bop[kk], acc[x]);
-                }
-#pragma unroll
-                for (int x = 0; x < 3; ++x) {
-                    const int tt = pb + x;
-                    if (tt < npan)
-#pragma unroll
-                        for (int v = 0; v < 4; ++v) {
-                            const int r = 16 * tt + M::row(lane, v), c = p0 + (lane & 15);
-                            if (r >= c) A[r][c] = cold[x][v] - acc[x][v];
-                        }
-                }
-                wave_lds_sync();
+            for (int v = 0; v < 4; ++v) {
+                const int r = M::row(lane, v);
+                cold[v] = A[p0 + max(r, l16)][p0 + min(r, l16)];
             }
-            T r[PW];
+            if constexpr (NX > 0)
 #pragma unroll
-            for (int c = 0; c < PW; ++c) r[c] = A[i][p0 + c];
+                for (int v = 0; v < 4; ++v) x[v] = A[16 * ti + M::row(lane, v)][p0 + l16];
 #pragma unroll
-            for (int c = 0; c < PW; ++c) {
-                const int j = p0 + c;
-                T d = lane_read(r[c], j);
-                if (BOOST) {
-                    const T fj = lane_read(flo, j);
-                    if (d < fj && j < nb) {  // a NaN compares false and still fails below
-                        d = fj;
-                        ++boosted;
-                    }
-                }
-                if (bad < 0 && j < nb && !finite_pos(d)) bad = j;
-                const T rs = rsqrt_nr(d);
-                if (i == j) rdg[j] = rs;
-                const T lij = (i == j) ? d * rs : r[c] * rs;
-                r[c] = lij;
+            for (int v = 0; v < 4; ++v) D[M::row(lane, v)][l16] = cold[v] - a0[v];
+            if constexpr (NX > 0) {
+                const acc_t ax = outer(ti, p, p - 1);
 #pragma unroll
-                for (int c2 = c + 1; c2 < PW; ++c2) r[c2] -= lij * lane_read(lij, p0 + c2);
+                for (int v = 0; v < 4; ++v) x[v] -= ax[v];
             }
-            // rows >= p0 in full: the entries above the diagonal hold
-            // scratch until the inverse levels overwrite every one of them
-            if (i >= p0)
+            wave_lds_sync();
 #pragma unroll
-                for (int c = 0; c < PW; ++c) A[i][p0 + c] = r[c];
-            lds_flag_store(&flag_panel, pb + 1);
+            for (int k = 0; k < 16; ++k) tt[k] = D[k][l16];
+            dmax = D[l16][l16];
+        } else {
+#pragma unroll
+            for (int k = 0; k < 16; ++k) tt[k] = A[max(k, l16)][min(k, l16)];
+            if constexpr (NX > 0)
+#pragma unroll
+                for (int v = 0; v < 4; ++v) x[v] = A[16 * ti + M::row(lane, v)][l16];
+            dmax = A[l16][l16];
         }
-    } else {
-        const int tw = wv - 1;  // trailing wave 0..2
-        for (int pb = 0; pb < npan; ++pb) {
-            const int p0 = PW * pb;
-            if (!lds_wait_geq(&flag_panel, pb + 1)) flag_err = 1;
-            // panel pb applied to the tiles (ti, tj), tj >= pb + 2, lower part;
-            // tile x = ti (ti + 1) / 2 + tj belongs to trailing wave x % 3
-            for (int x = tw; x < 10; x += 3) {
-                int ti = 0;
-                while ((ti + 1) * (ti + 2) / 2 <= x) ++ti;
-                const int tj = x - ti * (ti + 1) / 2;
-                if (tj < pb + 2 || ti >= npan) continue;
-                const int i0 = 16 * ti, j0 = 16 * tj;
-                acc_t acc = {0, 0, 0, 0};
+        T flo = BOOST ? (p0 + l16 < nb ? pfl.v[g0 + p0 + l16] : T(0)) : T(0);
+        T up = T(1), dn = T(1);
+        if (__any(dmax > R::big)) {  // near the top of the type's range
 #pragma unroll
-                for (int kk = 0; kk < PW; kk += 4)
-                    acc = M::run(A[i0 + (lane & 15)][p0 + kk + (lane >> 4)], A[j0 + (lane & 15)][p0 + kk + (lane >> 4)],
-                                 acc);
+            for (int k = 0; k < 16; ++k) tt[k] *= R::down;
 #pragma unroll
-                for (int v = 0; v < 4; ++v) {
-                    const int r = i0 + M::row(lane, v), c = j0 + (lane & 15);
-                    if (r >= c) A[r][c] -= acc[v];
-                }
-            }
-            if (lane == 0) lds_flag_add(&flag_trail[pb]);
-            else wave_lds_sync();
-            if (wv == 1) {
-                // inverse of panel pb's diagonal 16x16 triangle: 2x2 block
-                // formula from the diagonal (rdg = 1/l_jj) up, h = 1, 2, 4, 8;
-                // X21 is kept transposed in the upper triangle.  Scratch:
-                // rows 16.. of Tf (rows 0..15 belong to the merge of the
-                // first 32-column block, which wave 2 may be running)
-                T *tf = &Tf[16][0];
-                // fixed trip counts (h unrolled, terms masked) so each
-                // level issues its LDS reads together; lanes >= 8 h compute
-                // a clamped copy and store nothing
+            for (int e = 0; e < 4 * NX; ++e) x[e] *= R::down;
+            flo *= R::down;
+            up = T(1) / R::root;
+            dn = R::root;
+        }
+        if constexpr (INV)
 #pragma unroll
-                for (int lv = 0; lv < 4; ++lv) {
-                    const int h = 1 << lv, nel = 8 * h;  // 16 / (2h) blocks of h x h
-                    const int ln = min(lane, nel - 1);
-                    const int blk = ln / (h * h), rem = ln % (h * h), a = rem % h, b = rem / h, o = p0 + 2 * h * blk;
-                    T acc = T(0);  // (L21 X11)[a][b]
+            for (int k = 0; k < 16; ++k) z[k] = k == l16 ? T(1) : T(0);
+        eliminate16<T, NX, INV, BOOST, 0>(tt, x, z, flo, dl, boosted, l16);
+        const T rs = rsqrt_nr(dl);
+        if constexpr (INV) {
+            scale_rows16<T, 0>(z, rs * dn);
+            if (lane < 16)
 #pragma unroll
-                    for (int c = 0; c < h; ++c) {
-                        const T l = A[o + h + a][o + c], x = SPC_INV(o + c, o + b);
-                        acc += (c >= b) ? l * x : T(0);
-                    }
-                    if (lane < nel) tf[lane] = acc;
-                    wave_lds_sync();
-                    T out = T(0);  // -(X22 (L21 X11))[a][b]
+                for (int k = 0; k < 16; ++k) D[k][l16] = z[k];
+        } else {
+            const T ls = rs * up;
+            if constexpr (NX > 0)
 #pragma unroll
-                    for (int c = 0; c < h; ++c) {
-                        const T x = SPC_INV(o + h + a, o + h + c), u = tf[blk * h * h + b * h + c];
-                        out -= (c <= a) ? x * u : T(0);
-                    }
-                    wave_lds_sync();
-                    if (lane < nel) A[o + b][o + h + a] = out;
-                    wave_lds_sync();
-                }
-                lds_flag_store(&flag_dinv, pb + 1);
-                if (pflags) {
-                    // the panel's diagonal 16x16 block of the inverse
+                for (int v = 0; v < 4; ++v) A[16 * ti + M::row(lane, v)][p0 + l16] = x[v] * ls;
+            if (wv == 0) {
+                const unsigned long long fail = __ballot(!finite_pos(dl) && lane < 16 && p0 + lane < nb);
+                if (fail && bad < 0) bad = p0 + __builtin_ctzll(fail);
+                // L of the diagonal tile, transposed, above the diagonal, and
+                // its diagonal apart: another wave may still have to read the
+                // tile's values before the elimination
+                if (lane < 16) {
+                    W.dg[p0 + l16] = dl * ls;
 #pragma unroll
-                    for (int q = 0; q < PW * PW / 64; ++q) {
-                        const int e = lane + 64 * q, i = p0 + e % PW, k = p0 + e / PW;
-                        dev_store(Vi + k * nb + i, SPC_INV(i, k));
-                    }
-                    panel_out(pb);
-                }
-                // the second 32-column block (its second 16-block may be
-                // identity padding) is merged right after its last panel
-                if (pb >= 2 && pb == npan - 1) inv16(32);
-            } else {
-                // waves 2 and 3 store L of panel pb (rows >= p0 of its
-                // columns), so that wave 1 keeps up with the panels
-                for (int e = lane + 64 * (wv - 2); e < PW * NB; e += 128) {
-                    const int k = p0 + e / NB, row = e % NB;
-                    if (k < nb && row >= k && row < nb) {
-                        T *dst = P + (int64_t)(c0 + k) * m + c0 + row;
-                        if (pflags) dev_store(dst, A[row][k]);
-                        else *dst = A[row][k];
-                    }
-                }
-                if (pflags) panel_out(pb);
-            }
-            if (pb == 1 && wv == 2) {
-                // the first 32-column block: merge its two inverted
-                // 16-blocks once wave 1 has both
-                if (!lds_wait_geq(&flag_dinv, 2)) flag_err = 1;
-                inv16(0);
-                lds_flag_store(&flag_x11, 1);
-            }
-            if (pb == 1 && nb > 2 * PW && wv >= 2) {
-                // the first 32-column block's inverse X11 is final: wave 2
-                // forms L21 X11 for the last merge, wave 3 stores the
-                // inverse's first 32 rows (X11, zeros to its right)
-                if (!lds_wait_geq(&flag_x11, 1)) flag_err = 1;
-                if (wv == 2) {
-#pragma unroll
-                    for (int tt = 0; tt < 4; ++tt) {
-                        const int ti = tt >> 1, tj = tt & 1;
-                        acc_t acc = {0, 0, 0, 0};
-#pragma unroll
-                        for (int kk = 0; kk < 32; kk += 4)
-                            acc = M::run(A[32 + 16 * ti + (lane & 15)][kk + (lane >> 4)],
-                                         SPC_INV(kk + (lane >> 4), 16 * tj + (lane & 15)), acc);
-#pragma unroll
-                        for (int v = 0; v < 4; ++v) T32[16 * ti + M::row(lane, v)][16 * tj + (lane & 15)] = acc[v];
-                    }
-                } else {
-                    for (int e = lane; e < 32 * nb; e += 64) {
-                        const int i = e & 31, k = e >> 5;
-                        vi_put(k * nb + i, SPC_INV(i, k));
-                    }
+                    for (int k = 1; k < 16; ++k)
+                        if (k > l16) A[p0 + l16][p0 + k] = tt[k] * ls;
                 }
             }
         }
-    }
-    __syncthreads();
-    if (wv == 0 && lane == 0) {
-        if (bad >= 0) atomicMin(status, (unsigned long long)(g0 + bad));
-        if (flag_err) flag_device_error(deverr);
-        if (BOOST && boosted) atomicAdd(pfl.count, boosted);
-    }
-    if (nb > 32) {
-        // the two 32-blocks: X21 = -X22 (L21 X11), wave w the 16x16 tile
-        // (w / 2, w % 2); the first 32 rows of the inverse are stored already
-        const int ti = wv >> 1, tj = wv & 1;
-        acc_t acc = {0, 0, 0, 0};
+    };
+    // waves 2 and 3 (h = 0, 1): panel q goes out
+    auto store = [&](T *dst, T v) {
+        if (pflags) dev_store(dst, v);
+        else *dst = v;
+    };
+    auto hand_out = [&](int q, int h) {
+        // columns k0 .. k0 + 7, lane = row
+        const int k0 = PW * q + 8 * h;
+        T v[8];
 #pragma unroll
-        for (int kk = 0; kk < 32; kk += 4)
-            acc = M::run(SPC_INV(32 + 16 * ti + (lane & 15), 32 + kk + (lane >> 4)),
-                         T32[kk + (lane >> 4)][16 * tj + (lane & 15)], acc);
+        for (int e = 0; e < 8; ++e) {
+            const int k = k0 + e;
+            v[e] = *(lane == k ? &W.dg[k] : (lane >> 4 == q ? &A[k][lane] : &A[lane][k]));
+        }
+        T *dst = P + (int64_t)(c0 + k0) * m + c0 + lane;
 #pragma unroll
-        for (int v = 0; v < 4; ++v) A[16 * tj + (lane & 15)][32 + 16 * ti + M::row(lane, v)] = -acc[v];
+        for (int e = 0; e < 8; ++e)
+            if (k0 + e < nb && lane >= k0 + e && lane < nb) store(dst + e * m, v[e]);
+        if (pflags)  // the panel's diagonal 16x16 block of the inverse (full blocks)
+#pragma unroll
+            for (int e = 0; e < 2; ++e) {
+                const int k = 8 * h + 4 * e + lg;
+                dev_store(Vi + (PW * q + k) * nb + PW * q + l16, W.xd[q][l16][k]);
+            }
+    };
+    auto flag_out = [&](int q) {
+        if (!pflags) return;
+        __builtin_amdgcn_s_waitcnt(0);
+        if (lane == 0) __hip_atomic_fetch_add(pflags + q, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    };
+    // X_qj = -X_qq S_qj, in place in the tile (j, q) of A
+    auto inverse_tile = [&](int q, int j) {
+        acc_t acc[2] = {acc_t{0, 0, 0, 0}, acc_t{0, 0, 0, 0}};
+#pragma unroll
+        for (int kk = 0; kk < PW; kk += 4)
+            acc[kk >> 3] = M::run(W.xd[q][l16][kk + lg], A[PW * j + kk + lg][PW * q + l16], acc[kk >> 3]);
+#pragma unroll
+        for (int v = 0; v < 4; ++v) A[PW * j + M::row(lane, v)][PW * q + l16] = -(acc[0][v] + acc[1][v]);
+    };
+    // S_ij += L_iq X_qj (a new sum for q = j), the tile (j, i) of A
+    auto inverse_sum = [&](int i, int q, int j) {
+        acc_t acc[2] = {acc_t{0, 0, 0, 0}, acc_t{0, 0, 0, 0}};
+        if (q > j)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) acc[0][v] = A[PW * j + M::row(lane, v)][PW * i + l16];
+#pragma unroll
+        for (int kk = 0; kk < PW; kk += 4)
+            acc[kk >> 3] = M::run(A[PW * i + l16][PW * q + kk + lg],
+                                  q == j ? W.xd[q][kk + lg][l16] : A[PW * j + kk + lg][PW * q + l16], acc[kk >> 3]);
+#pragma unroll
+        for (int v = 0; v < 4; ++v) A[PW * j + M::row(lane, v)][PW * i + l16] = acc[0][v] + acc[1][v];
+    };
+    // rows 16 r .. of the block inverse to memory, by NTH threads (th)
+    auto store_inverse_rows = [&](int r, int th, auto nthc) {
+        constexpr int NTH = decltype(nthc)::value, N = PW * kNB / NTH;
+        T v[N];
+#pragma unroll
+        for (int u = 0; u < N; ++u) {
+            const int e = th + NTH * u, a = e & 15, k = e >> 4, tk = k >> 4, b = k & 15;
+            const T *src = tk == r ? &W.xd[r][a][b] : &A[PW * min(tk, r) + a][PW * r + b];
+            v[u] = tk <= r ? *src : T(0);
+        }
+#pragma unroll
+        for (int u = 0; u < N; ++u) {
+            const int e = th + NTH * u, i = PW * r + (e & 15), k = e >> 4;
+            if (i < nb && k < nb) Vi[k * nb + i] = v[u];
+        }
+    };
+    using Int0 = std::integral_constant<int, 0>;
+    using Int1 = std::integral_constant<int, 1>;
+    for (int p = 0; p < npan; ++p) {
+        fresh();
+        const int ti = p + (wv == 0 ? 1 : wv);  // this wave's tile below the diagonal
+        if (wv == 1) panel(p, p, Int0{}, std::true_type{});
+        else if (ti < npan) panel(p, ti, Int1{}, std::false_type{});
+        else if (wv == 0) panel(p, p, Int0{}, std::false_type{});
+        if (p > 0 && wv >= 2) {
+            const int h = wv - 2, q = p - 1;
+            fresh();
+            hand_out(q, h);
+            // panel q applied to the tiles (i, j), j > p, and the next rows of
+            // the block inverse (columns j of its tiles: wave 3 - j % 2); in
+            // step 1 wave 2 has a tile of the panel and wave 3 does both
+            int x = 0;
+            for (int i = p + 1; i < npan; ++i)
+                for (int j = p + 1; j <= i; ++j, ++x) {
+                    if (p == 1 ? h == 0 : (x & 1) == h) continue;
+                    const acc_t acc = outer(i, j, q);
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) A[16 * i + M::row(lane, v)][16 * j + l16] -= acc[v];
+                }
+            flag_out(q);
+            for (int j = 1 - h; j <= q; j += 2) {
+                if (j < q) {
+                    inverse_tile(q, j);
+                    wave_lds_sync();
+                }
+                for (int i = p; i < npan; ++i) inverse_sum(i, q, j);
+            }
+            if (p > 1) store_inverse_rows(p - 2, lane + 64 * h, std::integral_constant<int, 128>{});
+        }
         __syncthreads();
-#pragma unroll
-        for (int q = 0; q < 32 * NB / 256; ++q) {
-            const int e = t + 256 * q, i = 32 + e % 32, k = e / 32;
-            if (i < nb && k < nb) vi_put(k * nb + i, SPC_INV(i, k));
-        }
-    } else {
-#pragma unroll
-        for (int q = 0; q < NB * NB / 256; ++q) {
-            const int e = t + 256 * q, i = e % NB, k = e / NB;
-            if (i < nb && k < nb) vi_put(k * nb + i, SPC_INV(i, k));
-        }
     }
-#undef SPC_INV
+    fresh();
+    const int q = npan - 1;
+    if (wv >= 2) {
+        hand_out(q, wv - 2);
+        flag_out(q);
+        if (wv == 3 && q == 3) inverse_tile(q, 2);
+    } else if (wv < q) {
+        inverse_tile(q, wv);
+    }
+    if (t == 0 && bad >= 0) atomicMin(status, (unsigned long long)(g0 + bad));
+    if (BOOST && t == 0 && boosted) atomicAdd(pfl.count, boosted);
+    __syncthreads();
+    if (q > 0) store_inverse_rows(q - 1, t, std::integral_constant<int, 256>{});
+    store_inverse_rows(q, t, std::integral_constant<int, 256>{});
 }
 
+// ---------------------------------------------------------------------------
+// k_potrf: one workgroup per diagonal block (nb <= kNB = 64), held in LDS
+// (potrf_lds).
+// ---------------------------------------------------------------------------
 template <typename T, bool BOOST>
 __global__ __launch_bounds__(256) void k_potrf(const PanelTask *tasks, T *Lx, T *Linv,
                                                unsigned long long *status, const int32_t *status_slot,
-                                               int32_t *deverr, PivotFloor<T> pfl) {
+                                               PivotFloor<T> pfl) {
     constexpr int NB = kNB;
     __shared__ T A[NB][NB + 1];
-    __shared__ T rdg[NB];
-    __shared__ T Tf[32][33];
-    __shared__ T T32[32][33];
-    __shared__ int flags[8];
+    __shared__ PotrfLds<T> W;
     const PanelTask tk = tasks[blockIdx.x];
     const int64_t m = tk.m;
     const int c0 = tk.c0, nb = tk.c1 - tk.c0;
@@ -546,8 +563,8 @@ __global__ __launch_bounds__(256) void k_potrf(const PanelTask *tasks, T *Lx, T 
         }
     }
     __syncthreads();
-    potrf_lds<T, BOOST>(A, rdg, Tf, T32, flags, nb, P, m, c0, Linv + tk.ioff,
-                        status + (status_slot ? status_slot[tk.s] : 0), deverr, tk.g0, nullptr, pfl);
+    potrf_lds<T, BOOST>(A, W, nb, P, m, c0, Linv + tk.ioff, status + (status_slot ? status_slot[tk.s] : 0), tk.g0,
+                        nullptr, pfl);
 }
 
 // ---------------------------------------------------------------------------
@@ -1375,10 +1392,8 @@ __global__ __launch_bounds__(256, 3) void k_tiles(const TileTask *tasks, const i
         // LDS for the factorization: the tile buffers, free now (cb and cr
         // hold no scatter addresses in this mode)
         T(*A)[TM + 1] = Cs;
-        T *rdg = reinterpret_cast<T *>(cb);
-        int *flags = reinterpret_cast<int *>(cr);
-        T(*Tf)[33] = reinterpret_cast<T(*)[33]>(&Bs[0][0]);
-        T(*T32)[33] = reinterpret_cast<T(*)[33]>(&As[0][0]);
+        static_assert(sizeof(PotrfLds<T>) <= sizeof(ABs), "the factorization's scratch fits the chunk buffers");
+        PotrfLds<T> &W = *reinterpret_cast<PotrfLds<T> *>(&ABs[0][0][0]);
 #pragma unroll
         for (int cc = 0; cc < CPT; ++cc) {
             const int c = cg * CPT + cc;
@@ -1388,9 +1403,8 @@ __global__ __launch_bounds__(256, 3) void k_tiles(const TileTask *tasks, const i
         // with a flag, each panel goes to the tiles below as it comes out
         // (also after a failed pivot, which the status word reports, so
         // that no tile waits in vain)
-        potrf_lds<T, BF>(A, rdg, Tf, T32, flags, nb2, P, m, tk.j0, Linv + tk.aux,
-                         status + (status_slot ? status_slot[tk.s] : 0), wctl.err, tk.blk,
-                         tk.flag >= 0 ? hflags + kFlagsPerBlock * tk.flag : nullptr, pfl);
+        potrf_lds<T, BF>(A, W, nb2, P, m, tk.j0, Linv + tk.aux, status + (status_slot ? status_slot[tk.s] : 0),
+                         tk.blk, tk.flag >= 0 ? hflags + kFlagsPerBlock * tk.flag : nullptr, pfl);
         return;
     }
     if (MODE == MODE_TRAILING && tk.flag >= 0) {
@@ -1399,7 +1413,7 @@ __global__ __launch_bounds__(256, 3) void k_tiles(const TileTask *tasks, const i
         // columns at a time as the block's panels come out: X_p = C_p
         // L_pp^{-T}, then C_q -= X_p L_qp^T for the later panels q.  Each
         // wave owns 16 rows of the tile, so the waves never wait for each
-        // other, only for the panel flags (3 once a panel is out).
+        // other, only for the panel flags (kPanelParts once a panel is out).
         static_assert(TM == kNB && TM == 64, "four 16-column panels per block");
 #pragma unroll
         for (int cc = 0; cc < CPT; ++cc) Cs[cg * CPT + cc][r] = old[cc] - Cs[cg * CPT + cc][r];
@@ -1414,7 +1428,7 @@ __global__ __launch_bounds__(256, 3) void k_tiles(const TileTask *tasks, const i
             // wait for panel p (every lane reads the same word: one load)
             bool ready = false;
             for (int it = 0; ok && it < wctl.spin; ++it) {
-                if (__builtin_amdgcn_readfirstlane(dev_load(pf + p)) >= 3) {
+                if (__builtin_amdgcn_readfirstlane(dev_load(pf + p)) >= kPanelParts) {
                     ready = true;
                     break;
                 }
@@ -2940,14 +2954,14 @@ void launch_pivot_floor(const DevPlan &P, int64_t n, const double *values, doubl
 
 template <typename T>
 void launch_potrf(const DevPlan &P, int64_t t0, int64_t t1, T *Lx, T *Linv, unsigned long long *status,
-                  int32_t *deverr, PivotFloor<T> pfl, hipStream_t st) {
+                  PivotFloor<T> pfl, hipStream_t st) {
     if (t1 <= t0) return;
     if (pfl.v)
         hipLaunchKernelGGL((k_potrf<T, true>), dim3((unsigned)(t1 - t0)), dim3(256), 0, st, P.potrf_tasks + t0, Lx,
-                           Linv, status, P.status_slot, deverr, pfl);
+                           Linv, status, P.status_slot, pfl);
     else
         hipLaunchKernelGGL((k_potrf<T, false>), dim3((unsigned)(t1 - t0)), dim3(256), 0, st, P.potrf_tasks + t0, Lx,
-                           Linv, status, P.status_slot, deverr, pfl);
+                           Linv, status, P.status_slot, pfl);
 }
 
 template <typename T>
@@ -3251,7 +3265,7 @@ template void launch_zero<unsigned long long>(unsigned long long *, int64_t, hip
     template void launch_zero<T>(T *, int64_t, hipStream_t);                                                \
     template void launch_assemble<T>(const DevPlan &, int64_t, const double *, T *, hipStream_t);           \
     template void launch_potrf<T>(const DevPlan &, int64_t, int64_t, T *, T *, unsigned long long *,         \
-                                  int32_t *, PivotFloor<T>, hipStream_t);                                   \
+                                  PivotFloor<T>, hipStream_t);                                              \
     template void launch_pivot_floor<T>(const DevPlan &, int64_t, const double *, double, T *, hipStream_t); \
     template void launch_tiles<T>(const DevPlan &, int, int64_t, int64_t, T *, T *, unsigned long long *,    \
                                   int32_t *, WaitCtl, bool, PivotFloor<T>, hipStream_t);                    \

@@ -122,3 +122,25 @@ def test_small_supernode_shapes(lib, w, b, persist, precision):
     err, eta, S = factor_and_solve(lib, arrow(w, b), {"tiny_w": -1, "persist": persist}, precision)
     print(f"w={w} b={b} persist={persist} {precision}: worst supernode {err:.2e}, eta {eta:.2e}", flush=True)
     assert S.nsuper == 3 and err <= (1e-10 if precision == "fp64" else 1e-4) and eta <= BAR[precision]
+
+
+@pytest.mark.parametrize("precision", ["fp64", "fp32"])
+@pytest.mark.parametrize("n", [1, 15, 16, 17, 31, 33, 48, 49, 63, 64, 65, 80, 127, 129, 193])
+def test_diagonal_block_shapes(lib, n, precision):
+    """The factorization of a 64-column block at one to four 16-column panels,
+    full and ragged, alone and after other blocks of its supernode."""
+    err, eta, S = factor_and_solve(lib, dense(n), BLOCKED, precision)
+    print(f"n={n} {precision}: worst supernode {err:.2e}, eta {eta:.2e}", flush=True)
+    assert err <= (1e-10 if precision == "fp64" else 1e-4) and eta <= BAR[precision]
+
+
+@pytest.mark.parametrize("precision,scale", [("fp64", 2.0 ** 1010), ("fp64", 2.0 ** -1000), ("fp32", 2.0 ** 119),
+                                             ("fp32", 2.0 ** -110)])
+@pytest.mark.parametrize("tuning", [{}, BLOCKED], ids=["small", "blocked"])
+def test_values_near_the_ends_of_the_range(lib, tuning, precision, scale):
+    """Pivots near the largest and smallest normal numbers of the precision:
+    the factor scales with the square root of the matrix."""
+    colptr, rowidx, values, perm = arrow(20, 30)
+    err, _, _ = factor_and_solve(lib, (colptr, rowidx, values * scale, perm), tuning, precision)
+    print(f"{precision} scale {scale:.1e} {tuning}: worst supernode {err:.2e}", flush=True)
+    assert err <= (1e-10 if precision == "fp64" else 1e-4)
