@@ -363,20 +363,27 @@ void enqueue_factor(const spc::Symbolic &S, const spc::DevPlan &P, const double 
     }
     for (int32_t l = 0; l < S.nlevels; ++l) {
         prof.level = l;
-        if (S.tiny_ptr[l + 1] > S.tiny_ptr[l])
-            prof.run(SPC_K_TINY, S.tiny_flops[l], st, [&] {
-                spc::launch_tiny<T>(P, S.tiny_ptr[l], S.tiny_e16[l], S.tiny_e32[l], S.tiny_ptr[l + 1], Lx, Linv,
-                                    status, pfl, st);
-            });
-        if (S.small_ptr[l + 1] > S.small_ptr[l])
-            prof.run(SPC_K_SMALL, S.small_flops[l], st, [&] {
-                spc::launch_small<T>(P, S.small_ptr[l], S.small_ptr[l + 1], Lx, Linv, status, pfl, st);
-            });
-        for (int64_t k = S.level_step_ptr[l]; k < S.level_step_ptr[l + 1]; ++k) {
+        const int64_t k0 = S.level_step_ptr[l], k1 = S.level_step_ptr[l + 1];
+        const int64_t f0 = k1 > k0 ? S.steps[k0].f0 : 0, f1 = k1 > k0 ? S.steps[k0].f1 : 0;
+        const int64_t s0 = S.small_ptr[l], s1 = S.small_ptr[l + 1];
+        const spc::TinyRange tiny{S.tiny_ptr[l], S.tiny_e16[l], S.tiny_e32[l], S.tiny_ptr[l + 1]};
+        const spc::TinyRange none{tiny.t0, tiny.t0, tiny.t0, tiny.t0};
+        if (prof.f && prof.f->profiling) {
+            // one launch per class, so that each can be timed
+            if (tiny.t1 > tiny.t0)
+                prof.run(SPC_K_TINY, S.tiny_flops[l], st,
+                         [&] { spc::launch_level<T>(P, f0, f0, s0, s0, tiny, Lx, Linv, status, pfl, st); });
+            if (s1 > s0)
+                prof.run(SPC_K_SMALL, S.small_flops[l], st,
+                         [&] { spc::launch_level<T>(P, f0, f0, s0, s1, none, Lx, Linv, status, pfl, st); });
+            if (f1 > f0)
+                prof.run(SPC_K_POTRF, S.steps[k0].potrf_flops, st,
+                         [&] { spc::launch_level<T>(P, f0, f1, s0, s0, none, Lx, Linv, status, pfl, st); });
+        } else {
+            spc::launch_level<T>(P, f0, f1, s0, s1, tiny, Lx, Linv, status, pfl, st);
+        }
+        for (int64_t k = k0; k < k1; ++k) {
             const auto &stp = S.steps[k];
-            if (stp.f1 > stp.f0)
-                prof.run(SPC_K_POTRF, stp.potrf_flops, st,
-                         [&] { spc::launch_potrf<T>(P, stp.f0, stp.f1, Lx, Linv, status, pfl, st); });
             if (stp.p1 > stp.p0)
                 prof.run(SPC_K_TRSM, stp.trsm_flops, st, [&] {
                     spc::launch_tiles<T>(P, spc::kTilesTrsm, stp.p0, stp.p1, Lx, Linv, status, nullptr, wc, false, pfl,

@@ -104,17 +104,16 @@ void launch_assemble(const DevPlan &P, int64_t nnz, const double *values, T *Lx,
 // floor[j] = theta * A's diagonal entry of permuted column j (BF16 updates)
 template <typename T>
 void launch_pivot_floor(const DevPlan &P, int64_t n, const double *values, double theta, T *floor, hipStream_t st);
+// The tiny supernodes of a level: tasks t0.. in groups of 16 lanes, e16.. of
+// 32, e32 .. t1 one wave each.
+struct TinyRange {
+    int64_t t0, e16, e32, t1;
+};
+// What a level starts with: the first diagonal blocks p0..p1 of its wide
+// supernodes, its small supernodes s0..s1 and its tiny ones.
 template <typename T>
-void launch_potrf(const DevPlan &P, int64_t t0, int64_t t1, T *Lx, T *Linv, unsigned long long *status,
-                  PivotFloor<T> pfl, hipStream_t st);
-template <typename T>
-void launch_small(const DevPlan &P, int64_t t0, int64_t t1, T *Lx, T *Linv, unsigned long long *status,
-                  PivotFloor<T> pfl, hipStream_t st);
-template <typename T>
-// tasks t0..t16-1 in groups of 16 lanes, t16..t32-1 in groups of 32, the
-// rest one wave each
-void launch_tiny(const DevPlan &P, int64_t t0, int64_t t16, int64_t t32, int64_t t1, T *Lx, T *Linv,
-                 unsigned long long *status, PivotFloor<T> pfl, hipStream_t st);
+void launch_level(const DevPlan &P, int64_t p0, int64_t p1, int64_t s0, int64_t s1, TinyRange tiny, T *Lx, T *Linv,
+                  unsigned long long *status, PivotFloor<T> pfl, hipStream_t st);
 template <typename T>
 // bf16: (float panels only) the trailing and scatter updates multiply
 // operands rounded to BF16 on BF16 MFMA with FP32 accumulation

@@ -9,7 +9,9 @@
 //
 // Kernels (paper Sec. 3, Listing 1 names the dense operations):
 //   k_assemble     scatter A into the zeroed panels
-//   k_potrf        POTRF of one diagonal block in LDS, plus its inverse
+//   k_level        what a level starts with: whole small and tiny supernodes,
+//                  and POTRF of the first diagonal blocks of the wide ones,
+//                  with the block inverses
 //   k_tiles        MFMA tiles: TRSM (rows times the transposed block
 //                  inverse), trailing SYRK/GEMM inside a supernode, and the
 //                  SYRK/GEMM update scatter-added through relative indices
@@ -533,17 +535,19 @@ __device__ __forceinline__ void potrf_lds(T (*A)[kNB + 1], PotrfLds<T> &W, int n
 }
 
 // ---------------------------------------------------------------------------
-// k_potrf: one workgroup per diagonal block (nb <= kNB = 64), held in LDS
-// (potrf_lds).
+// One workgroup's diagonal block (nb <= kNB = 64), from its panel, held in
+// LDS (potrf_lds).
 // ---------------------------------------------------------------------------
+template <typename T>
+struct BlockLds {
+    T A[kNB][kNB + 1];
+    PotrfLds<T> W;
+};
 template <typename T, bool BOOST>
-__global__ __launch_bounds__(256) void k_potrf(const PanelTask *tasks, T *Lx, T *Linv,
-                                               unsigned long long *status, const int32_t *status_slot,
-                                               PivotFloor<T> pfl) {
+__device__ __forceinline__ void potrf_body(const PanelTask &tk, BlockLds<T> &L, T *Lx, T *Linv,
+                                           unsigned long long *status, const int32_t *status_slot,
+                                           PivotFloor<T> pfl) {
     constexpr int NB = kNB;
-    __shared__ T A[NB][NB + 1];
-    __shared__ PotrfLds<T> W;
-    const PanelTask tk = tasks[blockIdx.x];
     const int64_t m = tk.m;
     const int c0 = tk.c0, nb = tk.c1 - tk.c0;
     T *P = Lx + tk.loff;
@@ -559,42 +563,56 @@ __global__ __launch_bounds__(256) void k_potrf(const PanelTask *tasks, T *Lx, T 
 #pragma unroll
         for (int q = 0; q < NB * NB / 256; ++q) {
             const int e = t + 256 * q, i = e % NB, k = e / NB;
-            A[i][k] = (i < nb && k <= i) ? ld[q] : (i == k ? T(1) : T(0));
+            L.A[i][k] = (i < nb && k <= i) ? ld[q] : (i == k ? T(1) : T(0));
         }
     }
     __syncthreads();
-    potrf_lds<T, BOOST>(A, W, nb, P, m, c0, Linv + tk.ioff, status + (status_slot ? status_slot[tk.s] : 0), tk.g0,
-                        nullptr, pfl);
+    potrf_lds<T, BOOST>(L.A, L.W, nb, P, m, c0, Linv + tk.ioff, status + (status_slot ? status_slot[tk.s] : 0),
+                        tk.g0, nullptr, pfl);
 }
 
 // ---------------------------------------------------------------------------
-// k_tiny: one wave per supernode with w <= kTinyW and m <= kTinyM (four per
-// workgroup, no LDS, no barriers): lane = row of the panel, the row's w
-// entries in registers, values of other rows read from their lanes.
+// Tiny supernodes: one wave per supernode with w <= kTinyW and m <= kTinyM (four per
+// workgroup, no barriers): lane = row of the panel, the row's w entries in
+// registers, values of other rows read from their lanes.
 //   1. column Cholesky: l_jj = sqrt(d_j), l_ij = a_ij / l_jj, then
 //      a_ik -= l_ij l_kj for the later columns;
 //   2. inverse of the diagonal triangle: lane c < w forms column c by
 //      forward substitution;
-//   3. the update C[i][k] = sum_j l_ij l_kj of the rows below (w <= k <= i),
-//      scatter-added into the ancestors: C[i][k] goes to cbase[k] +
-//      rel[crel[k] + i].
+//   3. the update C[i][k] = sum_j l_ij l_kj of the rows below (w <= k <= i)
+//      in 16x16 MFMA tiles (L through LDS; tiles transposed, so 16 lanes add
+//      to 16 rows of one target column), scatter-added into the ancestors:
+//      C[i][k] goes to cbase[k] + rel[crel[k] + i].
 // Pivots that are not positive and finite lower the status word.
+// Bound by latency in the narrow levels, where a launch is one round trip
+// after the other (task, panel, scatter addresses, atomics), and by the
+// atomics in the wide ones.  The scatter addresses do not depend on the
+// values, so they are loaded before the factorization (the far row tiles'
+// after it, together); loading them 8 columns at a time after it took 21 us a
+// launch over the levels of a 34^3 grid (FP32) and 45 over those of the 60^3
+// grid (FP64), this form 9 and 38.
 // ---------------------------------------------------------------------------
-__device__ __forceinline__ int64_t lane_read_i64(int64_t v, int src) {
-    const int lo = __builtin_amdgcn_readlane((int)(v & 0xffffffffll), src);
-    const int hi = __builtin_amdgcn_readlane((int)(v >> 32), src);
-    return ((int64_t)hi << 32) | (uint32_t)lo;
-}
+// LDS of one wave's tiny supernode: L[c][row] (the stride puts the four k of
+// a 16x16x4 operand in different banks), and the scatter addressing of its
+// row positions taken as columns.
+template <typename T>
+struct TinyLds {
+    T l[kTinyW][kTinyM + 16];
+    int64_t cb[kTinyM], cr[kTinyM];
+};
 
-// One wave's tiny supernode (the body of k_tiny and of the persistent
-// launch).  COH: the panel is read with device-scope loads, for a launch in
+// One wave's tiny supernode (of k_level and of the persistent launch).  COH: the panel is read with device-scope loads, for a launch in
 // which other workgroups (on other XCDs) scatter-added into it.
 template <typename T, bool COH>
-__device__ __forceinline__ void tiny_body(const SmallTask &tk, const int64_t *cbase, const int64_t *crel,
-                                          const int32_t *rel, T *Lx, T *Linv, unsigned long long *status,
-                                          const int32_t *status_slot, PivotFloor<T> pfl) {
-    constexpr int WT = kTinyW, CB = 8;  // CB: update columns per batch of loads
-    const int lane = threadIdx.x & 63;
+__device__ __forceinline__ void tiny_body(const SmallTask &tk, TinyLds<T> &L, const int64_t *cbase,
+                                          const int64_t *crel, const int32_t *rel, T *Lx, T *Linv,
+                                          unsigned long long *status, const int32_t *status_slot,
+                                          PivotFloor<T> pfl) {
+    constexpr int WT = kTinyW, NTM = kTinyM / 16;  // NTM: row tiles below, at most
+    static_assert(NTM == 4, "three near tiles, seven far ones");
+    using M = Mfma<T>;
+    using acc_t = typename M::acc;
+    const int lane = threadIdx.x & 63, l16 = lane & 15, lg = lane >> 4;
     const int m = tk.m, w = tk.w;
     T *P = Lx + tk.loff;
     const int rc = min(lane, m - 1);
@@ -604,9 +622,38 @@ __device__ __forceinline__ void tiny_body(const SmallTask &tk, const int64_t *cb
         const T *src = &P[(int64_t)min(c, w - 1) * m + rc];
         r[c] = COH ? dev_load(src) : *src;
     }
-    // scatter addressing of this lane's row position taken as a column
-    const int64_t kpos = tk.roff + min(max(lane, w), m - 1);
-    const int64_t my_cb = cbase[kpos], my_cr = crel[kpos];
+    // scatter addresses: lane's row i = w + 16 ti + l16 of C, columns
+    // k = w + 16 tj + M::row(lane, v)
+    const int nt = (m - w + 15) >> 4;
+    if (nt > 0) {
+        const int64_t kpos = tk.roff + min(max(lane, w), m - 1);
+        const int64_t cb = cbase[kpos], cr = crel[kpos];
+        L.cb[lane] = cb;
+        L.cr[lane] = cr;
+        wave_lds_sync();
+    }
+    auto row_of = [&](int ti) { return w + 16 * ti + l16; };
+    auto col_of = [&](int tj, int v) { return w + 16 * tj + M::row(lane, v); };
+    // offsets of the row tiles T0 .. T1 - 1, tile (ti, tj) at ti (ti + 1) / 2 +
+    // tj less that of (T0, 0); those of the first two are loaded ahead
+    auto offsets = [&](auto t0c, auto t1c, auto &rv) {
+        constexpr int T0 = decltype(t0c)::value, T1 = decltype(t1c)::value;
+        int x = 0;
+#pragma unroll
+        for (int ti = T0; ti < T1; ++ti)
+#pragma unroll
+            for (int tj = 0; tj <= ti; ++tj, ++x)
+#pragma unroll
+                for (int v = 0; v < 4; ++v)
+                    rv[x][v] = rel[L.cr[min(col_of(tj, v), m - 1)] + min(max(row_of(ti), col_of(tj, v)), m - 1)];
+    };
+    using I0 = std::integral_constant<int, 0>;
+    using I1 = std::integral_constant<int, 1>;
+    using I2 = std::integral_constant<int, 2>;
+    using I4 = std::integral_constant<int, NTM>;
+    int32_t near[3][4], far[7][4];
+    if (nt > 1) offsets(I0{}, I2{}, near);
+    else if (nt == 1) offsets(I0{}, I1{}, near);
     // 1. column Cholesky
     int bad = -1, boosted = 0;
     T rdg[WT];
@@ -635,6 +682,36 @@ __device__ __forceinline__ void tiny_body(const SmallTask &tk, const int64_t *cb
     if (lane == 0 && bad >= 0)
         atomicMin(status + (status_slot ? status_slot[tk.s] : 0), (unsigned long long)(tk.g0 + bad));
     if (lane == 0 && boosted) atomicAdd(pfl.count, boosted);
+    // 3. update of the rows below, scatter-added into the ancestors
+    if (nt > 0) {
+#pragma unroll
+        for (int c = 0; c < WT; ++c) L.l[c][lane] = c < w ? r[c] : T(0);
+        wave_lds_sync();
+    }
+    auto operand = [&](int t, int h) { return L.l[4 * h + lg][row_of(t)]; };  // columns 4 h + lg of row tile t
+    auto update = [&](auto t0c, auto t1c, auto &rv) {
+        constexpr int T0 = decltype(t0c)::value, T1 = decltype(t1c)::value;
+        int x = 0;
+#pragma unroll
+        for (int ti = T0; ti < T1; ++ti) {
+            if (ti >= nt) break;  // (uniform)
+            const T b0 = operand(ti, 0), b1 = operand(ti, 1);
+#pragma unroll
+            for (int tj = 0; tj <= ti; ++tj, ++x) {
+                acc_t acc = {0, 0, 0, 0};
+                acc = M::run(operand(tj, 0), b0, acc);
+                acc = M::run(operand(tj, 1), b1, acc);
+#pragma unroll
+                for (int v = 0; v < 4; ++v)
+                    if (row_of(ti) < m && col_of(tj, v) <= row_of(ti))
+                        atomicAdd(&Lx[L.cb[col_of(tj, v)] + rv[x][v]], -acc[v]);
+            }
+        }
+    };
+    if (nt > 2) offsets(I2{}, I4{}, far);
+    if (nt > 1) update(I0{}, I2{}, near);
+    else if (nt == 1) update(I0{}, I1{}, near);
+    if (nt > 2) update(I2{}, I4{}, far);
     if (lane < m)
 #pragma unroll
         for (int c = 0; c < WT; ++c)
@@ -654,29 +731,6 @@ __device__ __forceinline__ void tiny_body(const SmallTask &tk, const int64_t *cb
 #pragma unroll
             for (int a = 0; a < WT; ++a)
                 if (a < w) Vi[lane * w + a] = y[a];
-    }
-    // 3. update of the rows below, scatter-added into the ancestors
-    for (int k0 = w; k0 < m; k0 += CB) {
-        int32_t rv[CB];
-        int64_t cbk[CB];
-        T acc[CB];
-        bool ok[CB];
-#pragma unroll
-        for (int u = 0; u < CB; ++u) {
-            const int k = k0 + u, kc = min(k, m - 1);
-            cbk[u] = lane_read_i64(my_cb, kc);
-            const int64_t crk = lane_read_i64(my_cr, kc);
-            ok[u] = k < m && lane >= k && lane < m;
-            rv[u] = rel[crk + (ok[u] ? lane : kc)];
-            T a = T(0);
-#pragma unroll
-            for (int j = 0; j < WT; ++j)
-                if (j < w) a += r[j] * lane_read(r[j], kc);
-            acc[u] = a;
-        }
-#pragma unroll
-        for (int u = 0; u < CB; ++u)
-            if (ok[u]) atomicAdd(&Lx[cbk[u] + rv[u]], -acc[u]);
     }
 }
 
@@ -706,7 +760,7 @@ template <typename T, int G, bool COH>
 __device__ __forceinline__ void group_body(const SmallTask &tk, bool live, const int64_t *cbase, const int64_t *crel,
                                            const int32_t *rel, T *Lx, T *Linv, unsigned long long *status,
                                            const int32_t *status_slot, PivotFloor<T> pfl) {
-    constexpr int WG = kGroupW, CB = 4;
+    constexpr int WG = kGroupW;
     static_assert(G == 16 || G == 32, "group of 16 or 32 lanes");
     const int lane = threadIdx.x & 63, gi = lane & (G - 1), gb = lane - gi;
     const int m = live ? tk.m : 1, w = live ? tk.w : 1;
@@ -727,6 +781,16 @@ __device__ __forceinline__ void group_body(const SmallTask &tk, bool live, const
         const int64_t kpos = tk.roff + min(max(gi, w), m - 1);
         my_cb = cbase[kpos];
         my_cr = crel[kpos];
+    }
+    // scatter addresses of the columns k (lane = row), before the
+    // factorization as in tiny_body
+    auto column_live = [&](int k) { return live && k >= w && k < m; };
+    int32_t rv[G];
+#pragma unroll
+    for (int k = 0; k < G; ++k) {
+        if (k == 0) continue;
+        const int64_t crk = lane_pull(my_cr, gb + min(k, m - 1));
+        rv[k] = rel[column_live(k) ? crk + min(max(gi, k), m - 1) : 0];
     }
     const T flo = (live && pfl.v) ? pfl.v[tk.g0 + min(gi, w - 1)] : T(0);
     // 1. column Cholesky (columns past w are padding: left alone)
@@ -779,43 +843,29 @@ __device__ __forceinline__ void group_body(const SmallTask &tk, bool live, const
     }
     // 3. update of the rows below, scatter-added into the ancestors
 #pragma unroll
-    for (int k0 = 0; k0 < G; k0 += CB) {
-        int32_t rv[CB];
-        int64_t cbk[CB];
-        T acc[CB];
-        bool ok[CB];
+    for (int k = 1; k < G; ++k) {
+        if (!__any(column_live(k))) continue;
+        T a = T(0);
 #pragma unroll
-        for (int u = 0; u < CB; ++u) {
-            const int k = k0 + u, kc = min(max(k, w), m - 1);
-            cbk[u] = lane_pull(my_cb, gb + kc);
-            const int64_t crk = lane_pull(my_cr, gb + kc);
-            ok[u] = live && k >= w && k < m && gi >= k && gi < m;
-            rv[u] = ok[u] ? rel[crk + gi] : 0;
-            T a = T(0);
-#pragma unroll
-            for (int j = 0; j < WG; ++j) {
-                const T lk = lane_pull(r[j], gb + kc);
-                if (j < w) a += r[j] * lk;
-            }
-            acc[u] = a;
+        for (int j = 0; j < WG; ++j) {
+            const T lk = lane_pull(r[j], gb + min(k, m - 1));
+            if (j < w) a += r[j] * lk;
         }
-#pragma unroll
-        for (int u = 0; u < CB; ++u)
-            if (ok[u]) atomicAdd(&Lx[cbk[u] + rv[u]], -acc[u]);
+        const int64_t cbk = lane_pull(my_cb, gb + min(k, m - 1));
+        if (column_live(k) && gi >= k && gi < m) atomicAdd(&Lx[cbk + rv[k]], -a);
     }
 }
 
-// The tiny supernodes of one level: tasks [0, n16) in groups of 16 lanes
-// (16 per workgroup), [n16, n32) in groups of 32 (8 per workgroup), the
-// rest one wave each (4 per workgroup); the workgroups of the three parts
-// follow each other.
+// Workgroup b of the tiny supernodes of one level: tasks [0, n16) in groups
+// of 16 lanes (16 per workgroup), [n16, n32) in groups of 32 (8 per
+// workgroup), the rest one wave each (4 per workgroup); the workgroups of
+// the three parts follow each other.
 template <typename T>
-__global__ __launch_bounds__(256) void k_tiny(const SmallTask *tasks, int64_t n16, int64_t n32, int64_t ntasks,
-                                              const int64_t *cbase, const int64_t *crel, const int32_t *rel, T *Lx,
-                                              T *Linv, unsigned long long *status, const int32_t *status_slot,
-                                              PivotFloor<T> pfl) {
-    const int wv = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    int64_t b = blockIdx.x;
+__device__ __forceinline__ void tiny_block(int64_t b, const SmallTask *tasks, int64_t n16, int64_t n32,
+                                           int64_t ntasks, TinyLds<T> *L, const int64_t *cbase, const int64_t *crel,
+                                           const int32_t *rel, T *Lx, T *Linv, unsigned long long *status,
+                                           const int32_t *status_slot, PivotFloor<T> pfl) {
+    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
     const int64_t b16 = (n16 + 15) / 16, b32 = (n32 - n16 + 7) / 8;
     if (b < b16) {
         const int64_t gi = b * 16 + wv * 4 + (lane >> 4);
@@ -834,16 +884,16 @@ __global__ __launch_bounds__(256) void k_tiny(const SmallTask *tasks, int64_t n1
     b -= b32;
     const int64_t ti = n32 + b * 4 + wv;
     if (ti >= ntasks) return;  // the whole wave
-    tiny_body<T, false>(tasks[ti], cbase, crel, rel, Lx, Linv, status, status_slot, pfl);
+    tiny_body<T, false>(tasks[ti], L[wv], cbase, crel, rel, Lx, Linv, status, status_slot, pfl);
 }
 
 // ---------------------------------------------------------------------------
-// k_small: one workgroup per small supernode (w <= kSmallW, m <= kSmallM),
+// Small supernodes: one workgroup each (w <= kSmallW, m <= kSmallM),
 // the whole m x w panel in LDS:
 //   1. column Cholesky by panels of 16 columns: each wave holds the panel's
 //      16 diagonal rows in lanes 0..15 and 48 rows below in the others, 16
 //      columns of a row in registers, pivots and multipliers read from their
-//      lanes as in k_tiny (POTRF of the diagonal block and TRSM of the rows
+//      lanes as for the tiny ones (POTRF of the diagonal block and TRSM of the rows
 //      below at once); every wave factors the diagonal rows for itself, so
 //      the pivot chain crosses no barrier.  Waves 0..2 cover all the rows.
 //      The second panel's columns are brought up to date in 16x16 MFMA tiles
@@ -875,8 +925,8 @@ struct SmallLds {
     int tile;
 };
 
-// One workgroup's small supernode (the body of k_small and of the
-// persistent launch); COH as in tiny_body.
+// One workgroup's small supernode (of k_level and of the persistent
+// launch); COH as in tiny_body.
 template <typename T, bool COH>
 __device__ __forceinline__ void small_body(const SmallTask &tk, SmallLds<T> &L, const int64_t *cbase,
                                            const int64_t *crel, const int32_t *rel, T *Lx, T *Linv,
@@ -1068,12 +1118,40 @@ __device__ __forceinline__ void small_body(const SmallTask &tk, SmallLds<T> &L, 
     }
 }
 
+// ---------------------------------------------------------------------------
+// k_level: what a level starts with, in one launch: the first diagonal blocks
+// of its wide supernodes, then its small supernodes, then its tiny ones,
+// one workgroup range after the other (longest first).  They do not depend
+// on each other (their scatter goes to later levels only), and in the narrow
+// levels each is a chain of latencies on a few workgroups.  With the tiny
+// supernodes in a launch of their own the factorizations of the 64^2 grid
+// (FP64) and a 34^3 grid (FP32) took 296 and 2062 us, in one launch 257 and
+// 1988; with three launches 325 and 2160.  The wide levels of a batch of 160
+// systems lose nothing by the lower occupancy (11.2 ms either way): the
+// atomics bound them.
+// ---------------------------------------------------------------------------
 template <typename T>
-__global__ __launch_bounds__(256, 3) void k_small(const SmallTask *tasks, const int64_t *cbase, const int64_t *crel,
-                                               const int32_t *rel, T *Lx, T *Linv, unsigned long long *status,
-                                               const int32_t *status_slot, PivotFloor<T> pfl) {
-    __shared__ SmallLds<T> L;
-    small_body<T, false>(tasks[blockIdx.x], L, cbase, crel, rel, Lx, Linv, status, status_slot, pfl);
+union LevelLds {
+    BlockLds<T> block;
+    SmallLds<T> small;
+    TinyLds<T> tiny[4];
+};
+template <typename T, bool BOOST>
+__global__ __launch_bounds__(256, 3) void k_level(const PanelTask *potrf, int npotrf, const SmallTask *small,
+                                                  int nsmall, const SmallTask *tiny, int64_t n16, int64_t n32,
+                                                  int64_t ntiny, const int64_t *cbase, const int64_t *crel,
+                                                  const int32_t *rel, T *Lx, T *Linv, unsigned long long *status,
+                                                  const int32_t *status_slot, PivotFloor<T> pfl) {
+    __shared__ __align__(16) char mem[sizeof(LevelLds<T>)];
+    LevelLds<T> &L = *reinterpret_cast<LevelLds<T> *>(mem);
+    const int b = blockIdx.x;
+    if (b < npotrf)
+        potrf_body<T, BOOST>(potrf[b], L.block, Lx, Linv, status, status_slot, pfl);
+    else if (b < npotrf + nsmall)
+        small_body<T, false>(small[b - npotrf], L.small, cbase, crel, rel, Lx, Linv, status, status_slot, pfl);
+    else
+        tiny_block<T>(b - npotrf - nsmall, tiny, n16, n32, ntiny, L.tiny, cbase, crel, rel, Lx, Linv, status,
+                      status_slot, pfl);
 }
 
 // ---------------------------------------------------------------------------
@@ -1104,9 +1182,10 @@ __global__ __launch_bounds__(256, 3) void k_persist_small(const PersistEntry *qu
                                                        const int64_t *cbase, const int64_t *crel, const int32_t *rel,
                                                        T *Lx, T *Linv, unsigned long long *status,
                                                        const int32_t *status_slot, PivotFloor<T> pfl, WaitCtl wc) {
-    __shared__ SmallLds<T> L;
+    __shared__ SmallLds<T> L;  // also the four waves' TinyLds
+    static_assert(4 * sizeof(TinyLds<T>) <= sizeof(L), "the waves' tiny supernodes fit");
     __shared__ int32_t slot;
-    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
     for (;;) {
         if (tid == 0) slot = atomicAdd(qctr, 1);
         __syncthreads();
@@ -1130,7 +1209,7 @@ __global__ __launch_bounds__(256, 3) void k_persist_small(const PersistEntry *qu
                 const SmallTask tk = ptiny[e.first + wv];
                 if (lane == 0) wait_value(&pdep[tk.s], 0, wc.err, wc.spin);
                 __asm__ volatile("" ::: "memory");
-                tiny_body<T, true>(tk, cbase, crel, rel, Lx, Linv, status, status_slot, pfl);
+                tiny_body<T, true>(tk, reinterpret_cast<TinyLds<T> *>(&L)[wv], cbase, crel, rel, Lx, Linv, status, status_slot, pfl);
                 __builtin_amdgcn_s_waitcnt(0);
                 for (int64_t k = ptgt_ptr[tk.s] + lane; k < ptgt_ptr[tk.s + 1]; k += 64)
                     atomicSub(&pdep[ptgt[k]], 1);
@@ -2952,34 +3031,23 @@ void launch_pivot_floor(const DevPlan &P, int64_t n, const double *values, doubl
     hipLaunchKernelGGL(k_pivot_floor<T>, dim3(grid1(n, 256)), dim3(256), 0, st, P.dsrc, n, values, theta, floor);
 }
 
-template <typename T>
-void launch_potrf(const DevPlan &P, int64_t t0, int64_t t1, T *Lx, T *Linv, unsigned long long *status,
-                  PivotFloor<T> pfl, hipStream_t st) {
-    if (t1 <= t0) return;
-    if (pfl.v)
-        hipLaunchKernelGGL((k_potrf<T, true>), dim3((unsigned)(t1 - t0)), dim3(256), 0, st, P.potrf_tasks + t0, Lx,
-                           Linv, status, P.status_slot, pfl);
-    else
-        hipLaunchKernelGGL((k_potrf<T, false>), dim3((unsigned)(t1 - t0)), dim3(256), 0, st, P.potrf_tasks + t0, Lx,
-                           Linv, status, P.status_slot, pfl);
+static int64_t tiny_blocks(const TinyRange &t) {
+    const int64_t n16 = t.e16 - t.t0, n32 = t.e32 - t.t0, nt = t.t1 - t.t0;
+    return (n16 + 15) / 16 + (n32 - n16 + 7) / 8 + (nt - n32 + 3) / 4;
 }
 
 template <typename T>
-void launch_tiny(const DevPlan &P, int64_t t0, int64_t t16, int64_t t32, int64_t t1, T *Lx, T *Linv,
-                 unsigned long long *status, PivotFloor<T> pfl, hipStream_t st) {
-    if (t1 <= t0) return;
-    const int64_t n16 = t16 - t0, n32 = t32 - t0, nt = t1 - t0;
-    const int64_t blocks = (n16 + 15) / 16 + (n32 - n16 + 7) / 8 + (nt - n32 + 3) / 4;
-    hipLaunchKernelGGL(k_tiny<T>, dim3((unsigned)blocks), dim3(256), 0, st, P.tiny_tasks + t0, n16, n32, nt,
-                       P.cbase, P.crel, P.rel, Lx, Linv, status, P.status_slot, pfl);
-}
-
-template <typename T>
-void launch_small(const DevPlan &P, int64_t t0, int64_t t1, T *Lx, T *Linv, unsigned long long *status,
-                  PivotFloor<T> pfl, hipStream_t st) {
-    if (t1 <= t0) return;
-    hipLaunchKernelGGL(k_small<T>, dim3((unsigned)(t1 - t0)), dim3(256), 0, st, P.small_tasks + t0, P.cbase,
-                       P.crel, P.rel, Lx, Linv, status, P.status_slot, pfl);
+void launch_level(const DevPlan &P, int64_t p0, int64_t p1, int64_t s0, int64_t s1, TinyRange t, T *Lx, T *Linv,
+                  unsigned long long *status, PivotFloor<T> pfl, hipStream_t st) {
+    const int64_t blocks = (p1 - p0) + (s1 - s0) + tiny_blocks(t);
+    if (blocks <= 0) return;
+    const auto launch = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(256), 0, st, P.potrf_tasks + p0, (int)(p1 - p0),
+                           P.small_tasks + s0, (int)(s1 - s0), P.tiny_tasks + t.t0, t.e16 - t.t0, t.e32 - t.t0,
+                           t.t1 - t.t0, P.cbase, P.crel, P.rel, Lx, Linv, status, P.status_slot, pfl);
+    };
+    if (pfl.v) launch(k_level<T, true>);
+    else launch(k_level<T, false>);
 }
 
 template <typename T>
@@ -3264,15 +3332,11 @@ template void launch_zero<unsigned long long>(unsigned long long *, int64_t, hip
 #define SPC_INSTANTIATE(T)                                                                                  \
     template void launch_zero<T>(T *, int64_t, hipStream_t);                                                \
     template void launch_assemble<T>(const DevPlan &, int64_t, const double *, T *, hipStream_t);           \
-    template void launch_potrf<T>(const DevPlan &, int64_t, int64_t, T *, T *, unsigned long long *,         \
-                                  PivotFloor<T>, hipStream_t);                                              \
+    template void launch_level<T>(const DevPlan &, int64_t, int64_t, int64_t, int64_t, TinyRange, T *, T *,  \
+                                  unsigned long long *, PivotFloor<T>, hipStream_t);                        \
     template void launch_pivot_floor<T>(const DevPlan &, int64_t, const double *, double, T *, hipStream_t); \
     template void launch_tiles<T>(const DevPlan &, int, int64_t, int64_t, T *, T *, unsigned long long *,    \
                                   int32_t *, WaitCtl, bool, PivotFloor<T>, hipStream_t);                    \
-    template void launch_small<T>(const DevPlan &, int64_t, int64_t, T *, T *, unsigned long long *,         \
-                                  PivotFloor<T>, hipStream_t);                                              \
-    template void launch_tiny<T>(const DevPlan &, int64_t, int64_t, int64_t, int64_t, T *, T *,             \
-                                 unsigned long long *, PivotFloor<T>, hipStream_t);                         \
     template void launch_tiles128<T>(const DevPlan &, int64_t, int64_t, T *, bool, hipStream_t);            \
     template void launch_trail128<T>(const DevPlan &, int64_t, int64_t, T *, bool, hipStream_t);            \
     template void launch_persist_small<T>(const DevPlan &, int64_t, int64_t, int32_t *, int32_t *, T *, T *, \

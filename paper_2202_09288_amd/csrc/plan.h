@@ -16,8 +16,8 @@ constexpr int kTileBig = 128;
 constexpr int kBigMin = 256;
 constexpr int kBigMinK = 128;
 // Supernodes with w <= kSmallW and m <= kSmallM are factored, inverted and
-// scatter-added by one workgroup each (k_small); those with w <= kTinyW and
-// m <= kTinyM by one wave each (k_tiny, four per workgroup).
+// scatter-added by one workgroup each; those with w <= kTinyW and
+// m <= kTinyM by one wave each, four per workgroup (k_level).
 constexpr int kSmallW = 32;
 constexpr int kSmallM = 128;
 constexpr int kTinyW = 8;
@@ -127,7 +127,7 @@ struct PanelTask {
     int32_t pad;
 };
 
-// A whole small supernode (k_small): factor, invert, scatter its update.
+// A whole small or tiny supernode (k_level): factor, invert, scatter its update.
 struct SmallTask {
     int64_t loff;  // lptr[s]
     int64_t roff;  // rptr[s]

@@ -144,3 +144,17 @@ def test_values_near_the_ends_of_the_range(lib, tuning, precision, scale):
     err, _, _ = factor_and_solve(lib, (colptr, rowidx, values * scale, perm), tuning, precision)
     print(f"{precision} scale {scale:.1e} {tuning}: worst supernode {err:.2e}", flush=True)
     assert err <= (1e-10 if precision == "fp64" else 1e-4)
+
+
+@pytest.mark.parametrize("precision", ["fp64", "fp32"])
+@pytest.mark.parametrize("group", [1, -1])
+@pytest.mark.parametrize("w,b", [(1, 1), (1, 15), (2, 14), (4, 12), (4, 13), (3, 29), (4, 28), (1, 63), (5, 16),
+                                 (8, 17), (8, 33), (8, 56), (7, 49), (8, 0)])
+def test_tiny_supernode_shapes(lib, w, b, group, precision):
+    """Tiny supernodes at the edges of the 16-lane, 32-lane and one-wave forms
+    and of their 16-row tiles; the border's supernode is tiny, small or
+    blocked beside them."""
+    matrix = arrow(w, b, blocks=5) if b else arrow(w, 1, blocks=9)
+    err, eta, _ = factor_and_solve(lib, matrix, {"group": group}, precision)
+    print(f"w={w} b={b} group={group} {precision}: worst supernode {err:.2e}, eta {eta:.2e}", flush=True)
+    assert err <= (1e-10 if precision == "fp64" else 1e-4) and eta <= BAR[precision]
