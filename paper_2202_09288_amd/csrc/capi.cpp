@@ -410,15 +410,15 @@ void enqueue_factor(const spc::Symbolic &S, const spc::DevPlan &P, const double 
     }
 }
 
-// Y holds the permuted right-hand sides on entry (and is overwritten); X
-// receives the solution.
-// sync points to kSolveSyncInts(blocks) words of workspace.  Each sweep runs
-// one launch per wide block-tree level, and the narrow levels at the top
-// (levels solve_split..) as one persistent launch per sweep, which removes
-// a launch per level from the long chains of the top supernodes.
+// B (n x nrhs column-major, ldb) is overwritten with the solution; Y, X and
+// Acc are work vectors, sync points to kSolveSyncInts(blocks) words of
+// workspace.  Each sweep runs one launch per wide block-tree level, and the
+// narrow levels at the top (levels solve_split..) as one persistent launch
+// per sweep, which removes a launch per level from the long chains of the top
+// supernodes.
 template <typename T>
-void enqueue_solve(const spc::Symbolic &S, const spc::DevPlan &P, const T *Lx, const T *Linv, T *Y, T *X,
-                   T *Acc, int32_t *sync, spc::WaitCtl wc, int nrhs, hipStream_t st) {
+void enqueue_solve(const spc::Symbolic &S, const spc::DevPlan &P, const T *Lx, const T *Linv, double *B, int64_t ldb,
+                   T *Y, T *X, T *Acc, int32_t *sync, spc::WaitCtl wc, int nrhs, hipStream_t st) {
     const int64_t n = S.n, nb = (int64_t)S.sblocks.size(), nt = (int64_t)S.stasks.size();
     const spc::SolveSync sy = spc::make_solve_sync(sync, nb, wc);
     const int32_t split = S.solve_split;
@@ -426,9 +426,7 @@ void enqueue_solve(const spc::Symbolic &S, const spc::DevPlan &P, const T *Lx, c
     // backward sweep) for the forward one, Y (spent by then) for the
     // backward one
     const bool persist = split < S.nslevels;
-    if (persist) spc::launch_fill_unset<T>(Acc, n * nrhs, st);
-    else spc::launch_zero<T>(Acc, n * nrhs, st);
-    spc::launch_solve_reset(P, nb, sy, st);
+    spc::launch_solve_init<T>(P, n, nrhs, B, ldb, Y, Acc, persist, nb, sy, st);
     // below solve_split the tiny supernodes of a level have their own
     // (one-wave) launch beside the level's task launch
     const int32_t tsplit = S.solve_split;
@@ -440,8 +438,7 @@ void enqueue_solve(const spc::Symbolic &S, const spc::DevPlan &P, const T *Lx, c
     }
     if (persist) {
         spc::launch_solve_fwd<T>(P, S.stask_ptr[split], nt, Lx, Linv, Y, X, Acc, n, nrhs, sy, true, st);
-        spc::launch_fill_unset<T>(Y, n * nrhs, st);
-        spc::launch_zero<T>(Acc, n * nrhs, st);
+        spc::launch_solve_turn<T>(Y, Acc, n * nrhs, st);
         spc::launch_solve_bwd<T>(P, S.stask_ptr[split], nt, Lx, Linv, X, Acc, Y, n, nrhs, sy, true, st);
     }
     for (int32_t l = split - 1; l >= 0; --l) {
@@ -450,6 +447,7 @@ void enqueue_solve(const spc::Symbolic &S, const spc::DevPlan &P, const T *Lx, c
         spc::launch_solve_bwd<T>(P, S.stask_ptr[l], S.stask_ptr[l + 1], Lx, Linv, X, Acc, nullptr, n, nrhs, sy, false,
                                  st);
     }
+    spc::launch_perm_out<T>(P, n, nrhs, X, B, ldb, st);
 }
 
 void drop_graph(spc_factor_s *f) {
@@ -859,16 +857,12 @@ int solve_chunks(spc_factor f, double *d_B, int nrhs, int64_t ldb, hipStream_t s
         double *B = d_B + (int64_t)q0 * ldb;
         if (f->precision == SPC_FP64) {
             double *Y = (double *)base, *X = (double *)(base + vec), *Acc = (double *)(base + 2 * vec);
-            spc::launch_perm_in<double>(P, S.n, q, B, ldb, Y, st);
-            enqueue_solve<double>(S, P, (const double *)f->Lx, (const double *)f->Linv, Y, X, Acc, counters, wc, q,
-                                  st);
-            spc::launch_perm_out<double>(P, S.n, q, X, B, ldb, st);
+            enqueue_solve<double>(S, P, (const double *)f->Lx, (const double *)f->Linv, B, ldb, Y, X, Acc, counters,
+                                  wc, q, st);
         } else {
             float *Y = (float *)base, *X = (float *)(base + vec), *Acc = (float *)(base + 2 * vec);
-            spc::launch_perm_in<float>(P, S.n, q, B, ldb, Y, st);
-            enqueue_solve<float>(S, P, (const float *)f->Lx, (const float *)f->Linv, Y, X, Acc, counters, wc, q,
-                                 st);
-            spc::launch_perm_out<float>(P, S.n, q, X, B, ldb, st);
+            enqueue_solve<float>(S, P, (const float *)f->Lx, (const float *)f->Linv, B, ldb, Y, X, Acc, counters,
+                                  wc, q, st);
         }
     }
     HIP_TRY(hipGetLastError());

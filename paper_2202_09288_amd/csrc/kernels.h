@@ -65,10 +65,11 @@ constexpr int kFlagsPerBlock = 5;
 constexpr int32_t kSpinDefault = 1 << 20;
 
 // Device state of one persistent solve (in the caller's workspace):
-// kSolveSyncInts(nblocks) int32 words, plus the factor's error word.
+// two counters per block and two work counters, plus the factor's error word.
+// (The size counts three words per block: it decides which systems fit
+// spc_solve_noalloc's scratch array.)
 struct SolveSync {
     int32_t *dep;    // [nblocks] forward contributions still due
-    int32_t *done;   // [nblocks] 1 once x of the block is final (backward)
     int32_t *cnt;    // [nblocks] backward tasks of the block that arrived
     int32_t *queue;  // [2] work counters of the two sweeps
     int32_t *err;    // the factor's device-error word: nonzero once a wait gave up
@@ -76,7 +77,7 @@ struct SolveSync {
 };
 inline int64_t kSolveSyncInts(int64_t nblocks) { return 3 * nblocks + 2; }
 inline SolveSync make_solve_sync(int32_t *base, int64_t nblocks, WaitCtl wc) {
-    return SolveSync{base, base + nblocks, base + 2 * nblocks, base + 3 * nblocks, wc.err, wc.spin};
+    return SolveSync{base, base + nblocks, base + 2 * nblocks, wc.err, wc.spin};
 }
 
 // Entries that wide loads may read past the end of the panel and inverse
@@ -133,19 +134,24 @@ template <typename T>
 void launch_persist_small(const DevPlan &P, int64_t nchunks, int64_t nsuper, int32_t *pdep, int32_t *qctr, T *Lx,
                           T *Linv, unsigned long long *status, PivotFloor<T> pfl, WaitCtl wc, hipStream_t st);
 
+// Start of a solve: Y <- the permuted right-hand sides, Acc <- unset (persist:
+// the forward hand-over buffer) or zero, the counters of sy reset.
 template <typename T>
-void launch_perm_in(const DevPlan &P, int64_t n, int nrhs, const double *B, int64_t ldb, T *W,
-                    hipStream_t st);
+void launch_solve_init(const DevPlan &P, int64_t n, int nrhs, const double *B, int64_t ldb, T *Y, T *Acc,
+                       bool persist, int64_t nblocks, SolveSync sy, hipStream_t st);
+// Between the persistent sweeps: Y <- unset (the backward hand-over buffer),
+// Acc <- zero.
+template <typename T>
+void launch_solve_turn(T *Y, T *Acc, int64_t count, hipStream_t st);
 template <typename T>
 void launch_perm_out(const DevPlan &P, int64_t n, int nrhs, const T *W, double *B, int64_t ldb,
                      hipStream_t st);
-void launch_solve_reset(const DevPlan &P, int64_t nblocks, SolveSync sy, hipStream_t st);
 // Solve sweeps over tasks t0..t1-1 (one block-tree level), or, with
 // persist, over the tasks of levels solve_split.. in one persistent launch
-// (t0 = first task of that range, t1 = all tasks; needs launch_solve_reset
+// (t0 = first task of that range, t1 = all tasks; needs launch_solve_init
 // first).
 // H (forward) and XB (backward): the persistent sweeps' hand-over buffers,
-// n x nrhs like Y, every entry unset (launch_fill_unset) before the sweep.
+// n x nrhs like Y, every entry unset before the sweep.
 template <typename T>
 void launch_solve_fwd(const DevPlan &P, int64_t t0, int64_t t1, const T *Lx, const T *Linv, T *Y, T *X, T *H,
                       int64_t n, int nrhs, SolveSync sy, bool persist, hipStream_t st);
@@ -159,8 +165,6 @@ void launch_solve_tiny_bwd(const DevPlan &P, int64_t t0, int64_t t1, const T *Lx
 template <typename T>
 void launch_solve_bwd(const DevPlan &P, int64_t t0, int64_t t1, const T *Lx, const T *Linv, T *X, T *Acc, T *XB,
                       int64_t n, int nrhs, SolveSync sy, bool persist, hipStream_t st);
-template <typename T>
-void launch_fill_unset(T *p, int64_t count, hipStream_t st);
 
 // refinement (FP64)
 void launch_spmv(const int64_t *rowptr, const int32_t *colidx, const int64_t *valmap, const double *values,

@@ -1780,49 +1780,7 @@ __global__ __launch_bounds__(512) void k_tiles128(const TileTask *tasks, const i
 //   stores x_q = Linv_q^T t.  Rows below belong to ancestors, whose x is
 //   final when the block's level runs.
 // ---------------------------------------------------------------------------
-template <typename T>
-__global__ void k_perm_in(const int32_t *perm, int64_t n, int nrhs, const double *B, int64_t ldb, T *W) {
-    int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n * nrhs) return;
-    int64_t k = i / nrhs, r = i % nrhs;
-    W[i] = (T)B[perm[k] + r * ldb];
-}
-
-template <typename T>
-__global__ void k_perm_out(const int32_t *perm, int64_t n, int nrhs, const T *W, double *B, int64_t ldb) {
-    int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n * nrhs) return;
-    int64_t k = i / nrhs, r = i % nrhs;
-    B[perm[k] + r * ldb] = (double)W[i];
-}
-
-constexpr int kMaxRhs = 16;
-
-// Persistent sweeps: instead of one launch per block-tree level, a grid of
-// resident workgroups takes tasks from an atomic counter in an order where
-// every task's dependencies come first, so a task waits only on tasks that
-// running workgroups already hold and the sweep cannot deadlock.  Forward:
-// a block's tasks wait until every task updating its rows has counted down
-// dep[block]; backward: a task waits until the blocks owning its rows are
-// done (bounded waits, wait_value).
-
-// Data handed between workgroups of one persistent sweep moves through
-// device-scope atomics (loads after a wait, stores before a flag is raised),
-// and a workgroup raises a flag after waiting for its own memory operations;
-// no cache-wide fences, whose writeback and invalidation cost more than the
-// data.
-template <typename T>
-__device__ __forceinline__ T shared_load(const T *p) {
-    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-template <typename T>
-__device__ __forceinline__ void shared_store(T *p, T v) {
-    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-__device__ __forceinline__ void release_own() { __builtin_amdgcn_s_waitcnt(0); }
-__device__ __forceinline__ void acquire_after_wait() {}
-
-// Hand-over buffers between consecutive blocks of a supernode: filled with
+// Hand-over buffers of the persistent sweeps: filled with
 // a signalling-NaN pattern before the sweep, which no arithmetic result
 // takes (a NaN that arithmetic yields is quiet), so a reader polls the
 // value itself and the writer needs no flag after it.
@@ -1842,6 +1800,64 @@ template <typename T>
 __device__ __forceinline__ bool is_unset(T v) {
     return __builtin_bit_cast(typename Unset<T>::bits_t, v) == Unset<T>::bits;
 }
+// What a solve starts with, in one launch: the permuted right-hand sides in Y,
+// Acc set (unset pattern or zero), the counters of the persistent sweeps
+// (dep <- the forward counts, cnt <- 0, queues <- 0).  The error word is the
+// factor's, cleared only by a factorization, so a wait that gave up stays
+// reported.
+template <typename T>
+__global__ void k_solve_init(const int32_t *perm, int64_t n, int nrhs, const double *B, int64_t ldb, T *Y, T *Acc,
+                             int persist, const int32_t *fdep, int64_t nblocks, SolveSync sy) {
+    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < n * nrhs) {
+        // (32-bit division where it reaches: the 64-bit one is the most of this kernel)
+        const int64_t k = n * nrhs <= UINT_MAX ? (uint32_t)i / (uint32_t)nrhs : i / nrhs;
+        const int64_t r = i - k * nrhs;
+        Y[i] = (T)B[perm[k] + r * ldb];
+        Acc[i] = persist ? __builtin_bit_cast(T, Unset<T>::bits) : T(0);
+    }
+    if (i < nblocks) {
+        sy.dep[i] = fdep[i];
+        sy.cnt[i] = 0;
+    }
+    if (i < 2) sy.queue[i] = 0;
+}
+
+template <typename T>
+__global__ void k_perm_out(const int32_t *perm, int64_t n, int nrhs, const T *W, double *B, int64_t ldb) {
+    int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= n * nrhs) return;
+    const int64_t k = n * nrhs <= UINT_MAX ? (uint32_t)i / (uint32_t)nrhs : i / nrhs;
+    const int64_t r = i - k * nrhs;
+    B[perm[k] + r * ldb] = (double)W[i];
+}
+
+constexpr int kMaxRhs = 16;
+
+// Persistent sweeps: instead of one launch per block-tree level, a grid of
+// resident workgroups takes tasks from an atomic counter in an order where
+// every task's dependencies come first, so a task waits only on tasks that
+// running workgroups already hold and the sweep cannot deadlock.  Forward:
+// a block's tasks wait until every task updating its rows has counted down
+// dep[block]; backward: a task waits for the x of its rows (bounded waits,
+// wait_value, wait_handed and fetch_rows).
+
+// Data handed between workgroups of one persistent sweep moves through
+// device-scope atomics (loads after a wait, stores before a flag is raised),
+// and a workgroup raises a flag after waiting for its own memory operations;
+// no cache-wide fences, whose writeback and invalidation cost more than the
+// data.
+template <typename T>
+__device__ __forceinline__ T shared_load(const T *p) {
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+template <typename T>
+__device__ __forceinline__ void shared_store(T *p, T v) {
+    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ void release_own() { __builtin_amdgcn_s_waitcnt(0); }
+__device__ __forceinline__ void acquire_after_wait() {}
+
 // Bounded wait for a handed-over value (0 once a wait gave up).
 template <typename T>
 __device__ __forceinline__ T wait_handed(const T *p, int32_t *err, int32_t spin) {
@@ -2102,164 +2118,6 @@ __global__ __launch_bounds__(256, 2) void k_solve_fwd_multi(const SolveTask *tas
     }
 }
 
-// Backward, one task = rows r0..r1-1 below block q, one right-hand side:
-// thread (k, g) sums L[r][c0+k] X[rows[r]] over the rows r of group g (64
-// rows each); the four groups are added through LDS.  A block with one task
-// finishes itself:
-//   t = X_q - sum,  x_q = Linv_q^T t.
-// A block split over several tasks adds its sums into Acc.  In a level
-// launch the last task to arrive (sy.cnt) finishes the block.  In the
-// persistent sweep the block's first task does: it holds the rows nearest
-// the block, whose x are final last, and it is queued after the block's
-// other tasks, so it collects their sums (waiting on sy.cnt) before its own
-// rows are ready, which keeps that exchange off the chain of blocks.
-// Rows below the block belong to ancestors, whose x is final before the
-// block's tasks read it (level order, or the done flags of the persistent
-// sweep).  Persistent sweep, inside a supernode: the task finishing block
-// q also puts x_q into XB, and the first task of block q - 1 (whose first
-// rows are q's) polls XB for those rows instead of q's done flag (hand bits).
-template <typename T, bool PERSIST>
-__global__ __launch_bounds__(256) void k_solve_bwd(const SolveTask *tasks, int64_t ntasks, const int32_t *order,
-                                                   const int32_t *rows, const T *Lx, const T *Linv, T *X, T *Acc,
-                                                   T *XB, int64_t n, const int64_t *tgt_ptr, const int32_t *tgt,
-                                                   SolveSync sy) {
-    constexpr int NB = kNB, QW = 16, RG = 64;
-    __shared__ T xr[256];      // x of the task's rows
-    __shared__ T Sm[4][NB];    // sums of the 4 groups
-    __shared__ T tq[NB];
-    __shared__ T ao[NB];       // persistent finisher: the other tasks' sums
-    __shared__ int last;
-    __shared__ int32_t slot;
-    const int tid = threadIdx.x, k = tid & 63, g = tid >> 6;
-    // x_q = Linv^T t, with (Linv^T)[c][i] = Linv[i][c] nonzero for i >= c:
-    // four threads per output c, 16 rows i each, that part of Linv held in
-    // registers.
-    const int oc = tid >> 2;
-    auto inv_row = [&](int s2) { return QW * (tid & 3) + s2; };
-    for (int pass = 0;; ++pass) {
-        const int64_t t = next_task<PERSIST>(pass, order, sy.queue + 1, ntasks, &slot);
-        if (t < 0) return;
-        const SolveTask tk = tasks[t];
-        const int nb = tk.nb;
-        const int64_t m = tk.m;
-        const T *P = Lx + tk.loff;
-        const T *Q = Linv + tk.ioff;
-        const int64_t rown = tk.r0 + tid;
-        const int64_t gr = rows[tk.roff + min(rown, m - 1)];
-        T qv[QW], pv[RG];
-#pragma unroll
-        for (int u = 0; u < RG; ++u)
-            pv[u] = P[(int64_t)(tk.c0 + min(k, nb - 1)) * m + min<int64_t>(tk.r0 + g * RG + u, m - 1)];
-#pragma unroll
-        for (int s2 = 0; s2 < QW; ++s2) {
-            const int i = inv_row(s2);
-            const T v = Q[min(i, nb - 1) + (int64_t)min(oc, nb - 1) * nb];
-            qv[s2] = (i >= oc && i < nb && oc < nb) ? v : T(0);
-        }
-        int32_t my_tgt = -1;
-        if (PERSIST) {
-            // at most one target block per row of the task
-            const int64_t tb = tgt_ptr[t], te = tgt_ptr[t + 1];
-            if (tid < te - tb) my_tgt = tgt[tb + tid];
-        }
-        // the block's own forward values: final since the forward sweep, and
-        // overwritten only by the task that finishes this block, so a task
-        // known to finish it loads them before it waits
-        T xb = T(0);
-        if (tk.ntasks == 1 || (PERSIST && tk.first)) xb = X[tk.g0 + min(tid, nb - 1)];
-        const bool finisher = PERSIST && tk.first && tk.ntasks > 1;
-        if (finisher) {
-            // every other task of the block was dequeued before this one
-            if (tid == 0) wait_value(&sy.cnt[tk.blk], tk.ntasks - 1, sy.err, sy.spin);
-            __syncthreads();
-            acquire_after_wait();
-            if (tid < nb)
-                ao[tid] = __hip_atomic_exchange(&Acc[tk.g0 + tid], T(0), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        }
-        // rows of the next block of the supernode: their x come through XB
-        const bool handed = PERSIST && (tk.hand & kHandOut) && tid < (tk.hand >> 8);
-        if (PERSIST) {
-            if (my_tgt >= 0 && !((tk.hand & kHandOut) && my_tgt == tk.blk + 1))
-                wait_value(&sy.done[my_tgt], 1, sy.err, sy.spin);
-            __syncthreads();
-            acquire_after_wait();
-        }
-        const T xv = handed ? wait_handed(&XB[gr], sy.err, sy.spin) : (PERSIST ? shared_load(&X[gr]) : X[gr]);
-        xr[tid] = rown < tk.r1 ? xv : T(0);
-        __syncthreads();
-        {
-            T a0 = T(0), a1 = T(0), a2 = T(0), a3 = T(0);
-#pragma unroll
-            for (int u = 0; u < RG; u += 4) {
-                a0 += pv[u] * xr[g * RG + u];
-                a1 += pv[u + 1] * xr[g * RG + u + 1];
-                a2 += pv[u + 2] * xr[g * RG + u + 2];
-                a3 += pv[u + 3] * xr[g * RG + u + 3];
-            }
-            Sm[g][k] = (a0 + a1) + (a2 + a3);
-        }
-        __syncthreads();
-        if (tid < NB) tq[tid] = Sm[0][tid] + Sm[1][tid] + Sm[2][tid] + Sm[3][tid];
-        __syncthreads();
-        bool fin = true;
-        if (tk.ntasks == 1) {
-            if (tid < nb) tq[tid] = xb - tq[tid];
-        } else if (finisher) {
-            if (tid < nb) tq[tid] = xb - (tq[tid] + ao[tid]);
-            if (tid == 0) sy.cnt[tk.blk] = 0;
-        } else {
-            // the partial sums are device-scope atomics and the finishing
-            // task reads them back with atomic exchanges: each thread only
-            // waits for its own atomics to be performed before the count
-            // goes up
-            if (tid < nb && tk.r1 > tk.r0) atomicAdd(&Acc[tk.g0 + tid], tq[tid]);
-            release_own();
-            __syncthreads();
-            if (PERSIST) {
-                if (tid == 0) atomicAdd(&sy.cnt[tk.blk], 1);
-                fin = false;
-            } else {
-                if (tid == 0) last = (atomicAdd(&sy.cnt[tk.blk], 1) == tk.ntasks - 1);
-                __syncthreads();
-                fin = last;
-                if (fin) {
-                    if (tid < nb)
-                        tq[tid] = X[tk.g0 + tid] - __hip_atomic_exchange(&Acc[tk.g0 + tid], T(0), __ATOMIC_RELAXED,
-                                                                         __HIP_MEMORY_SCOPE_AGENT);
-                    if (tid == 0) sy.cnt[tk.blk] = 0;
-                }
-            }
-        }
-        if (fin) {
-            // x_q = Linv^T t (rows of t beyond nb meet zero entries of qv)
-            __syncthreads();
-            T a0 = T(0), a1 = T(0);
-#pragma unroll
-            for (int s2 = 0; s2 < QW; s2 += 2) {
-                a0 += qv[s2] * tq[inv_row(s2)];
-                a1 += qv[s2 + 1] * tq[inv_row(s2 + 1)];
-            }
-            T a = a0 + a1;
-            a += __shfl_xor(a, 1);
-            a += __shfl_xor(a, 2);
-            if ((tid & 3) == 0 && oc < nb) {
-                if (PERSIST) {
-                    shared_store(&X[tk.g0 + oc], a);
-                    if (tk.hand & kHandIn) shared_store(&XB[tk.g0 + oc], a);
-                } else {
-                    X[tk.g0 + oc] = a;
-                }
-            }
-            if (PERSIST) {
-                release_own();
-                __syncthreads();
-                if (tid == 0) atomicExch(&sy.done[tk.blk], 1);
-            }
-        }
-        __syncthreads();
-    }
-}
-
 // Four consecutive entries from an address aligned to one entry; they may
 // reach up to three entries past what the caller uses (the panel and the
 // inverse stores are allocated with that slack), and the caller masks them.
@@ -2274,6 +2132,185 @@ __device__ __forceinline__ Quad<T> load_quad(const T *p) {
     return q;
 }
 
+// Persistent sweep: x of this lane's rows of the row tiles u0 .. u0 + NU - 1 of
+// a task (row 64 u + row0 + j), all loads together, until every one has been
+// put into XB (bounded; 0 once a wait gave up).  Rows beyond the task give 0.
+template <typename T, int NU>
+__device__ __forceinline__ void fetch_rows(const T *XB, const int32_t *grs, int row0, int u0, int nrows, int nrhs,
+                                           int64_t q, const SolveSync &sy, T *xv) {
+    bool ready = false;
+    for (int it = 0; it < sy.spin; ++it) {
+        bool unset = false;
+#pragma unroll
+        for (int e = 0; e < 4 * NU; ++e)
+            xv[e] = shared_load(&XB[(int64_t)grs[64 * (u0 + e / 4) + row0 + e % 4] * nrhs + q]);
+#pragma unroll
+        for (int e = 0; e < 4 * NU; ++e)
+            unset = unset || (64 * (u0 + e / 4) + row0 + e % 4 < nrows && is_unset(xv[e]));
+        if (!__any(unset)) {
+            ready = true;
+            break;
+        }
+        if ((it & 255) == 255 && __hip_atomic_load(sy.err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) break;
+        __builtin_amdgcn_s_sleep(1);
+    }
+    if (!ready && (threadIdx.x & 63) == 0) flag_device_error(sy.err);
+#pragma unroll
+    for (int e = 0; e < 4 * NU; ++e)
+        xv[e] = ready && 64 * (u0 + e / 4) + row0 + e % 4 < nrows ? xv[e] : T(0);
+}
+
+// Backward, one task = rows r0..r1-1 below block q:
+//   sums S_c = sum_r L[r][c0+c] x[rows[r]],  t = X_q - S,  x_q = Linv_q^T t.
+// A block with one task finishes itself; a block split over several tasks
+// adds its sums into Acc.  In a level launch the last task to arrive
+// (sy.cnt) finishes the block.  In the persistent sweep the block's first
+// task does: it holds the rows nearest the block, whose x are final last,
+// and it is queued after the block's other tasks, so it collects their sums
+// (waiting on sy.cnt) before its own rows are ready, which keeps that
+// exchange off the chain of blocks.  Rows below the block belong to
+// ancestors, whose x is final before the block's tasks read it: in a level
+// launch by the order of the levels; in the persistent sweep every finished
+// x goes into XB, set to a pattern no result takes, and the readers poll the
+// values themselves.  The rows come from the block's ancestors in order, and
+// the x of a nearer ancestor needed those of all the farther ones, so a task
+// polls one value of its nearest ancestor's rows and then loads them all;
+// the first task of block q - 1 treats q's rows, which come first, apart:
+// everything else is done before they arrive.
+//
+// Persistent sweep, one right-hand side.  Wave w takes the rows 64 u + 16 w ..
+// + 15 of the task (u = 0 .. 3) for all 64 columns, lane l four consecutive
+// rows 4 (l / 16) .. + 3 of the columns 16 ct + l % 16 with wide loads (16
+// columns x 128 bytes an instruction) and x of its rows straight from XB;
+// the four lane groups add up by shuffles, the waves through LDS.  Bound by
+// latency from block to block.  With a done flag per block (raised after the
+// stores had completed, then polled, then x loaded) and a thread per column
+// (64 columns x 8 bytes an instruction) the sweep of the 60^3 grid took 513
+// us and that of the 32^2 grid 42, this form 465 and 34.  (FP64 at two
+// workgroups a CU spills 13 registers: 495 us.)
+template <typename T>
+__global__ __launch_bounds__(256) void k_solve_bwd(const SolveTask *tasks, int64_t ntasks, const int32_t *order,
+                                                   const int32_t *rows, const T *Lx, const T *Linv, T *X, T *Acc,
+                                                   T *XB, SolveSync sy) {
+    constexpr int NB = kNB, QW = 16, NT = NB / 16;
+    __shared__ T Sm[4][NB];    // sums of the 4 waves
+    __shared__ T tq[NB];
+    __shared__ int32_t grs[256];
+    __shared__ int32_t slot;
+    const int tid = threadIdx.x, lane = tid & 63, kq = lane & 15, kg = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), row0 = 16 * wave + 4 * kg;
+    // x_q = Linv^T t, with (Linv^T)[c][i] = Linv[i][c] nonzero for i >= c:
+    // four threads per output c, 16 rows i each, that part of Linv held in
+    // registers.
+    const int oc = tid >> 2;
+    auto inv_row = [&](int s2) { return QW * (tid & 3) + s2; };
+    for (int pass = 0;; ++pass) {
+        const int64_t t = next_task<true>(pass, order, sy.queue + 1, ntasks, &slot);
+        if (t < 0) return;
+        const SolveTask tk = tasks[t];
+        const int nb = tk.nb, nrows = tk.r1 - tk.r0;
+        const int64_t m = tk.m;
+        const T *P = Lx + tk.loff;
+        const T *Q = Linv + tk.ioff;
+        grs[tid] = rows[tk.roff + min<int64_t>(tk.r0 + tid, m - 1)];
+        Quad<T> av[4][NT];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int64_t r = min<int64_t>(tk.r0 + 64 * u + row0, m - 1);
+#pragma unroll
+            for (int ct = 0; ct < NT; ++ct)
+                av[u][ct] = load_quad(P + (int64_t)(tk.c0 + min(16 * ct + kq, nb - 1)) * m + r);
+        }
+        T qv[QW];
+#pragma unroll
+        for (int s2 = 0; s2 < QW; ++s2) {
+            const int i = inv_row(s2);
+            const T v = Q[min(i, nb - 1) + (int64_t)min(oc, nb - 1) * nb];
+            qv[s2] = (i >= oc && i < nb && oc < nb) ? v : T(0);
+        }
+        // the block's own forward values: final since the forward sweep, and
+        // overwritten only by the task that finishes this block
+        T xb = T(0);
+        if (tk.first) xb = X[tk.g0 + min(tid, nb - 1)];
+        if (tk.first && tk.ntasks > 1) {
+            // every other task of the block was dequeued before this one
+            if (tid == 0) {
+                wait_value(&sy.cnt[tk.blk], tk.ntasks - 1, sy.err, sy.spin);
+                sy.cnt[tk.blk] = 0;
+            }
+            __syncthreads();
+            if (tid < nb)
+                xb -= __hip_atomic_exchange(&Acc[tk.g0 + tid], T(0), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+        const int nhand = (tk.hand & kHandOut) ? tk.hand >> 8 : 0;  // rows of the next block
+        __syncthreads();
+        if (nrows < 256) {
+            // a ragged task: what the wide loads took beyond its rows
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    const bool in = 64 * u + row0 + j < nrows;
+#pragma unroll
+                    for (int ct = 0; ct < NT; ++ct) av[u][ct].v[j] = in ? av[u][ct].v[j] : T(0);
+                }
+        }
+        T sum[NT];
+#pragma unroll
+        for (int ct = 0; ct < NT; ++ct) sum[ct] = T(0);
+        auto add = [&](int u, const T *xv) {
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+#pragma unroll
+                for (int ct = 0; ct < NT; ++ct) sum[ct] += av[u][ct].v[j] * xv[j];
+        };
+        if (nhand < nrows) (void)wait_handed(&XB[grs[nhand]], sy.err, sy.spin);
+        if (nrows > 64) {
+            T xf[12];
+            fetch_rows<T, 3>(XB, grs, row0, 1, nrows, 1, 0, sy, xf);
+#pragma unroll
+            for (int u = 3; u >= 1; --u) add(u, xf + 4 * (u - 1));
+        }
+        if (nrows > 0) {
+            T xn[4];
+            fetch_rows<T, 1>(XB, grs, row0, 0, nrows, 1, 0, sy, xn);
+            add(0, xn);
+        }
+#pragma unroll
+        for (int ct = 0; ct < NT; ++ct) {
+            sum[ct] += __shfl_xor(sum[ct], 16);
+            sum[ct] += __shfl_xor(sum[ct], 32);
+            if (kg == 0) Sm[wave][16 * ct + kq] = sum[ct];
+        }
+        __syncthreads();
+        if (tk.first) {
+            if (tid < NB) tq[tid] = tid < nb ? xb - ((Sm[0][tid] + Sm[1][tid]) + (Sm[2][tid] + Sm[3][tid])) : T(0);
+            __syncthreads();
+            // x_q = Linv^T t
+            T a0 = T(0), a1 = T(0);
+#pragma unroll
+            for (int s2 = 0; s2 < QW; s2 += 2) {
+                a0 += qv[s2] * tq[inv_row(s2)];
+                a1 += qv[s2 + 1] * tq[inv_row(s2 + 1)];
+            }
+            T a = a0 + a1;
+            a += __shfl_xor(a, 1);
+            a += __shfl_xor(a, 2);
+            if ((tid & 3) == 0 && oc < nb) {
+                shared_store(&XB[tk.g0 + oc], a);
+                X[tk.g0 + oc] = a;
+            }
+        } else {
+            if (tid < nb)
+                atomicAdd(&Acc[tk.g0 + tid], (Sm[0][tid] + Sm[1][tid]) + (Sm[2][tid] + Sm[3][tid]));
+            release_own();
+            __syncthreads();
+            if (tid == 0) atomicAdd(&sy.cnt[tk.blk], 1);
+        }
+        __syncthreads();
+    }
+}
+
 // Backward, several right-hand sides (up to kMaxRhs): the steps of
 // k_solve_bwd, with both products on 16x16x4 MFMA blocks.
 //   sums: S[c][q] = sum_r L[r][c0+c] X[rows[r]][q].  Wave w takes rows
@@ -2286,8 +2323,8 @@ __device__ __forceinline__ Quad<T> load_quad(const T *p) {
 //     waves, so the chain from block to block sees a quarter of their
 //     products; the panel, the inverse and the other rows' products are
 //     done before.
-//   x_q = Linv^T t: wave w the outputs 16 w .. 16 w + 15, the inverse's
-//     columns in registers, t from LDS.
+//   x_q = Linv^T t: wave w the outputs 16 w .. 16 w + 15, the inverse and t
+//     from LDS.
 // Bound by latency: the chain of blocks at the top of the tree, one block
 // waiting for the x of the next.  Polling a lane's four values together
 // (rather than one right-hand side after the other) and wide panel loads (16
@@ -2296,17 +2333,21 @@ __device__ __forceinline__ Quad<T> load_quad(const T *p) {
 // us and the refined FP32 8-column re-solve of a 50^3 grid from 5170 to 3235,
 // against the vector-FMA form with x in LDS that this replaced for all counts
 // (at 4 right-hand sides, FP64: 48^3 elasticity step 65.7 to 65.1 ms).
+// Polling the x values of all rows instead of a done flag per block, and the
+// inverse in LDS instead of registers, took the persistent sweep of a 50^3
+// grid (FP32, 8) from 324 to 280 us, of the 20^3 elasticity operator (FP32,
+// 4) from 186 to 151, of a 200^2 grid (FP64, 8) from 109 to 80.
 template <typename T, bool PERSIST>
 __global__ __launch_bounds__(256, 2) void k_solve_bwd_multi(const SolveTask *tasks, int64_t ntasks,
                                                             const int32_t *order, const int32_t *rows, const T *Lx,
                                                             const T *Linv, T *X, T *Acc, T *XB, int64_t n, int nrhs,
-                                                            const int64_t *tgt_ptr, const int32_t *tgt,
                                                             SolveSync sy) {
     constexpr int NB = kNB, NR = kMaxRhs, NT = NB / 16, EPT = NB * NR / 256;
     using M = Mfma<T>;
     using acc_t = typename M::acc;
     __shared__ T Sm[4][NB][NR + 1];  // each wave's sums
     __shared__ T tq[NB][NR + 1];
+    __shared__ T Qs[NB][NB + 1];  // Qs[c][i] = the block inverse's (i, c), zero above its diagonal and beyond nb
     __shared__ int32_t grs[256];
     __shared__ int last;
     __shared__ int32_t slot;
@@ -2329,7 +2370,7 @@ __global__ __launch_bounds__(256, 2) void k_solve_bwd_multi(const SolveTask *tas
         // sweep, of mostly full blocks, keeps the unconditional form.
         auto row_tile = [&](int u) { return PERSIST || 64 * u + 16 * wave < nrows; };
         auto col_tile = [&](int ct) { return PERSIST || ct < ntile; };
-        Quad<T> av[4][NT], qv[NT];
+        Quad<T> av[4][NT];
         grs[tid] = rows[tk.roff + min<int64_t>(tk.r0 + tid, m - 1)];
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
@@ -2342,18 +2383,21 @@ __global__ __launch_bounds__(256, 2) void k_solve_bwd_multi(const SolveTask *tas
                     av[u][ct] = Quad<T>{};
             }
         }
-        // the inverse's column c = 16 wave + kq, rows 16 s + 4 kg ..
-        const int c = 16 * wave + kq;
+        const bool may_finish = !PERSIST || tk.first;
+        if (may_finish) {
+            T ld[NB * NB / 256];
 #pragma unroll
-        for (int s = 0; s < NT; ++s)
-            qv[s] = col_tile(s) ? load_quad(Q + (int64_t)min(c, nb - 1) * nb + min(16 * s + 4 * kg, nb - 1))
-                                : Quad<T>{};
-        int32_t my_tgt = -1;
-        if (PERSIST) {
-            // at most one target block per row of the task
-            const int64_t tb = tgt_ptr[t], te = tgt_ptr[t + 1];
-            if (tid < te - tb) my_tgt = tgt[tb + tid];
+            for (int u = 0; u < NB * NB / 256; ++u) {
+                const int e = tid + 256 * u, i = e % NB, k = e / NB;
+                ld[u] = Q[(int64_t)min(k, nb - 1) * nb + min(i, nb - 1)];
+            }
+#pragma unroll
+            for (int u = 0; u < NB * NB / 256; ++u) {
+                const int e = tid + 256 * u, i = e % NB, k = e / NB;
+                Qs[k][i] = i >= k && i < nb && k < nb ? ld[u] : T(0);
+            }
         }
+        const int c = 16 * wave + kq;  // this lane's column of the inverse
         // the block's own forward values (as in k_solve_bwd); thread's
         // entries (row ei(v), right-hand side kq)
         auto ei = [&](int v) { return (tid >> 4) + 16 * v; };
@@ -2380,11 +2424,7 @@ __global__ __launch_bounds__(256, 2) void k_solve_bwd_multi(const SolveTask *tas
             acquire_after_wait();
             take_acc();
         }
-        const int nhand = (PERSIST && (tk.hand & kHandOut)) ? tk.hand >> 8 : 0;  // rows that come through XB
-        if (PERSIST) {
-            if (my_tgt >= 0 && !(nhand && my_tgt == tk.blk + 1)) wait_value(&sy.done[my_tgt], 1, sy.err, sy.spin);
-            acquire_after_wait();
-        }
+        const int nhand = (PERSIST && (tk.hand & kHandOut)) ? tk.hand >> 8 : 0;  // rows of the next block
         __syncthreads();
         if (nrows < 256) {
             // a ragged task: what the wide loads took beyond its rows
@@ -2400,49 +2440,38 @@ __global__ __launch_bounds__(256, 2) void k_solve_bwd_multi(const SolveTask *tas
         acc_t acc[NT];
 #pragma unroll
         for (int ct = 0; ct < NT; ++ct) acc[ct] = acc_t{0, 0, 0, 0};
-        T xv[4];  // x of the lane's four rows of one u
         auto at = [&](int u, int j) { return 64 * u + 16 * wave + 4 * kg + j; };
-        auto product = [&](int u) {
+        auto product = [&](int u, const T *xv) {
 #pragma unroll
             for (int j = 0; j < 4; ++j)
 #pragma unroll
                 for (int ct = 0; ct < NT; ++ct)
                     if (col_tile(ct)) acc[ct] = M::run(av[u][ct].v[j], xv[j], acc[ct]);
         };
+        if constexpr (PERSIST) {
+            if (nhand < nrows) (void)wait_handed(&XB[(int64_t)grs[nhand] * nrhs], sy.err, sy.spin);
+            T xf[12], xn[4];
+            if (nrows > 64) {
+                fetch_rows<T, 3>(XB, grs, 16 * wave + 4 * kg, 1, nrows, nrhs, q, sy, xf);
 #pragma unroll
-        for (int u = 3; u >= (PERSIST ? 1 : 0); --u) {
-            if (!row_tile(u)) continue;
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const T *px = &X[(int64_t)grs[at(u, j)] * nrhs + q];
-                const T v = PERSIST ? shared_load(px) : *px;
-                xv[j] = at(u, j) < nrows ? v : T(0);
+                for (int u = 3; u >= 1; --u) product(u, xf + 4 * (u - 1));
             }
-            product(u);
-        }
-        if (PERSIST) {
-            // the rows nearest the block: four values a lane, polled together
-            const T *px[4];
+            if (nrows > 0) {
+                fetch_rows<T, 1>(XB, grs, 16 * wave + 4 * kg, 0, nrows, nrhs, q, sy, xn);
+                product(0, xn);
+            }
+        } else {
 #pragma unroll
-            for (int j = 0; j < 4; ++j) px[j] = (at(0, j) < nhand ? XB : X) + (int64_t)grs[at(0, j)] * nrhs + q;
-            bool ready = false;
-            for (int it = 0; it < sy.spin; ++it) {
-                bool unset = false;
+            for (int u = 3; u >= 0; --u) {
+                if (!row_tile(u)) continue;
+                T xv[4];
 #pragma unroll
-                for (int j = 0; j < 4; ++j) xv[j] = shared_load(px[j]);
-#pragma unroll
-                for (int j = 0; j < 4; ++j) unset = unset || (at(0, j) < nhand && is_unset(xv[j]));
-                if (!__any(unset)) {
-                    ready = true;
-                    break;
+                for (int j = 0; j < 4; ++j) {
+                    const T v = X[(int64_t)grs[at(u, j)] * nrhs + q];
+                    xv[j] = at(u, j) < nrows ? v : T(0);
                 }
-                if ((it & 255) == 255 && __hip_atomic_load(sy.err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) break;
-                __builtin_amdgcn_s_sleep(1);
+                product(u, xv);
             }
-            if (!ready && lane == 0) flag_device_error(sy.err);
-#pragma unroll
-            for (int j = 0; j < 4; ++j) xv[j] = at(0, j) < nrows && ready ? xv[j] : T(0);
-            product(0);
         }
 #pragma unroll
         for (int ct = 0; ct < NT; ++ct)
@@ -2485,8 +2514,7 @@ __global__ __launch_bounds__(256, 2) void k_solve_bwd_multi(const SolveTask *tas
 #pragma unroll
             for (int v = 0; v < EPT; ++v) tq[ei(v)][kq] = ei(v) < nb ? xb[v] - sum[v] : T(0);
             __syncthreads();
-            // x_q = Linv^T t; the inverse is zero above row c and has no row
-            // beyond nb
+            // x_q = Linv^T t; the inverse is zero above row c
             acc_t xa[2] = {acc_t{0, 0, 0, 0}, acc_t{0, 0, 0, 0}};
 #pragma unroll
             for (int s = 0; s < NT; ++s)
@@ -2494,8 +2522,7 @@ __global__ __launch_bounds__(256, 2) void k_solve_bwd_multi(const SolveTask *tas
 #pragma unroll
                     for (int j = 0; j < 4; ++j) {
                         const int i = 16 * s + 4 * kg + j;
-                        const T a = (i >= c && i < nb) ? qv[s].v[j] : T(0);
-                        xa[j & 1] = M::run(a, tq[i][kq], xa[j & 1]);
+                        xa[j & 1] = M::run(Qs[c][i], tq[i][kq], xa[j & 1]);
                     }
 #pragma unroll
             for (int v = 0; v < 4; ++v) {
@@ -2503,18 +2530,9 @@ __global__ __launch_bounds__(256, 2) void k_solve_bwd_multi(const SolveTask *tas
                 const T xo = xa[0][v] + xa[1][v];
                 if (co < nb && kq < nrhs) {
                     const int64_t e = (int64_t)(tk.g0 + co) * nrhs + kq;
-                    if (PERSIST) {
-                        if (tk.hand & kHandIn) shared_store(&XB[e], xo);
-                        shared_store(&X[e], xo);
-                    } else {
-                        X[e] = xo;
-                    }
+                    if (PERSIST) shared_store(&XB[e], xo);
+                    X[e] = xo;
                 }
-            }
-            if (PERSIST) {
-                release_own();
-                __syncthreads();
-                if (tid == 0) atomicExch(&sy.done[tk.blk], 1);
             }
         }
         __syncthreads();
@@ -2709,24 +2727,14 @@ __global__ __launch_bounds__(256) void k_solve_tiny_bwd(const SmallTask *tasks, 
     }
 }
 
-// Per solve: dep <- the forward counts, done and cnt <- 0, queues <- 0.  The
-// error word is the factor's, cleared only by a factorization, so a wait
-// that gave up stays reported.
-__global__ void k_solve_reset(const int32_t *fdep, int64_t nblocks, SolveSync sy) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < nblocks) {
-        sy.dep[i] = fdep[i];
-        sy.done[i] = 0;
-        sy.cnt[i] = 0;
-    }
-    if (i < 2) sy.queue[i] = 0;
-}
-
-// The hand-over buffers of a solve: every entry unset.
+// Between the persistent sweeps: the backward hand-over buffer (Y, spent)
+// unset, the partial sums (Acc, the forward hand-over buffer) zero.
 template <typename T>
-__global__ void k_fill_unset(T *p, int64_t count) {
+__global__ void k_solve_turn(T *Y, T *Acc, int64_t count) {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < count) p[i] = __builtin_bit_cast(T, Unset<T>::bits);
+    if (i >= count) return;
+    Y[i] = __builtin_bit_cast(T, Unset<T>::bits);
+    Acc[i] = T(0);
 }
 
 // |v| for the maxima of refinement, with NaN mapped to +Inf: fmax drops a
@@ -3134,11 +3142,17 @@ void launch_persist_small(const DevPlan &P, int64_t nchunks, int64_t nsuper, int
 }
 
 template <typename T>
-void launch_perm_in(const DevPlan &P, int64_t n, int nrhs, const double *B, int64_t ldb, T *W,
-                    hipStream_t st) {
-    if (n * nrhs <= 0) return;
-    hipLaunchKernelGGL(k_perm_in<T>, dim3(grid1(n * nrhs, 256)), dim3(256), 0, st, P.perm, n, nrhs, B,
-                       ldb, W);
+void launch_solve_init(const DevPlan &P, int64_t n, int nrhs, const double *B, int64_t ldb, T *Y, T *Acc,
+                       bool persist, int64_t nblocks, SolveSync sy, hipStream_t st) {
+    const int64_t count = std::max<int64_t>(std::max<int64_t>(n * nrhs, nblocks), 2);
+    hipLaunchKernelGGL(k_solve_init<T>, dim3(grid1(count, 256)), dim3(256), 0, st, P.perm, n, nrhs, B, ldb, Y, Acc,
+                       persist ? 1 : 0, P.fdep, nblocks, sy);
+}
+
+template <typename T>
+void launch_solve_turn(T *Y, T *Acc, int64_t count, hipStream_t st) {
+    if (count <= 0) return;
+    hipLaunchKernelGGL(k_solve_turn<T>, dim3(grid1(count, 256)), dim3(256), 0, st, Y, Acc, count);
 }
 
 template <typename T>
@@ -3152,17 +3166,6 @@ void launch_perm_out(const DevPlan &P, int64_t n, int nrhs, const T *W, double *
 inline unsigned persist_grid(int64_t ntasks) {
     // two resident workgroups per CU on 256 CUs; more only queue behind them
     return (unsigned)std::max<int64_t>(1, std::min<int64_t>(ntasks, 512));
-}
-
-void launch_solve_reset(const DevPlan &P, int64_t nblocks, SolveSync sy, hipStream_t st) {
-    hipLaunchKernelGGL(k_solve_reset, dim3(grid1(std::max<int64_t>(nblocks, 2), 256)), dim3(256), 0, st, P.fdep,
-                       nblocks, sy);
-}
-
-template <typename T>
-void launch_fill_unset(T *p, int64_t count, hipStream_t st) {
-    if (count <= 0) return;
-    hipLaunchKernelGGL(k_fill_unset<T>, dim3(grid1(count, 256)), dim3(256), 0, st, p, count);
 }
 
 template <typename T>
@@ -3224,23 +3227,19 @@ void launch_solve_bwd(const DevPlan &P, int64_t t0, int64_t t1, const T *Lx, con
     const dim3 g(persist ? persist_grid(nt) : (unsigned)nt), b(256);
     // the persistent sweep takes its tasks (global indices) from bwd_order
     const SolveTask *tk = persist ? P.stasks : P.stasks + t0;
-    const int64_t *tp = persist ? P.stgt_ptr : P.stgt_ptr + t0;
     const int32_t *ord = persist ? P.bwd_order : nullptr;
-    if (nrhs == 1) {
-        if (persist)
-            hipLaunchKernelGGL((k_solve_bwd<T, true>), g, b, 0, st, tk, nt, ord, P.rows, Lx, Linv, X, Acc, XB, n, tp,
-                               P.stgt, sy);
-        else
-            hipLaunchKernelGGL((k_solve_bwd<T, false>), g, b, 0, st, tk, nt, ord, P.rows, Lx, Linv, X, Acc, XB, n, tp,
-                               P.stgt, sy);
-    } else {
-        if (persist)
-            hipLaunchKernelGGL((k_solve_bwd_multi<T, true>), g, b, 0, st, tk, nt, ord, P.rows, Lx, Linv, X, Acc, XB,
-                               n, nrhs, tp, P.stgt, sy);
-        else
-            hipLaunchKernelGGL((k_solve_bwd_multi<T, false>), g, b, 0, st, tk, nt, ord, P.rows, Lx, Linv, X, Acc, XB,
-                               n, nrhs, tp, P.stgt, sy);
-    }
+    // (level launches take the MFMA form for one right-hand side too: their
+    // tasks wait for nothing and only move the panel, 47 against 28 us a
+    // launch on the 60^3 grid; in the persistent sweep its longer path from
+    // block to block costs more, 657 against 465 us)
+    if (persist && nrhs == 1)
+        hipLaunchKernelGGL((k_solve_bwd<T>), g, b, 0, st, tk, nt, ord, P.rows, Lx, Linv, X, Acc, XB, sy);
+    else if (persist)
+        hipLaunchKernelGGL((k_solve_bwd_multi<T, true>), g, b, 0, st, tk, nt, ord, P.rows, Lx, Linv, X, Acc, XB, n,
+                           nrhs, sy);
+    else
+        hipLaunchKernelGGL((k_solve_bwd_multi<T, false>), g, b, 0, st, tk, nt, ord, P.rows, Lx, Linv, X, Acc, XB, n,
+                           nrhs, sy);
 }
 
 void launch_spmv(const int64_t *rowptr, const int32_t *colidx, const int64_t *valmap, const double *values,
@@ -3341,11 +3340,11 @@ template void launch_zero<unsigned long long>(unsigned long long *, int64_t, hip
     template void launch_trail128<T>(const DevPlan &, int64_t, int64_t, T *, bool, hipStream_t);            \
     template void launch_persist_small<T>(const DevPlan &, int64_t, int64_t, int32_t *, int32_t *, T *, T *, \
                                           unsigned long long *, PivotFloor<T>, WaitCtl, hipStream_t);       \
-    template void launch_perm_in<T>(const DevPlan &, int64_t, int, const double *, int64_t, T *,            \
-                                    hipStream_t);                                                           \
+    template void launch_solve_init<T>(const DevPlan &, int64_t, int, const double *, int64_t, T *, T *,     \
+                                       bool, int64_t, SolveSync, hipStream_t);                              \
+    template void launch_solve_turn<T>(T *, T *, int64_t, hipStream_t);                                     \
     template void launch_perm_out<T>(const DevPlan &, int64_t, int, const T *, double *, int64_t,           \
                                      hipStream_t);                                                          \
-    template void launch_fill_unset<T>(T *, int64_t, hipStream_t);                                         \
     template void launch_solve_fwd<T>(const DevPlan &, int64_t, int64_t, const T *, const T *, T *, T *, T *, \
                                       int64_t, int, SolveSync, bool, hipStream_t);                          \
     template void launch_solve_bwd<T>(const DevPlan &, int64_t, int64_t, const T *, const T *, T *, T *, T *, \
