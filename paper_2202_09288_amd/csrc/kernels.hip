@@ -191,6 +191,41 @@ __device__ __forceinline__ float row_bcast(float v) {
     return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x150 + C, 0xf, 0xf, true));
 }
 
+// Sums across lanes without a trip through LDS.  pair_add<CTRL>: v plus the
+// value of the lane that the DPP control names (kXor1, kXor2: inside a quad;
+// kRor4, kRor8: rotations of a row of 16); half_add<16 or 32>: v plus that of
+// the lane 16 or 32 away.
+constexpr int kXor1 = 0xb1, kXor2 = 0x4e, kRor4 = 0x124, kRor8 = 0x128;
+template <int CTRL>
+__device__ __forceinline__ float pair_add(float v) {
+    return v + __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xf, 0xf, true));
+}
+template <int CTRL>
+__device__ __forceinline__ double pair_add(double v) {
+    const long long b = __double_as_longlong(v);
+    const int lo = __builtin_amdgcn_update_dpp(0, (int)b, CTRL, 0xf, 0xf, true);
+    const int hi = __builtin_amdgcn_update_dpp(0, (int)(b >> 32), CTRL, 0xf, 0xf, true);
+    return v + __longlong_as_double(((long long)hi << 32) | (uint32_t)lo);
+}
+template <int D>
+__device__ __forceinline__ auto half_swap(uint32_t v) {
+    static_assert(D == 16 || D == 32, "rows or halves of the wave");
+    if constexpr (D == 16) return __builtin_amdgcn_permlane16_swap(v, v, false, false);
+    else return __builtin_amdgcn_permlane32_swap(v, v, false, false);
+}
+template <int D>
+__device__ __forceinline__ float half_add(float v) {
+    const auto r = half_swap<D>((uint32_t)__float_as_int(v));
+    return __int_as_float((int)r[0]) + __int_as_float((int)r[1]);
+}
+template <int D>
+__device__ __forceinline__ double half_add(double v) {
+    const long long b = __double_as_longlong(v);
+    const auto lo = half_swap<D>((uint32_t)b), hi = half_swap<D>((uint32_t)(b >> 32));
+    return __longlong_as_double(((long long)hi[0] << 32) | lo[0]) +
+           __longlong_as_double(((long long)hi[1] << 32) | lo[1]);
+}
+
 // 1/d: hardware estimate and one correction step (of third order in double,
 // whose estimate is good to about 1e-8).
 __device__ __forceinline__ double rcp_nr(double d) {
@@ -1949,12 +1984,8 @@ __global__ __launch_bounds__(256) void k_solve_fwd(const SolveTask *tasks, int64
                 a1 += (c + 1 <= vi ? qv[k + 1] : T(0)) * yq[c + 1];
             }
             T a = a0 + a1;
-            a += __shfl_xor(a, 1);
-            a += __shfl_xor(a, 2);
-            if (vp == 0) {
-                xq[vi] = vi < nb ? a : T(0);
-                if (tk.first && vi < nb) X[tk.g0 + vi] = a;
-            }
+            a = pair_add<kXor2>(pair_add<kXor1>(a));
+            if (vp == 0) xq[vi] = vi < nb ? a : T(0);
         }
         __syncthreads();
         if (r < tk.r1) {
@@ -1976,6 +2007,8 @@ __global__ __launch_bounds__(256) void k_solve_fwd(const SolveTask *tasks, int64
             __syncthreads();
             if (my_tgt >= 0 && !((tk.hand & kHandOut) && my_tgt == tk.blk + 1)) atomicSub(&sy.dep[my_tgt], 1);
         }
+        // (off the chain: after what others wait for)
+        if (tk.first && tid < nb) X[tk.g0 + tid] = xq[tid];
     }
 }
 
@@ -1988,6 +2021,11 @@ __global__ __launch_bounds__(256) void k_solve_fwd(const SolveTask *tasks, int64
 // form then keeps 256 registers with a spill of two): the persistent sweep
 // runs twice as many resident workgroups, so the tasks waiting on a block
 // leave room for the ones on the chain.
+// Bound by latency from block to block.  A thread's handed-over values polled
+// together instead of one after the other, and x stored after what other
+// tasks wait for, took the persistent sweep of a 50^3 grid (FP32, 8 right-hand
+// sides) from 382 to 312 us, of the 30x29x27 elasticity operator (FP64, 16)
+// from 441 to 376.
 template <typename T, bool PERSIST>
 __global__ __launch_bounds__(256, 2) void k_solve_fwd_multi(const SolveTask *tasks, int64_t ntasks,
                                                          const int32_t *rows, const T *Lx, const T *Linv, T *Y,
@@ -2066,11 +2104,35 @@ __global__ __launch_bounds__(256, 2) void k_solve_fwd_multi(const SolveTask *tas
             const T *py = &Y[(tk.g0 + min(i, nb - 1)) * nrhs + min(q, nrhs - 1)];
             yv[u] = PERSIST ? shared_load(py) : *py;
         }
+        if (PERSIST && (tk.hand & kHandIn)) {
+            // the previous block's sums for these rows, a thread's values
+            // polled together (padding repeats a real entry)
+            T hv[YPT];
+            bool ready = false;
+            for (int it = 0; it < sy.spin; ++it) {
+                bool unset = false;
+#pragma unroll
+                for (int u = 0; u < YPT; ++u) {
+                    const int e = tid + 256 * u, i = e / NR, q = e % NR;
+                    hv[u] = shared_load(&H[(tk.g0 + min(i, nb - 1)) * nrhs + min(q, nrhs - 1)]);
+                }
+#pragma unroll
+                for (int u = 0; u < YPT; ++u) unset = unset || is_unset(hv[u]);
+                if (!__any(unset)) {
+                    ready = true;
+                    break;
+                }
+                if ((it & 255) == 255 && __hip_atomic_load(sy.err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
+                    break;
+                __builtin_amdgcn_s_sleep(1);
+            }
+            if (!ready && lane == 0) flag_device_error(sy.err);
+#pragma unroll
+            for (int u = 0; u < YPT; ++u) yv[u] -= ready ? hv[u] : T(0);
+        }
 #pragma unroll
         for (int u = 0; u < YPT; ++u) {
             const int e = tid + 256 * u, i = e / NR, q = e % NR;
-            if (PERSIST && (tk.hand & kHandIn) && i < nb && q < nrhs)
-                yv[u] -= wait_handed(&H[(tk.g0 + i) * nrhs + q], sy.err, sy.spin);
             yq[i][q] = (i < nb && q < nrhs) ? yv[u] : T(0);
         }
         __syncthreads();
@@ -2083,11 +2145,6 @@ __global__ __launch_bounds__(256, 2) void k_solve_fwd_multi(const SolveTask *tas
             for (int v = 0; v < 4; ++v) xq[16 * wave + Mfma<T>::row(lane, v)][lane & 15] = xa[v];
         }
         __syncthreads();
-        if (tk.first)
-            for (int e = tid; e < nb * nrhs; e += 256) {
-                const int i = e / nrhs, q = e % nrhs;
-                X[(tk.g0 + i) * nrhs + q] = xq[i][q];
-            }
         // rows of x_q beyond nb are zero, so the clamped columns contribute nothing
 #pragma unroll
         for (int tt = 0; tt < 4; ++tt) {
@@ -2114,6 +2171,11 @@ __global__ __launch_bounds__(256, 2) void k_solve_fwd_multi(const SolveTask *tas
             __syncthreads();
             if (my_tgt >= 0 && !((tk.hand & kHandOut) && my_tgt == tk.blk + 1)) atomicSub(&sy.dep[my_tgt], 1);
         }
+        if (tk.first)
+            for (int e = tid; e < nb * nrhs; e += 256) {
+                const int i = e / nrhs, q = e % nrhs;
+                X[(tk.g0 + i) * nrhs + q] = xq[i][q];
+            }
         __syncthreads();
     }
 }
@@ -2186,7 +2248,7 @@ __device__ __forceinline__ void fetch_rows(const T *XB, const int32_t *grs, int 
 // latency from block to block.  With a done flag per block (raised after the
 // stores had completed, then polled, then x loaded) and a thread per column
 // (64 columns x 8 bytes an instruction) the sweep of the 60^3 grid took 513
-// us and that of the 32^2 grid 42, this form 465 and 34.  (FP64 at two
+// us and that of the 32^2 grid 42, this form 444 and 30.  (FP64 at two
 // workgroups a CU spills 13 registers: 495 us.)
 template <typename T>
 __global__ __launch_bounds__(256) void k_solve_bwd(const SolveTask *tasks, int64_t ntasks, const int32_t *order,
@@ -2278,8 +2340,7 @@ __global__ __launch_bounds__(256) void k_solve_bwd(const SolveTask *tasks, int64
         }
 #pragma unroll
         for (int ct = 0; ct < NT; ++ct) {
-            sum[ct] += __shfl_xor(sum[ct], 16);
-            sum[ct] += __shfl_xor(sum[ct], 32);
+            sum[ct] = half_add<32>(half_add<16>(sum[ct]));
             if (kg == 0) Sm[wave][16 * ct + kq] = sum[ct];
         }
         __syncthreads();
@@ -2294,8 +2355,7 @@ __global__ __launch_bounds__(256) void k_solve_bwd(const SolveTask *tasks, int64
                 a1 += qv[s2 + 1] * tq[inv_row(s2 + 1)];
             }
             T a = a0 + a1;
-            a += __shfl_xor(a, 1);
-            a += __shfl_xor(a, 2);
+            a = pair_add<kXor2>(pair_add<kXor1>(a));
             if ((tid & 3) == 0 && oc < nb) {
                 shared_store(&XB[tk.g0 + oc], a);
                 X[tk.g0 + oc] = a;
@@ -2643,9 +2703,8 @@ __global__ __launch_bounds__(256) void k_solve_tiny_fwd(const SmallTask *tasks, 
 
 template <typename T>
 __device__ __forceinline__ T wave_sum(T v) {
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off);
-    return v;
+    v = pair_add<kRor8>(pair_add<kRor4>(pair_add<kXor2>(pair_add<kXor1>(v))));
+    return half_add<32>(half_add<16>(v));
 }
 
 // Backward: t_c = X[g0 + c] - sum_{i >= w} L[i][c] X[rows[i]] for the w
@@ -3231,7 +3290,7 @@ void launch_solve_bwd(const DevPlan &P, int64_t t0, int64_t t1, const T *Lx, con
     // (level launches take the MFMA form for one right-hand side too: their
     // tasks wait for nothing and only move the panel, 47 against 28 us a
     // launch on the 60^3 grid; in the persistent sweep its longer path from
-    // block to block costs more, 657 against 465 us)
+    // block to block costs more, 657 against 444 us)
     if (persist && nrhs == 1)
         hipLaunchKernelGGL((k_solve_bwd<T>), g, b, 0, st, tk, nt, ord, P.rows, Lx, Linv, X, Acc, XB, sy);
     else if (persist)
