@@ -80,7 +80,9 @@ typedef struct spc_options {
      *   small_w, small_m  the same limits for one workgroup each; at most 32
      *                     and 128 (default 32, 128)
      *   big_min, big_min_k  scatter updates with m - w >= big_min and
-     *                     w >= big_min_k use 128x128 tiles (default 256, 128)
+     *                     w >= big_min_k use 128x128 tiles (default 256, 128,
+     *                     and then only in the levels that have at least 256
+     *                     such tiles)
      *   solve_persist_max  solve levels from the top with fewer tasks than
      *                     this run as one persistent launch per sweep
      *                     (default 1024)
@@ -101,7 +103,9 @@ typedef struct spc_options {
      *                     64-column blocks receive the group's update once,
      *                     with K = 64 * delay, while each next block inside
      *                     the group is brought up to date on its own; at most
-     *                     8 (default 1; a negative value keeps 1)
+     *                     8; a negative value keeps 1.  Default: 4 with
+     *                     lookahead and hand-over rule 2 where a level has at
+     *                     least 3500 64x64 tiles beyond the step's block, else 1
      *   persist           1: every small subtree (a supernode whose whole
      *                     subtree is within the one-wave or one-workgroup
      *                     limits), of every system of a batch, is factored by
@@ -124,8 +128,9 @@ typedef struct spc_options {
      *                     only the next group's columns at once; the columns
      *                     beyond get it in the next group's other steps,
      *                     beside their column updates and factorizations; a
-     *                     negative value (the default, 0) updates them all
-     *                     at the end of the group
+     *                     negative value updates them all at the end of the
+     *                     group.  Default: off with a given delay, on with the
+     *                     default one
      * Values beyond a kernel's limit give SPC_INVALID_INPUT. */
     int32_t tiny_w, tiny_m, small_w, small_m;
     int32_t big_min, big_min_k, solve_persist_max;

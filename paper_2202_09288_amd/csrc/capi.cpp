@@ -923,7 +923,9 @@ int spc_analyze(int64_t n, const int64_t *h_colptr, const int32_t *h_rowidx, con
                         pick(opts->ordering, 0, 2, 0, &tu.ordering) &&
                         pick(opts->group, 1, 1, 0, &tu.group) &&
                         pick(opts->bulk128, 0, 1, 0, &tu.bulk128) &&
-                        pick(opts->lookahead, 0, 1, 0, &tu.lookahead);
+                        pick(opts->lookahead, opts->delay == 0 ? 1 : 0, 1, 0, &tu.lookahead);
+        tu.delay_auto = opts->delay == 0;
+        tu.big_fill = opts->big_min == 0 && opts->big_min_k == 0 ? spc::kBigFill : 0;
         if (!ok) {
             delete s;
             return SPC_INVALID_INPUT;

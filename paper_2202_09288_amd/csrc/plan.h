@@ -30,16 +30,30 @@ constexpr int kGroupW = 4;
 // triangle gets an explicit inverse in the inverse store.
 constexpr int kNB = 64;
 constexpr int kPanelNB = kNB;
-// Column blocks per bulk trailing update (default; a tuning option): the
-// columns beyond a group of `delay` blocks are updated once, with all of the
-// group's panels (K = delay * kNB), while each next block inside the group
-// is brought up to date on its own just before it is factored.  Measured on
-// the 60^3 grid: 1 -> 16.3 ms, 2 -> 16.6, 3 -> 17.0, 4 -> 17.3 (the
-// column-only launches lengthen the chain of dependent steps more than the
-// deeper updates save); workloads whose top supernodes are bound by the
-// trailing update's memory traffic rather than by that chain can gain.
+// A level uses 128x128 scatter tiles only if it has at least this many of
+// them, one per CU: with fewer, four times as many 64x64 tiles finish sooner
+// because each has a quarter of the work and CUs stay idle otherwise.
+// Measured, without the rule and with 128, 256, 512: 34^3 FP64 2.42, 2.28,
+// 2.23, 2.23 ms, 34^3 FP32 2.00, 1.90, 1.85, 1.86, 48^3 elasticity (whose
+// levels have thousands) 59.4, 59.2, 59.4, 59.5.
+constexpr int kBigFill = 256;
+// Column blocks per bulk trailing update (a tuning option): the columns
+// beyond a group of `delay` blocks are updated once, with all of the group's
+// panels (K = delay * kNB), while each next block inside the group is brought
+// up to date on its own just before it is factored.  A deeper update reads
+// and writes the trailing columns once for all its panels but lengthens the
+// chain of dependent steps.  So by default a group has one block, and
+// kDelayAuto where the level has at least kDelayTiles 64x64 tiles beyond the
+// step's block: those move about 130 KB each at K = 64, which 3,500 take 90 us
+// for, several times a step of the chain.  Measured at thresholds 1000, 2000,
+// 3000, 4500, 9000 and none: 48^3 elasticity FP64 52.9, 53.0, 52.9, 53.2,
+// 55.4, 59.4 ms; 60^3 12.21, 12.00, 12.03, 11.99, 12.06, 12.05; 30x29x27
+// elasticity 5.52, 5.41, 5.39, 5.37, 5.40, 5.37.  Groups of 2, 3, 4, 6, 8:
+// 48^3 elasticity 55.7, 54.3, 53.8, 54.4, 54.8.
 constexpr int kDelay = 1;
 constexpr int kDelayMax = 8;
+constexpr int kDelayAuto = 4;
+constexpr int kDelayTiles = 3500;
 constexpr int kSolveNB = kNB;
 // Rows of one solve-update task.
 constexpr int kSolveRows = 256;
@@ -61,11 +75,13 @@ struct Tuning {
     int32_t solve_persist_max = kSolvePersistMax;
     int32_t handover = 1;  // fused TRSM with in-launch waits (0: off, 2: only where few tiles wait)
     int32_t delay = kDelay;  // column blocks per bulk trailing update
+    bool delay_auto = true;  // instead: kDelayAuto or one, by the rule at kDelayTiles
     int32_t persist = 0;     // small subtrees in one persistent launch (0: per level)
     int32_t ordering = 0;    // order computed by analyze when none is given (order_graph's method)
     int32_t group = 1;       // tiny supernodes of 16 / 32 rows share a wave (0: one wave each)
     int32_t bulk128 = 0;     // bulk trailing updates (K >= 128) on 128x128 tiles in a launch of their own
-    int32_t lookahead = 0;   // bulk update beyond the next group spread over that group's steps (delay >= 2)
+    int32_t big_fill = kBigFill;  // fewest 128x128 tiles of a level for them to be used
+    int32_t lookahead = 1;   // bulk update beyond the next group spread over that group's steps (delay >= 2)
 };
 
 // One pair (source supernode s, ancestor t) of the scatter: rows

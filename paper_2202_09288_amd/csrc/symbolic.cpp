@@ -17,6 +17,7 @@
 #include <new>
 
 #include "plan.h"
+
 #include "../../include/spchol.h"
 
 namespace spc {
@@ -524,6 +525,33 @@ int build_schedule(Symbolic &S) {
             int64_t w = S.super_ptr[s + 1] - S.super_ptr[s];
             maxb = std::max(maxb, (w + kNB - 1) / kNB);
         }
+        // groups of column blocks, the same for every supernode of the level:
+        // tu.delay blocks each, or, with delay_auto, by the rule at
+        // kDelayTiles on the 64x64 tiles of the columns beyond a step's block
+        std::vector<int32_t> gfirst(maxb), glast(maxb);  // of the group that holds block b
+        {
+            std::vector<int64_t> tiles(maxb, 0);
+            for (int32_t s : bylevel[l]) {
+                const int64_t w = S.super_ptr[s + 1] - S.super_ptr[s], m = S.rptr[s + 1] - S.rptr[s];
+                const int64_t nblk = (w + kNB - 1) / kNB, mt = (m + kNB - 1) / kNB;
+                for (int64_t b = 0; b + 1 < nblk; ++b) {
+                    const int64_t left = nblk - b - 1;
+                    tiles[b] += left * (mt - b - 1) - left * (left - 1) / 2;
+                }
+            }
+            for (int64_t b = 0; b < maxb;) {
+                int64_t d = tu.delay;
+                if (tu.delay_auto) d = tiles[b] >= kDelayTiles ? kDelayAuto : 1;
+                const int64_t e = std::min<int64_t>(b + d, maxb);
+                for (int64_t i = b; i < e; ++i) {
+                    gfirst[i] = (int32_t)b;
+                    glast[i] = (int32_t)(e - 1);
+                }
+                b = e;
+            }
+        }
+        // (a group that delay_auto made takes the hand-over by rule 2)
+        auto grouped = [&](int64_t b) { return tu.delay_auto && glast[b] > gfirst[b]; };
         // handover 2: a step takes the hand-over only where few of its
         // tiles wait (they hold their CUs while the block is factored):
         // eight or more supernodes get one, or the waiting tiles are at most
@@ -541,16 +569,17 @@ int build_schedule(Symbolic &S) {
         std::vector<std::vector<TileTask>> rest_at(maxb);
         std::vector<double> rest_fl(maxb, 0.0);
         {
-            const int64_t d = tu.delay;
-            const bool spread = tu.lookahead && d >= 2;
             for (int32_t s : bylevel[l]) {
                 const int64_t w = S.super_ptr[s + 1] - S.super_ptr[s], m = S.rptr[s + 1] - S.rptr[s];
                 for (int64_t b = 0; b * kNB < w; ++b) {
                     const int64_t c1 = std::min<int64_t>(b * kNB + kNB, w), cx = std::min<int64_t>(c1 + kNB, w);
                     if (c1 >= w) continue;
-                    const int64_t k0 = (b - b % d) * kNB, kd = c1 - k0;
-                    const bool close = b % d == d - 1 || cx >= w;
+                    const int64_t k0 = gfirst[b] * kNB, kd = c1 - k0;
+                    const bool close = b == glast[b] || cx >= w;
                     if (!close || (tu.bulk128 && kd >= kTileBig)) continue;
+                    // the next group, whose other steps take the columns beyond it
+                    const int64_t d = glast[b + 1] - b;
+                    const bool spread = tu.lookahead && d >= 2;
                     const int64_t cn = spread ? std::min<int64_t>(w, c1 + d * kNB) : w;
                     int64_t t = 0;
                     for (int64_t j0 = c1 + kTile; j0 < w; j0 += kTile)
@@ -570,11 +599,11 @@ int build_schedule(Symbolic &S) {
         }
         std::vector<char> fuse_step(maxb, 0);
         for (int64_t b = 0; b < maxb; ++b) {
-            if (tu.handover == 1) {
+            if (tu.handover == 1 && !grouped(b)) {
                 fuse_step[b] = 1;
                 continue;
             }
-            if (tu.handover != 2) continue;
+            if (tu.handover <= 0) continue;
             int64_t B = 0, nsup = 0;
             for (int32_t s : bylevel[l]) {
                 const int64_t w = S.super_ptr[s + 1] - S.super_ptr[s], m = S.rptr[s + 1] - S.rptr[s];
@@ -597,12 +626,12 @@ int build_schedule(Symbolic &S) {
             st.f0 = (int64_t)S.potrf_tasks.size();
             st.p0 = (int64_t)S.trsm_tiles.size();
             st.t0 = (int64_t)S.int_tiles.size();
-            // Blocks go in groups of tu.delay.  Inside a group, step b brings
+            // Blocks go in groups (above).  Inside a group, step b brings
             // block b+1's columns up to date with the group's panels so far
             // (one column of tiles, K = the group's columns up to b) and
             // factors block b+1 in that column's diagonal tile; the last step
             // of a group updates every column beyond with all of the group's
-            // panels at once (K = tu.delay blocks).
+            // panels at once (K = the group's blocks).
             // The trailing launch holds the diagonal tiles of block b+1 first
             // (which also factor it), then the columns beyond block b+1 and
             // the tiles below block b+1's diagonal.  When block b+1 is a full
@@ -611,8 +640,8 @@ int build_schedule(Symbolic &S) {
             // own; the block's factorization is claimed by the first of its
             // workgroups to arrive (k_tiles), so no tile ever waits for one
             // that has not started.
-            const int64_t gb = b - b % tu.delay;  // first block of b's group
-            const bool bulk = b % tu.delay == tu.delay - 1;
+            const int64_t gb = gfirst[b];  // first block of b's group
+            const bool bulk = b == glast[b];
             std::vector<TileTask> diag, rest(rest_at[b]), below;
             st.rest_flops += rest_fl[b];
             std::vector<int32_t> below_diag;  // diagonal tile of each waiting tile (index into diag)
@@ -748,9 +777,18 @@ int build_schedule(Symbolic &S) {
         }
         S.level_step_ptr[l + 1] = (int64_t)S.steps.size();
         double ef = 0.0, efb = 0.0;
+        // 128x128 tiles only where a level has enough of them (kBigFill)
+        int64_t big_tiles = 0;
+        for (int32_t s : bylevel[l]) {
+            const int64_t w = S.super_ptr[s + 1] - S.super_ptr[s], m = S.rptr[s + 1] - S.rptr[s];
+            if (m - w < tu.big_min || w < tu.big_min_k) continue;
+            const int64_t t = (m - w + kTileBig - 1) / kTileBig;
+            big_tiles += t * (t + 1) / 2;
+        }
+        const bool big_level = big_tiles >= tu.big_fill;
         for (int32_t s : bylevel[l]) {
             int64_t w = S.super_ptr[s + 1] - S.super_ptr[s], m = S.rptr[s + 1] - S.rptr[s];
-            const bool big = m - w >= tu.big_min && w >= tu.big_min_k;
+            const bool big = big_level && m - w >= tu.big_min && w >= tu.big_min_k;
             (big ? efb : ef) += (double)(m - w) * (double)(m - w + 1) * (double)w;
             const int64_t tsz = big ? kTileBig : kTile;
             for (int64_t j0 = w; j0 < m; j0 += tsz)

@@ -158,3 +158,14 @@ def test_tiny_supernode_shapes(lib, w, b, group, precision):
     err, eta, _ = factor_and_solve(lib, matrix, {"group": group}, precision)
     print(f"w={w} b={b} group={group} {precision}: worst supernode {err:.2e}, eta {eta:.2e}", flush=True)
     assert err <= (1e-10 if precision == "fp64" else 1e-4) and eta <= BAR[precision]
+
+
+def test_default_groups_of_blocks(lib):
+    """Levels with enough trailing tiles take groups of four column blocks by
+    default, on every supernode of the level, ragged last blocks included:
+    the factor is the oracle's and that of one block a group."""
+    matrix = arrow(700, 8, blocks=64)
+    for tuning in ({}, {"delay": 1}, {"lookahead": -1}, {"handover": -1}):
+        err, eta, S = factor_and_solve(lib, matrix, tuning, nrhs=1)
+        print(f"{tuning}: worst supernode {err:.2e}, eta {eta:.2e}", flush=True)
+        assert S.nsuper == 65 and err <= 1e-10 and eta <= BAR["fp64"]
