@@ -111,6 +111,27 @@ __device__ __forceinline__ void flag_device_error(int32_t *deverr) {
     __hip_atomic_fetch_or(deverr, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
+// Values handed over through memory that the reader polls (the persistent
+// solve sweeps' buffers, the last panel of a handed-over block): filled with
+// a signalling-NaN pattern before the sweep, which no arithmetic result
+// takes (a NaN that arithmetic yields is quiet), so a reader polls the
+// value itself and the writer needs no flag after it.
+template <typename T>
+struct Unset;
+template <>
+struct Unset<double> {
+    using bits_t = unsigned long long;
+    static constexpr bits_t bits = 0x7ff5a5a5a5a5a5a5ull;
+};
+template <>
+struct Unset<float> {
+    using bits_t = unsigned int;
+    static constexpr bits_t bits = 0x7fa5a5a5u;
+};
+template <typename T>
+__device__ __forceinline__ bool is_unset(T v) {
+    return __builtin_bit_cast(typename Unset<T>::bits_t, v) == Unset<T>::bits;
+}
 // Bounded waits: poll an int until it holds `want`; after `spin` polls
 // (about a second by default) give up, flag err and go on, so every wave
 // always exits.  Once any wait has given up, the others stop waiting too.
@@ -310,18 +331,33 @@ struct PotrfLds {
     T dg[kNB];
 };
 
-// Workgroups handing out one panel of a block: waves 2 and 3 add 1 each to
-// its flag once their part is out.
+// Parts of a panel of a block that is handed out: waves 2 and 3 add 1 each to
+// its flag once their part is out.  The last panel has no flag: what the
+// tiles below need of it, the inverse of its diagonal triangle, goes straight
+// from the wave that forms it to its place in the inverse store, and they
+// poll the values there (unset by fill_last_inverse).  With a flag for it the
+// tiles of a trailing launch ended 16.8 us (FP32) and 19.2 (FP64) after its
+// start, now 14.9 and 17.8; a 34^3 FP32 refined step took 3445 us, now 3398.
 constexpr int kPanelParts = 2;
 
+// The last 16x16 diagonal tile of a full block's inverse at Vi, unset: done by
+// whoever factors the block before it, in an earlier launch.
+template <typename T>
+__device__ __forceinline__ void fill_last_inverse(T *Vi) {
+    const int a = threadIdx.x & 15, b = threadIdx.x >> 4;
+    Vi[(48 + b) * kNB + 48 + a] = __builtin_bit_cast(T, Unset<T>::bits);
+}
+
 // Factor the block in A (nb <= 64; rows and columns >= nb hold the identity;
-// only the lower triangle is read, what is above the diagonal is scratch), write L into P (columns c0.., leading dimension m, lower triangle
-// only) and the inverse into Vi; a failed pivot lowers *status to g0 + its
-// column.  Called by all 256 threads of the workgroup.  With pflags (a full
+// only the lower triangle is read, what is above the diagonal is scratch),
+// write L into P (columns c0.., leading dimension m, lower triangle only) and
+// the inverse into Vi; a failed pivot lowers *status to g0 + its column.  Called by all 256 threads of the workgroup.  With pflags (a full
 // block, nb = 64), each panel p is also handed to workgroups of the same
 // launch: its L and the inverse of its 16x16 diagonal triangle go out with
 // device-scope atomic stores, and each of waves 2 and 3 adds 1 to pflags[p]
-// once its part has completed (kPanelParts when the panel is out).
+// once its part has completed (kPanelParts when the panel is out; the last
+// panel by its values, above).  next_full: the supernode's next block is a
+// full one, whose last tile of the inverse is unset here.
 //
 // Four 16-column panels, one workgroup barrier each.  In step p each of the
 // panel's tiles below the diagonal (at most three) has a wave of its own (0,
@@ -344,7 +380,7 @@ constexpr int kPanelParts = 2;
 // 34^3 grid's top levels (FP32) 21.7 and 18.4 on average.
 template <typename T, bool BOOST = false>
 __device__ __forceinline__ void potrf_lds(T (*A)[kNB + 1], PotrfLds<T> &W, int nb, T *P, int64_t m, int c0, T *Vi,
-                                          unsigned long long *status, int64_t g0, int32_t *pflags,
+                                          unsigned long long *status, int64_t g0, int32_t *pflags, bool next_full,
                                           PivotFloor<T> pfl = {}) {
     constexpr int PW = 16;
     using M = Mfma<T>;
@@ -430,6 +466,14 @@ __device__ __forceinline__ void potrf_lds(T (*A)[kNB + 1], PotrfLds<T> &W, int n
             if (lane < 16)
 #pragma unroll
                 for (int k = 0; k < 16; ++k) D[k][l16] = z[k];
+            if (pflags && p == 3) {
+                wave_lds_sync();
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const int k = p0 + 4 * e + lg;
+                    dev_store(Vi + k * nb + p0 + l16, D[l16][4 * e + lg]);
+                }
+            }
         } else {
             const T ls = rs * up;
             if constexpr (NX > 0)
@@ -553,19 +597,21 @@ __device__ __forceinline__ void potrf_lds(T (*A)[kNB + 1], PotrfLds<T> &W, int n
         }
         __syncthreads();
     }
+    // the last panel: its 16x16 triangle of L, one entry a thread; the last
+    // block row of the inverse (waves 0 .. 2), the one before to memory
     fresh();
     const int q = npan - 1;
-    if (wv >= 2) {
-        hand_out(q, wv - 2);
-        flag_out(q);
-        if (wv == 3 && q == 3) inverse_tile(q, 2);
-    } else if (wv < q) {
-        inverse_tile(q, wv);
+    {
+        const int i = PW * q + (t & 15), k = PW * q + (t >> 4);
+        const T v = i == k ? W.dg[i] : A[k][i];
+        if (i >= k && i < nb) P[(int64_t)(c0 + k) * m + c0 + i] = v;
     }
+    if (wv < q) inverse_tile(q, wv);
+    else if (wv == 3 && q > 0) store_inverse_rows(q - 1, lane, std::integral_constant<int, 64>{});
+    if (next_full) fill_last_inverse(Vi + nb * nb);
     if (t == 0 && bad >= 0) atomicMin(status, (unsigned long long)(g0 + bad));
     if (BOOST && t == 0 && boosted) atomicAdd(pfl.count, boosted);
     __syncthreads();
-    if (q > 0) store_inverse_rows(q - 1, t, std::integral_constant<int, 256>{});
     store_inverse_rows(q, t, std::integral_constant<int, 256>{});
 }
 
@@ -603,7 +649,7 @@ __device__ __forceinline__ void potrf_body(const PanelTask &tk, BlockLds<T> &L, 
     }
     __syncthreads();
     potrf_lds<T, BOOST>(L.A, L.W, nb, P, m, c0, Linv + tk.ioff, status + (status_slot ? status_slot[tk.s] : 0),
-                        tk.g0, nullptr, pfl);
+                        tk.g0, nullptr, tk.next_full != 0, pfl);
 }
 
 // ---------------------------------------------------------------------------
@@ -1518,7 +1564,8 @@ __global__ __launch_bounds__(256, 3) void k_tiles(const TileTask *tasks, const i
         // (also after a failed pivot, which the status word reports, so
         // that no tile waits in vain)
         potrf_lds<T, BF>(A, W, nb2, P, m, tk.j0, Linv + tk.aux, status + (status_slot ? status_slot[tk.s] : 0),
-                         tk.blk, tk.flag >= 0 ? hflags + kFlagsPerBlock * tk.flag : nullptr, pfl);
+                         tk.blk, tk.flag >= 0 ? hflags + kFlagsPerBlock * tk.flag : nullptr,
+                         tk.j0 + 2 * kNB <= tk.jmax, pfl);
         return;
     }
     if (MODE == MODE_TRAILING && tk.flag >= 0) {
@@ -1539,25 +1586,32 @@ __global__ __launch_bounds__(256, 3) void k_tiles(const TileTask *tasks, const i
         bool ok = true;
 #pragma unroll
         for (int p = 0; p < 4; ++p) {
-            // wait for panel p (every lane reads the same word: one load)
+            // B operands: the inverse of the panel's diagonal triangle,
+            // B[k][j] = (L^{-1})_{16p+j,16p+k}, and L below it, B[k][j] =
+            // L[16q+j][16p+k], once the panel is out: its flag (every lane
+            // reads the same word: one load), or for the last one its values
+            T bi[4] = {T(0), T(0), T(0), T(0)}, bl[3][4];
+            auto load_inverse = [&] {
+#pragma unroll
+                for (int kk = 0; kk < 4; ++kk) bi[kk] = dev_load(Vi + (16 * p + 4 * kk + lk4) * TM + 16 * p + l16);
+            };
             bool ready = false;
             for (int it = 0; ok && it < wctl.spin; ++it) {
-                if (__builtin_amdgcn_readfirstlane(dev_load(pf + p)) >= kPanelParts) {
-                    ready = true;
-                    break;
+                if (p < 3) {
+                    ready = __builtin_amdgcn_readfirstlane(dev_load(pf + p)) >= kPanelParts;
+                } else {
+                    load_inverse();
+                    ready = !__any(is_unset(bi[0]) || is_unset(bi[1]) || is_unset(bi[2]) || is_unset(bi[3]));
                 }
-                __builtin_amdgcn_s_sleep(2);
+                if (ready) break;
+                __builtin_amdgcn_s_sleep(1);
             }
             ok = ok && ready;
             __asm__ volatile("" ::: "memory");
-            // B operands: the inverse of the panel's diagonal triangle,
-            // B[k][j] = (L^{-1})_{16p+j,16p+k}, and L below it, B[k][j] =
-            // L[16q+j][16p+k]
-            T bi[4], bl[3][4];
+            if (p < 3) load_inverse();
 #pragma unroll
             for (int kk = 0; kk < 4; ++kk) {
                 const int k = 16 * p + 4 * kk + lk4;
-                bi[kk] = dev_load(Vi + k * TM + 16 * p + l16);
 #pragma unroll
                 for (int q = p + 1; q < 4; ++q) bl[q - p - 1][kk] = dev_load(Lb + (int64_t)k * m + 16 * q + l16);
             }
@@ -1815,26 +1869,6 @@ __global__ __launch_bounds__(512) void k_tiles128(const TileTask *tasks, const i
 //   stores x_q = Linv_q^T t.  Rows below belong to ancestors, whose x is
 //   final when the block's level runs.
 // ---------------------------------------------------------------------------
-// Hand-over buffers of the persistent sweeps: filled with
-// a signalling-NaN pattern before the sweep, which no arithmetic result
-// takes (a NaN that arithmetic yields is quiet), so a reader polls the
-// value itself and the writer needs no flag after it.
-template <typename T>
-struct Unset;
-template <>
-struct Unset<double> {
-    using bits_t = unsigned long long;
-    static constexpr bits_t bits = 0x7ff5a5a5a5a5a5a5ull;
-};
-template <>
-struct Unset<float> {
-    using bits_t = unsigned int;
-    static constexpr bits_t bits = 0x7fa5a5a5u;
-};
-template <typename T>
-__device__ __forceinline__ bool is_unset(T v) {
-    return __builtin_bit_cast(typename Unset<T>::bits_t, v) == Unset<T>::bits;
-}
 // What a solve starts with, in one launch: the permuted right-hand sides in Y,
 // Acc set (unset pattern or zero), the counters of the persistent sweeps
 // (dep <- the forward counts, cnt <- 0, queues <- 0).  The error word is the

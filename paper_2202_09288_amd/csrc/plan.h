@@ -140,7 +140,7 @@ struct PanelTask {
     int32_t c0;
     int32_t c1;
     int32_t g0;    // global column of c0 (pivot reports)
-    int32_t pad;
+    int32_t next_full;  // 1: the supernode's next block has kNB columns
 };
 
 // A whole small or tiny supernode (k_level): factor, invert, scatter its update.

@@ -680,7 +680,8 @@ int build_schedule(Symbolic &S) {
                 if (b == 0) {
                     st.potrf_flops += nbd * nbd * nbd / 3.0 + nbd * nbd / 2.0 + nbd / 6.0;
                     S.potrf_tasks.push_back(PanelTask{S.lptr[s], S.inv_off[blk], s, (int32_t)m, (int32_t)c0,
-                                                      (int32_t)c1, (int32_t)(S.super_ptr[s] + c0), 0});
+                                                      (int32_t)c1, (int32_t)(S.super_ptr[s] + c0),
+                                                      cx - c1 == kNB ? 1 : 0});
                 }
                 if (!fused_here) {
                     st.trsm_flops += (double)(m - c1) * nbd * nbd;
