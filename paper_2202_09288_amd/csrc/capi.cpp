@@ -667,37 +667,30 @@ int refine_chunk(const RefineTarget &T, const double *B, double *X, int q, int64
     const int ns = T.nseg;
     constexpr int C = kRefineChunk;
     const int64_t K = (int64_t)C * ns;  // (column, system) slots
-    // workspace: 7 vectors of n x C (leading dimension n), then scalars
+    // workspace: 6 vectors of n x C (leading dimension n), then scalars
     const size_t vec = ((size_t)n * C * sizeof(double) + 255) & ~size_t(255);
-    const size_t scal = (size_t)(9 * K + ns) * sizeof(double);
-    int rc = ensure_bytes((void **)&T.f->refine, &T.f->refine_bytes, 7 * vec + scal);
+    const size_t scal = (size_t)(8 * K + ns) * sizeof(double);
+    int rc = ensure_bytes((void **)&T.f->refine, &T.f->refine_bytes, 6 * vec + scal);
     if (rc) return rc;
     char *base = (char *)T.f->refine;
-    double *Bw = (double *)base, *Xw = (double *)(base + vec), *Tv = (double *)(base + 2 * vec),
-           *Rv = (double *)(base + 3 * vec), *Zv = (double *)(base + 4 * vec), *Pv = (double *)(base + 5 * vec),
-           *Qv = (double *)(base + 6 * vec);
-    unsigned long long *umax = (unsigned long long *)(base + 7 * vec);  // r[K], x[K], b[K], |A|[ns]
+    double *Bw = (double *)base, *Xw = (double *)(base + vec), *Rv = (double *)(base + 2 * vec),
+           *Zv = (double *)(base + 3 * vec), *Pv = (double *)(base + 4 * vec), *Qv = (double *)(base + 5 * vec);
+    unsigned long long *umax = (unsigned long long *)(base + 6 * vec);  // r[K], x[K], b[K], |A|[ns]
     double *dots = (double *)(umax + 3 * K + ns);                          // [K]
-    double *coef = dots + K;                                               // alpha[K], -alpha[K], beta[K]
-    double *rho = coef + 3 * K;                                            // [K] r.z of the current step
+    double *coef = dots + K;                                               // alpha[K], beta[K]
+    double *rho = coef + 2 * K;                                            // [K] r.z of the current step
     double *frz = rho + K;                                                 // [K] 1 for a converged slot
-    auto colmax = [&](const double *V, unsigned long long *out) {
-        if (T.seg) spc::launch_seg_colmax(V, T.seg, n, q, n, ns, out, st);
-        else spc::launch_colmax(V, n, q, n, out, st);
-    };
     auto axpby = [&](const double *a, double a0, const double *Xv, const double *bb, double b0, double *Y) {
         if (T.seg) spc::launch_seg_axpby(a, a0, Xv, bb, b0, Y, T.seg, n, q, n, ns, st);
         else spc::launch_axpby(a, a0, Xv, bb, b0, Y, n, q, n, st);
     };
 
-    spc::launch_copy_cols(B, ld, Bw, n, n, q, st);
-    spc::launch_copy_cols(Bw, n, Xw, n, n, q, st);
+    spc::launch_zero<unsigned long long>(umax, 4 * K + ns, st);  // the maxima and dots
+    spc::launch_refine_start(B, ld, Bw, Xw, T.seg, n, q, ns, umax + 2 * K, st);
     rc = spc_solve(T.f, Xw, q, n, st);
     if (rc) return rc;
-    spc::launch_zero<unsigned long long>(umax, 3 * K + ns, st);
     if (T.seg) spc::launch_seg_norm_inf_A(T.rp, T.vm, T.values, T.seg, n, umax + 3 * K, st);
     else spc::launch_norm_inf_A(T.rp, T.vm, T.values, n, T.nnz, umax + 3 * K, st);
-    colmax(Bw, umax + 2 * K);
 
     // the per-step copies go through pinned host memory (no staging)
     const size_t host_need = (3 * K + ns) * sizeof(unsigned long long) + K * sizeof(double);
@@ -716,28 +709,26 @@ int refine_chunk(const RefineTarget &T, const double *B, double *X, int q, int64
     std::atomic<bool> &start_cg = owner_of(T.f)->refine_cg;  // per factorization (a batch's for a view)
     bool cg = start_cg, cg_started = false;
     int it = 0;
-    // dot products per slot into dots, left on the device: the CG
-    // coefficients are formed there too, so a step synchronizes only for
-    // its backward errors
-    auto dot = [&](const double *U, const double *V) {
-        spc::launch_zero<double>(dots, K, st);
-        if (T.seg) spc::launch_seg_coldot(U, V, T.seg, n, q, n, ns, dots, st);
-        else spc::launch_coldot(U, V, n, q, n, dots, st);
-    };
+    // dot products per slot into dots (clear between them), left on the
+    // device: the CG coefficients are formed there too, so a step
+    // synchronizes only for its backward errors
+    auto dot = [&](const double *U, const double *V) { spc::launch_coldot(U, V, T.seg, n, q, n, ns, dots, st); };
     std::vector<double> e_slot(K, 0.0);
     for (;;) {
         // Once CG runs, its recursive residual r tracks b - A x to rounding,
         // so a step's backward error is first estimated from r; the true
         // residual (one more SpMV) is taken before any column counts as
         // converged and at the step limit, so every reported backward error
-        // is the true one.  After a true residual, r is replaced by it.
+        // is the true one, and r is replaced by it.  The estimate's maxima
+        // come with the step that updates r and x; z holds r, for the next
+        // preconditioner solve.
         bool est = cg_started;
         double eta = 0.0;
         for (;;) {
-            if (!est) spc::launch_spmv(T.rp, T.ci, T.vm, T.values, Xw, Bw, Tv, n, T.nnz, q, n, st);  // T = b - A x
-            spc::launch_zero<unsigned long long>(umax, 2 * K, st);
-            colmax(est ? Rv : Tv, umax);
-            colmax(Xw, umax + K);
+            if (!est) {  // r = z = b - A x
+                spc::launch_spmv(T.rp, T.ci, T.vm, T.values, Xw, Bw, Rv, Zv, n, T.nnz, q, n, umax, 2 * K, st);
+                spc::launch_colmax(Rv, Xw, T.seg, n, q, n, ns, umax, K, st);
+            }
             HIP_TRY(hipMemcpyAsync(hb, umax, (3 * K + ns) * sizeof(unsigned long long), hipMemcpyDeviceToHost, st));
             HIP_TRY(hipStreamSynchronize(st));
             if ((rc = check_deverr(T.f))) return rc;
@@ -768,7 +759,6 @@ int refine_chunk(const RefineTarget &T, const double *B, double *X, int q, int64
             }
             break;
         }
-        if (cg_started && !est) spc::launch_copy_cols(Tv, n, Rv, n, n, q, st);  // residual replacement
         for (int64_t j = 0; j < (int64_t)q * ns; ++j) frozen[j] = e_slot[j] <= tol ? 1.0 : 0.0;
         for (int sg = 0; sg < ns; ++sg) {
             res[sg].berr = eta_s[sg];
@@ -787,7 +777,6 @@ int refine_chunk(const RefineTarget &T, const double *B, double *X, int q, int64
         if (!cg && h >= 2 && !(eta_hist[h - 1] <= 0.1 * eta_hist[h - 2])) cg = start_cg = true;
         ++it;
         if (!cg) {
-            spc::launch_copy_cols(Tv, n, Zv, n, n, q, st);
             rc = spc_solve(T.f, Zv, q, n, st);  // d = M^{-1} r
             if (rc) return rc;
             axpby(nullptr, 1.0, Zv, nullptr, 1.0, Xw);  // x += d
@@ -796,32 +785,23 @@ int refine_chunk(const RefineTarget &T, const double *B, double *X, int q, int64
         // frozen is next written after the next step's synchronization,
         // so this copy from it has finished by then
         HIP_TRY(hipMemcpyAsync(frz, frozen, K * sizeof(double), hipMemcpyHostToDevice, st));
-        if (!cg_started) {
-            // r = b - A x, z = M^{-1} r, p = z, rho = r.z
-            spc::launch_copy_cols(Tv, n, Rv, n, n, q, st);
-            spc::launch_copy_cols(Rv, n, Zv, n, n, q, st);
-            rc = spc_solve(T.f, Zv, q, n, st);
-            if (rc) return rc;
+        // (the preconditioner solve of a step's residual comes after that
+        // step's convergence check, so the step that converges makes none)
+        rc = spc_solve(T.f, Zv, q, n, st);  // z = M^{-1} r
+        if (rc) return rc;
+        dot(Rv, Zv);
+        if (!cg_started) {  // p = z, rho = r.z
             spc::launch_copy_cols(Zv, n, Pv, n, n, q, st);
-            dot(Rv, Zv);
-            HIP_TRY(hipMemcpyAsync(rho, dots, K * sizeof(double), hipMemcpyDeviceToDevice, st));
+            spc::launch_cg_coef(dots, rho, frz, coef, umax, K, spc::CG_START, st);
             cg_started = true;
-        } else {
-            // the preconditioner solve of the last step's residual comes
-            // after that step's convergence check, so the step that
-            // converges makes none
-            spc::launch_copy_cols(Rv, n, Zv, n, n, q, st);
-            rc = spc_solve(T.f, Zv, q, n, st);  // z = M^{-1} r
-            if (rc) return rc;
-            dot(Rv, Zv);
-            spc::launch_cg_coef(dots, rho, frz, coef, K, false, st);  // beta = r.z / rho, rho = r.z
-            axpby(nullptr, 1.0, Zv, coef + 2 * K, 0.0, Pv);  // p = z + beta p
+        } else {  // beta = r.z / rho, rho = r.z, p = z + beta p
+            spc::launch_cg_coef(dots, rho, frz, coef, umax, K, spc::CG_BETA, st);
+            axpby(nullptr, 1.0, Zv, coef + K, 0.0, Pv);
         }
-        spc::launch_spmv(T.rp, T.ci, T.vm, T.values, Pv, nullptr, Qv, n, T.nnz, q, n, st);  // q = A p
+        spc::launch_spmv(T.rp, T.ci, T.vm, T.values, Pv, nullptr, Qv, nullptr, n, T.nnz, q, n, nullptr, 0, st);  // q = A p
         dot(Pv, Qv);
-        spc::launch_cg_coef(dots, rho, frz, coef, K, true, st);  // alpha = rho / p.q
-        axpby(coef, 0.0, Pv, nullptr, 1.0, Xw);      // x += alpha p
-        axpby(coef + K, 0.0, Qv, nullptr, 1.0, Rv);  // r -= alpha q
+        spc::launch_cg_coef(dots, rho, frz, coef, umax, K, spc::CG_ALPHA, st);  // alpha = rho / p.q
+        spc::launch_cg_update(coef, Pv, Qv, Xw, Rv, Zv, T.seg, n, q, ns, umax, K, st);
     }
     spc::launch_copy_cols(Xw, n, X, ld, n, q, st);
     HIP_TRY(hipGetLastError());

@@ -168,16 +168,29 @@ void launch_solve_bwd(const DevPlan &P, int64_t t0, int64_t t1, const T *Lx, con
 
 // refinement (FP64)
 void launch_spmv(const int64_t *rowptr, const int32_t *colidx, const int64_t *valmap, const double *values,
-                 const double *X, const double *B, double *Y, int64_t n, int64_t nnz, int nrhs, int64_t ld,
-                 hipStream_t st);
+                 const double *X, const double *B, double *Y, double *Y2, int64_t n, int64_t nnz, int nrhs,
+                 int64_t ld, unsigned long long *zero, int64_t nzero, hipStream_t st);
 void launch_norm_inf_A(const int64_t *rowptr, const int64_t *valmap, const double *values, int64_t n, int64_t nnz,
                        unsigned long long *out, hipStream_t st);
-void launch_colmax(const double *V, int64_t n, int nrhs, int64_t ld, unsigned long long *out, hipStream_t st);
-void launch_coldot(const double *U, const double *V, int64_t n, int nrhs, int64_t ld, double *out, hipStream_t st);
-// The conjugate-gradient coefficients of K slots on the device (alpha, or
-// beta with the update of rho); frozen[j] != 0 marks a converged slot.
-void launch_cg_coef(const double *dots, double *rho, const double *frozen, double *coef, int64_t K, bool alpha,
-                    hipStream_t st);
+// Reductions and updates per slot (column q, system): q * nseg + seg[i] for
+// row i, with seg null for one system (nseg = 1).  Maxima of V0 to out, of V1
+// to out + K (bit patterns).
+void launch_colmax(const double *V0, const double *V1, const int32_t *seg, int64_t n, int nrhs, int64_t ld, int nseg,
+                   unsigned long long *out, int64_t K, hipStream_t st);
+void launch_coldot(const double *U, const double *V, const int32_t *seg, int64_t n, int nrhs, int64_t ld, int nseg,
+                   double *out, hipStream_t st);
+// b into Bw and Xw, max |b| to out
+void launch_refine_start(const double *B, int64_t ldb, double *Bw, double *Xw, const int32_t *seg, int64_t n,
+                         int nrhs, int nseg, unsigned long long *out, hipStream_t st);
+// x += alpha p, r -= alpha q, z = r; max |r| to out, max |x| to out + K
+void launch_cg_update(const double *alpha, const double *Pv, const double *Qv, double *X, double *R, double *Z,
+                      const int32_t *seg, int64_t n, int nrhs, int nseg, unsigned long long *out, int64_t K,
+                      hipStream_t st);
+// The conjugate-gradient coefficients of K slots on the device; frozen[j] !=
+// 0 marks a converged slot.  Clears dots, CG_ALPHA also umax[0 .. 2K).
+enum CgCoef { CG_START, CG_BETA, CG_ALPHA };
+void launch_cg_coef(double *dots, double *rho, const double *frozen, double *coef, unsigned long long *umax, int64_t K,
+                    CgCoef mode, hipStream_t st);
 void launch_axpby(const double *a, double a0, const double *X, const double *b, double b0, double *Y, int64_t n,
                   int nrhs, int64_t ld, hipStream_t st);
 void launch_copy_cols(const double *X, int64_t ldx, double *Y, int64_t ldy, int64_t n, int nrhs, hipStream_t st);
@@ -186,10 +199,6 @@ void launch_copy_cols(const double *X, int64_t ldx, double *Y, int64_t ldy, int6
 // system
 void launch_seg_norm_inf_A(const int64_t *rowptr, const int64_t *valmap, const double *values, const int32_t *seg,
                            int64_t n, unsigned long long *out, hipStream_t st);
-void launch_seg_colmax(const double *V, const int32_t *seg, int64_t n, int nrhs, int64_t ld, int nseg,
-                       unsigned long long *out, hipStream_t st);
-void launch_seg_coldot(const double *U, const double *V, const int32_t *seg, int64_t n, int nrhs, int64_t ld,
-                       int nseg, double *out, hipStream_t st);
 void launch_seg_axpby(const double *a, double a0, const double *X, const double *b, double b0, double *Y,
                       const int32_t *seg, int64_t n, int nrhs, int64_t ld, int nseg, hipStream_t st);
 void launch_batch_move(double *const *ptrs, const int64_t *lds, const int64_t *offs, double *M, int64_t n,

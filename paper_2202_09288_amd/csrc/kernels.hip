@@ -2842,36 +2842,83 @@ __device__ __forceinline__ double abs_key(double v) { return v != v ? __longlong
 // values (valmap), so refinement always uses the values given.  Vectors are
 // n x nrhs column-major with leading dimension ld.
 // ---------------------------------------------------------------------------
-// Y = B - A X (beta = -1, with B) or Y = A X (B == nullptr).  LPR
-// consecutive lanes share a row (LPR a power of two <= 64, so a group never
-// straddles a wave): lane j of the group takes entries j, j + LPR, ... of
-// the row, so a group's index and value loads are contiguous, and the
-// group's partial sums meet by shuffles.
-template <int LPR>
+// Sums of Q values over the LPR lanes j of a group: while there is more than
+// one value a lane gives half of them to lane j ^ OFF and adds what it gets
+// of the other half, so Q - 1 exchanges do for the first steps instead of
+// Q each.  Leaves Q / min(Q, LPR) values a lane (fold_first: the first's q).
+template <int Q, int OFF, int LPR, int N>
+__device__ __forceinline__ void fold_lanes(double (&acc)[N], int j) {
+    if constexpr (OFF < LPR) {
+        if constexpr (Q > 1) {
+            const bool up = (j & OFF) != 0;
+#pragma unroll
+            for (int k = 0; k < Q / 2; ++k) {
+                const double keep = up ? acc[k + Q / 2] : acc[k], give = up ? acc[k] : acc[k + Q / 2];
+                acc[k] = keep + __shfl_xor(give, OFF);
+            }
+            fold_lanes<Q / 2, 2 * OFF, LPR>(acc, j);
+        } else {
+            acc[0] += __shfl_xor(acc[0], OFF);
+            fold_lanes<1, 2 * OFF, LPR>(acc, j);
+        }
+    }
+}
+template <int Q, int OFF, int LPR>
+__device__ __forceinline__ int fold_first(int j) {
+    if constexpr (OFF < LPR && Q > 1) return ((j & OFF) ? Q / 2 : 0) + fold_first<Q / 2, 2 * OFF, LPR>(j);
+    else return 0;
+}
+
+// Y = B - A X (with B) or Y = A X (B == nullptr), also to Y2 if that is
+// given; zero[0 .. nzero) is cleared (the maxima that the next launch takes).
+// LPR consecutive lanes share a row (LPR a power of two <= 64, so a group
+// never straddles a wave): lane j of the group takes entries j, j + LPR, ...
+// of the row, so a group's index and value loads are contiguous.  Q >= nrhs
+// values a lane, the columns past nrhs those of the last one again: a test
+// on each column made every one of an entry's gathers wait for the one
+// before.  Bound by the gathers' latency at these sizes (125000 rows of 7
+// entries, 8 columns: 50 MB); with the tests and a shuffle per column and
+// step 31 us, now SPMV8; 32 systems of 4096 rows, 16 columns: 137, now SPMV16.
+template <int LPR, int Q>
 __global__ __launch_bounds__(256) void k_spmv(const int64_t *rowptr, const int32_t *colidx, const int64_t *valmap,
                                               const double *values, const double *X, const double *B, double *Y,
-                                              int64_t n, int nrhs, int64_t ld) {
-    const int64_t i = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / LPR;
+                                              double *Y2, int64_t n, int nrhs, int64_t ld, unsigned long long *zero,
+                                              int64_t nzero) {
+    const int64_t id = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    for (int64_t k = id; k < nzero; k += (int64_t)gridDim.x * blockDim.x) zero[k] = 0;
+    const int64_t i = id / LPR;
+    const int64_t ic = i < n ? i : n - 1;
     const int j = threadIdx.x % LPR;
-    double acc[kMaxRhs];
+    constexpr int F = Q > LPR ? Q / LPR : 1, S = Q > LPR ? LPR : Q;  // values a lane holds at the end, lanes that store
+    const int qf = fold_first<Q, 1, LPR>(j);
+    const int64_t e1 = rowptr[ic + 1];
+    int64_t e = rowptr[ic] + j;
+    double b[F];
 #pragma unroll
-    for (int q = 0; q < kMaxRhs; ++q) acc[q] = 0.0;
-    if (i < n)
-        for (int64_t e = rowptr[i] + j; e < rowptr[i + 1]; e += LPR) {
-            const double a = values[valmap[e]];
-            const int64_t c = colidx[e];
+    for (int k = 0; k < F; ++k) b[k] = B ? B[ic + (int64_t)min(qf + k, nrhs - 1) * ld] : 0.0;
+    double acc[Q];
 #pragma unroll
-            for (int q = 0; q < kMaxRhs; ++q)
-                if (q < nrhs) acc[q] += a * X[c + q * ld];
-        }
-    // every lane takes part in the shuffles (nrhs is the same for all)
+    for (int q = 0; q < Q; ++q) acc[q] = 0.0;
+    for (; e < e1; e += LPR) {
+        const double a = values[valmap[e]];
+        const double *x = X + colidx[e];
+        double v[Q];
 #pragma unroll
-    for (int q = 0; q < kMaxRhs; ++q)
-        if (q < nrhs)
+        for (int q = 0; q < Q; ++q) v[q] = x[(int64_t)min(q, nrhs - 1) * ld];
 #pragma unroll
-            for (int off = LPR / 2; off > 0; off >>= 1) acc[q] += __shfl_xor(acc[q], off);
-    if (i < n && j == 0)
-        for (int q = 0; q < nrhs; ++q) Y[i + q * ld] = B ? B[i + q * ld] - acc[q] : acc[q];
+        for (int q = 0; q < Q; ++q) acc[q] += a * v[q];
+    }
+    // every lane takes part in the shuffles
+    fold_lanes<Q, 1, LPR>(acc, j);
+    if (i < n && j < S)
+#pragma unroll
+        for (int k = 0; k < F; ++k)
+            if (qf + k < nrhs) {
+                const int64_t o = i + (int64_t)(qf + k) * ld;
+                const double y = B ? b[k] - acc[k] : acc[k];
+                Y[o] = y;
+                if (Y2) Y2[o] = y;
+            }
 }
 
 // out = max_i sum_j |a_ij| (as the bit pattern of a non-negative double):
@@ -2903,37 +2950,6 @@ __global__ __launch_bounds__(256) void k_norm_inf_A(const int64_t *rowptr, const
         atomicMax(out, (unsigned long long)__double_as_longlong(fmax(fmax(wmax[0], wmax[1]), fmax(wmax[2], wmax[3]))));
 }
 
-// out[q] = max_i |V[i, q]| (bit patterns), grid.y = q, 256 threads: one
-// atomic per workgroup (same-address atomics serialize at L2)
-__global__ __launch_bounds__(256) void k_colmax(const double *V, int64_t n, int64_t ld, unsigned long long *out) {
-    __shared__ double wmax[4];
-    const int q = blockIdx.y;
-    double mx = 0.0;
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
-        mx = fmax(mx, abs_key(V[i + q * ld]));
-    for (int off = 32; off > 0; off >>= 1) mx = fmax(mx, __shfl_xor(mx, off));
-    if ((threadIdx.x & 63) == 0) wmax[threadIdx.x >> 6] = mx;
-    __syncthreads();
-    if (threadIdx.x == 0)
-        atomicMax(&out[q], (unsigned long long)__double_as_longlong(fmax(fmax(wmax[0], wmax[1]),
-                                                                           fmax(wmax[2], wmax[3]))));
-}
-
-// out[q] += sum_i U[i, q] V[i, q], grid.y = q, 256 threads: one atomic per
-// workgroup, as in k_colmax
-__global__ __launch_bounds__(256) void k_coldot(const double *U, const double *V, int64_t n, int64_t ld,
-                                                double *out) {
-    __shared__ double wsum[4];
-    const int q = blockIdx.y;
-    double acc = 0.0;
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
-        acc += U[i + q * ld] * V[i + q * ld];
-    for (int off = 32; off > 0; off >>= 1) acc += __shfl_xor(acc, off);
-    if ((threadIdx.x & 63) == 0) wsum[threadIdx.x >> 6] = acc;
-    __syncthreads();
-    if (threadIdx.x == 0) atomicAdd(&out[q], (wsum[0] + wsum[1]) + (wsum[2] + wsum[3]));
-}
-
 // Y[:, q] = a_q X[:, q] + b_q Y[:, q]; a_q = a[q] (device) or a0 when a is
 // null, likewise b_q; b_q = 0 does not read Y.
 __global__ void k_axpby(const double *a, double a0, const double *X, const double *b, double b0, double *Y,
@@ -2945,23 +2961,30 @@ __global__ void k_axpby(const double *a, double a0, const double *X, const doubl
 }
 
 // Conjugate-gradient coefficients per (column, system) slot j < K, formed
-// on the device so that a step needs no host round trip.  alpha: coef[j] =
-// rho[j] / dots[j] and coef[K + j] = -coef[j]; beta: coef[2K + j] =
-// dots[j] / rho[j], then rho[j] = dots[j].  A frozen slot (its column has
-// met the tolerance) and a quotient that is not finite give 0, and a frozen
-// slot keeps its rho.
-__global__ void k_cg_coef(const double *dots, double *rho, const double *frozen, double *coef, int64_t K, int alpha) {
+// on the device so that a step needs no host round trip, from the dot
+// products in dots, which are cleared for the next ones.  CG_START: rho[j] =
+// dots[j].  CG_BETA: coef[K + j] = dots[j] / rho[j], then rho[j] = dots[j].
+// CG_ALPHA: coef[j] = rho[j] / dots[j]; umax[0 .. 2K), the maxima that
+// k_cg_update takes, are cleared.  A frozen slot (its column has met the
+// tolerance) and a quotient that is not finite give 0, and a frozen slot
+// keeps its rho.
+__global__ void k_cg_coef(double *dots, double *rho, const double *frozen, double *coef, unsigned long long *umax,
+                          int64_t K, int mode) {
     const int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (j >= K) return;
     const bool fz = frozen[j] != 0.0;
-    if (alpha) {
-        const double a = (!fz && dots[j] > 0.0 && isfinite(rho[j] / dots[j])) ? rho[j] / dots[j] : 0.0;
-        coef[j] = a;
-        coef[K + j] = -a;
+    const double d = dots[j], r = rho[j];
+    dots[j] = 0.0;
+    if (mode == CG_START) {
+        rho[j] = d;
+    } else if (mode == CG_BETA) {
+        const double bt = (r != 0.0 && isfinite(d / r)) ? d / r : 0.0;
+        coef[K + j] = fz ? 0.0 : bt;
+        if (!fz) rho[j] = d;
     } else {
-        const double bt = (rho[j] != 0.0 && isfinite(dots[j] / rho[j])) ? dots[j] / rho[j] : 0.0;
-        coef[2 * K + j] = fz ? 0.0 : bt;
-        if (!fz) rho[j] = dots[j];
+        coef[j] = (!fz && d > 0.0 && isfinite(r / d)) ? r / d : 0.0;
+        umax[j] = 0;
+        umax[K + j] = 0;
     }
 }
 
@@ -3011,79 +3034,196 @@ __global__ void k_seg_norm_inf_A(const int64_t *rowptr, const int64_t *valmap, c
     }
 }
 
-// The segmented column reductions give each workgroup of 256 threads
-// kSegRows consecutive rows.  A system's rows are contiguous, so when the
-// first and last row of the chunk belong to one system the whole chunk does:
-// one atomic per workgroup.  A chunk that spans systems falls back to one
-// atomic per wave (or per row where a wave spans systems).
-constexpr int kSegRows = 256 * 8;
+// Column reductions, grid.y = q: a workgroup of 256 threads takes kRedRows
+// consecutive rows, kRedPer a thread, their loads ahead of the first use.
+// One system (SEG false): the chunks of a workgroup follow each other at the
+// grid's stride, one atomic per workgroup (atomics on one address serialize
+// at L2).  A batch: a system's rows are contiguous, so when the first and
+// last row of the chunk belong to one system the whole chunk does: one
+// atomic too; a chunk that spans systems makes one per wave (or per row
+// where a wave spans systems).
+constexpr int kRedPer = 4, kRedRows = 256 * kRedPer;
 
-__global__ __launch_bounds__(256) void k_seg_colmax(const double *V, const int32_t *seg, int64_t n, int64_t ld,
-                                                    int nseg, unsigned long long *out) {
-    __shared__ double wm[4];
-    const int q = blockIdx.y;
-    const int64_t base = (int64_t)blockIdx.x * kSegRows;
-    const int64_t last = (base + kSegRows < n ? base + kSegRows : n) - 1;
-    if (seg[base] == seg[last]) {  // the same for every thread of the workgroup
-        double mx = 0.0;
-        for (int r = 0; r < kSegRows / 256; ++r) {
-            const int64_t i = base + r * 256 + threadIdx.x;
-            if (i < n) mx = fmax(mx, abs_key(V[i + q * ld]));
-        }
-        for (int off = 32; off > 0; off >>= 1) mx = fmax(mx, __shfl_xor(mx, off));
-        if ((threadIdx.x & 63) == 0) wm[threadIdx.x >> 6] = mx;
-        __syncthreads();
-        if (threadIdx.x == 0)
-            atomicMax(out + (int64_t)q * nseg + seg[base],
-                      (unsigned long long)__double_as_longlong(fmax(fmax(wm[0], wm[1]), fmax(wm[2], wm[3]))));
-        return;
-    }
-    for (int r = 0; r < kSegRows / 256; ++r) {
-        const int64_t i = base + r * 256 + threadIdx.x;
-        const int64_t ic = i < n ? i : n - 1;
-        const int s = seg[ic];
-        double mx = i < n ? abs_key(V[ic + q * ld]) : 0.0;
-        unsigned long long *o = out + (int64_t)q * nseg + s;
+// MAX: the larger of two magnitudes (out holds their bit patterns), else the sum
+template <bool MAX>
+__device__ __forceinline__ double red_op(double a, double b) { return MAX ? fmax(a, b) : a + b; }
+template <bool MAX>
+__device__ __forceinline__ void red_out(double *out, double v) {
+    if constexpr (MAX) atomicMax((unsigned long long *)out, (unsigned long long)__double_as_longlong(v));
+    else atomicAdd(out, v);
+}
+template <bool MAX>
+__device__ __forceinline__ double red_wave(double v) {
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) v = red_op<MAX>(v, __shfl_xor(v, off));
+    return v;
+}
+template <bool MAX>
+__device__ __forceinline__ void red_workgroup(double v, double *out, double *w4) {
+    v = red_wave<MAX>(v);
+    if ((threadIdx.x & 63) == 0) w4[threadIdx.x >> 6] = v;
+    __syncthreads();
+    if (threadIdx.x == 0) red_out<MAX>(out, red_op<MAX>(red_op<MAX>(w4[0], w4[1]), red_op<MAX>(w4[2], w4[3])));
+}
+// the workgroup's chunk lies in one system (the same answer for every thread)
+__device__ __forceinline__ bool chunk_in_one_segment(const int32_t *seg, int64_t n) {
+    const int64_t base = (int64_t)blockIdx.x * kRedRows;
+    return seg[base] == seg[(base + kRedRows < n ? base + kRedRows : n) - 1];
+}
+// a chunk that spans systems; v: this thread's rows (0 past n), out: the column's slots
+template <bool MAX>
+__device__ __forceinline__ void red_mixed(const double (&v)[kRedPer], const int32_t *seg, int64_t n, double *out) {
+#pragma unroll
+    for (int r = 0; r < kRedPer; ++r) {
+        const int64_t i = (int64_t)blockIdx.x * kRedRows + r * 256 + threadIdx.x;
+        const int s = seg[i < n ? i : n - 1];
         if (wave_in_one_segment(s)) {
-            for (int off = 32; off > 0; off >>= 1) mx = fmax(mx, __shfl_xor(mx, off));
-            if ((threadIdx.x & 63) == 0) atomicMax(o, (unsigned long long)__double_as_longlong(mx));
+            const double w = red_wave<MAX>(v[r]);
+            if ((threadIdx.x & 63) == 0) red_out<MAX>(out + s, w);
         } else if (i < n) {
-            atomicMax(o, (unsigned long long)__double_as_longlong(mx));
+            red_out<MAX>(out + s, v[r]);
         }
     }
 }
 
-__global__ __launch_bounds__(256) void k_seg_coldot(const double *U, const double *V, const int32_t *seg, int64_t n,
-                                                    int64_t ld, int nseg, double *out) {
-    __shared__ double ws[4];
-    const int q = blockIdx.y;
-    const int64_t base = (int64_t)blockIdx.x * kSegRows;
-    const int64_t last = (base + kSegRows < n ? base + kSegRows : n) - 1;
-    if (seg[base] == seg[last]) {  // the same for every thread of the workgroup
-        double acc = 0.0;
-        for (int r = 0; r < kSegRows / 256; ++r) {
+// out[z K + q nseg + s] = max |V_z[i, q]| over system s (bit patterns; NaN as
+// +Inf), V0 for grid.z = 0 and V1 for 1
+template <bool SEG>
+__global__ __launch_bounds__(256) void k_colmax(const double *V0, const double *V1, const int32_t *seg, int64_t n,
+                                                int64_t ld, int nseg, double *out, int64_t K) {
+    __shared__ double w4[4];
+    const double *V = (blockIdx.z ? V1 : V0) + blockIdx.y * ld;
+    out += blockIdx.z * K + (int64_t)blockIdx.y * nseg;
+    double v[kRedPer], mx = 0.0;
+    for (int64_t base = (int64_t)blockIdx.x * kRedRows; base < n; base += (int64_t)gridDim.x * kRedRows) {
+        // (past n the last row again, which is the same chunk's)
+#pragma unroll
+        for (int r = 0; r < kRedPer; ++r) v[r] = V[min(base + r * 256 + threadIdx.x, n - 1)];
+#pragma unroll
+        for (int r = 0; r < kRedPer; ++r) v[r] = abs_key(v[r]);
+#pragma unroll
+        for (int r = 0; r < kRedPer; ++r) mx = fmax(mx, v[r]);
+    }
+    if constexpr (SEG) {
+        if (!chunk_in_one_segment(seg, n)) return red_mixed<true>(v, seg, n, out);
+        out += seg[(int64_t)blockIdx.x * kRedRows];
+    }
+    red_workgroup<true>(mx, out, w4);
+}
+
+// out[q nseg + s] += sum U[i, q] V[i, q] over system s
+template <bool SEG>
+__global__ __launch_bounds__(256) void k_coldot(const double *U, const double *V, const int32_t *seg, int64_t n,
+                                                int64_t ld, int nseg, double *out) {
+    __shared__ double w4[4];
+    U += blockIdx.y * ld;
+    V += blockIdx.y * ld;
+    out += (int64_t)blockIdx.y * nseg;
+    double v[kRedPer], acc = 0.0;
+    for (int64_t base = (int64_t)blockIdx.x * kRedRows; base < n; base += (int64_t)gridDim.x * kRedRows) {
+        double u[kRedPer];
+#pragma unroll
+        for (int r = 0; r < kRedPer; ++r) {
+            const int64_t i = min(base + r * 256 + threadIdx.x, n - 1);
+            u[r] = U[i];
+            v[r] = V[i];
+        }
+#pragma unroll
+        for (int r = 0; r < kRedPer; ++r) {
+            v[r] = base + r * 256 + threadIdx.x < n ? u[r] * v[r] : 0.0;
+            acc += v[r];
+        }
+    }
+    if constexpr (SEG) {
+        if (!chunk_in_one_segment(seg, n)) return red_mixed<false>(v, seg, n, out);
+        out += seg[(int64_t)blockIdx.x * kRedRows];
+    }
+    red_workgroup<false>(acc, out, w4);
+}
+
+// What a refined solve starts with: b into Bw and Xw (leading dimension n),
+// out[q nseg + s] = max |b|
+template <bool SEG>
+__global__ __launch_bounds__(256) void k_refine_start(const double *B, int64_t ldb, double *Bw, double *Xw,
+                                                      const int32_t *seg, int64_t n, int nseg, double *out) {
+    __shared__ double w4[4];
+    B += blockIdx.y * ldb;
+    Bw += blockIdx.y * n;
+    Xw += blockIdx.y * n;
+    out += (int64_t)blockIdx.y * nseg;
+    double v[kRedPer], mx = 0.0;
+    for (int64_t base = (int64_t)blockIdx.x * kRedRows; base < n; base += (int64_t)gridDim.x * kRedRows) {
+#pragma unroll
+        for (int r = 0; r < kRedPer; ++r) v[r] = B[min(base + r * 256 + threadIdx.x, n - 1)];
+#pragma unroll
+        for (int r = 0; r < kRedPer; ++r) {
             const int64_t i = base + r * 256 + threadIdx.x;
-            if (i < n) acc += U[i + q * ld] * V[i + q * ld];
-        }
-        for (int off = 32; off > 0; off >>= 1) acc += __shfl_xor(acc, off);
-        if ((threadIdx.x & 63) == 0) ws[threadIdx.x >> 6] = acc;
-        __syncthreads();
-        if (threadIdx.x == 0) atomicAdd(out + (int64_t)q * nseg + seg[base], (ws[0] + ws[1]) + (ws[2] + ws[3]));
-        return;
-    }
-    for (int r = 0; r < kSegRows / 256; ++r) {
-        const int64_t i = base + r * 256 + threadIdx.x;
-        const int64_t ic = i < n ? i : n - 1;
-        const int s = seg[ic];
-        double acc = i < n ? U[ic + q * ld] * V[ic + q * ld] : 0.0;
-        double *o = out + (int64_t)q * nseg + s;
-        if (wave_in_one_segment(s)) {
-            for (int off = 32; off > 0; off >>= 1) acc += __shfl_xor(acc, off);
-            if ((threadIdx.x & 63) == 0) atomicAdd(o, acc);
-        } else if (i < n) {
-            atomicAdd(o, acc);
+            if (i < n) {
+                Bw[i] = v[r];
+                Xw[i] = v[r];
+            }
+            v[r] = abs_key(v[r]);
+            mx = fmax(mx, v[r]);
         }
     }
+    if constexpr (SEG) {
+        if (!chunk_in_one_segment(seg, n)) return red_mixed<true>(v, seg, n, out);
+        out += seg[(int64_t)blockIdx.x * kRedRows];
+    }
+    red_workgroup<true>(mx, out, w4);
+}
+
+// The end of a conjugate-gradient step in one pass: x += alpha p, r -= alpha
+// q, z = r (what the next preconditioner solve starts from), and the maxima
+// of r and x per slot (out, out + K; cleared by k_cg_coef).  As launches of
+// their own these were two updates, a copy, a clear and two reductions: 31 us
+// and their gaps on 24000 rows x 4 columns, now CGUPD us.
+template <bool SEG>
+__global__ __launch_bounds__(256) void k_cg_update(const double *alpha, const double *Pv, const double *Qv, double *X,
+                                                   double *R, double *Z, const int32_t *seg, int64_t n, int nseg,
+                                                   double *out, int64_t K) {
+    __shared__ double w4[8];
+    const int64_t o = blockIdx.y * n, slot = (int64_t)blockIdx.y * nseg;
+    double xv[kRedPer], rv[kRedPer], xm = 0.0, rm = 0.0;
+    for (int64_t base = (int64_t)blockIdx.x * kRedRows; base < n; base += (int64_t)gridDim.x * kRedRows) {
+        double pv[kRedPer], qv[kRedPer], a[kRedPer];
+#pragma unroll
+        for (int r = 0; r < kRedPer; ++r) {
+            const int64_t i = min(base + r * 256 + threadIdx.x, n - 1);
+            a[r] = alpha[slot + (SEG ? seg[i] : 0)];
+            xv[r] = X[o + i];
+            rv[r] = R[o + i];
+            pv[r] = Pv[o + i];
+            qv[r] = Qv[o + i];
+        }
+#pragma unroll
+        for (int r = 0; r < kRedPer; ++r) {
+            const int64_t i = base + r * 256 + threadIdx.x;
+            xv[r] += a[r] * pv[r];
+            rv[r] -= a[r] * qv[r];
+            if (i < n) {
+                X[o + i] = xv[r];
+                R[o + i] = rv[r];
+                Z[o + i] = rv[r];
+            }
+            // (past n another thread's row, perhaps already updated)
+            xv[r] = i < n ? abs_key(xv[r]) : 0.0;
+            rv[r] = i < n ? abs_key(rv[r]) : 0.0;
+            xm = fmax(xm, xv[r]);
+            rm = fmax(rm, rv[r]);
+        }
+    }
+    out += slot;
+    if constexpr (SEG) {
+        if (!chunk_in_one_segment(seg, n)) {
+            red_mixed<true>(rv, seg, n, out);
+            red_mixed<true>(xv, seg, n, out + K);
+            return;
+        }
+        out += seg[(int64_t)blockIdx.x * kRedRows];
+    }
+    red_workgroup<true>(rm, out, w4);
+    red_workgroup<true>(xm, out + K, w4 + 4);
 }
 
 // Y[:, q] = a X[:, q] + b Y[:, q] with a = a[q * nseg + seg[i]] (or a0 when
@@ -3335,30 +3475,39 @@ void launch_solve_bwd(const DevPlan &P, int64_t t0, int64_t t1, const T *Lx, con
                            nrhs, sy);
 }
 
+template <int LPR>
+static void launch_spmv_lanes(const int64_t *rowptr, const int32_t *colidx, const int64_t *valmap,
+                              const double *values, const double *X, const double *B, double *Y, double *Y2,
+                              int64_t n, int nrhs, int64_t ld, unsigned long long *zero, int64_t nzero,
+                              hipStream_t st) {
+    const dim3 g(grid1(n * LPR, 256)), b(256);
+    const int64_t nz = zero ? nzero : 0;
+    auto go = [&](auto qc) {
+        hipLaunchKernelGGL((k_spmv<LPR, decltype(qc)::value>), g, b, 0, st, rowptr, colidx, valmap, values, X, B, Y,
+                           Y2, n, nrhs, ld, zero, nz);
+    };
+    if (nrhs <= 1) go(std::integral_constant<int, 1>{});
+    else if (nrhs <= 2) go(std::integral_constant<int, 2>{});
+    else if (nrhs <= 4) go(std::integral_constant<int, 4>{});
+    else if (nrhs <= 8) go(std::integral_constant<int, 8>{});
+    else go(std::integral_constant<int, kMaxRhs>{});
+}
 void launch_spmv(const int64_t *rowptr, const int32_t *colidx, const int64_t *valmap, const double *values,
-                 const double *X, const double *B, double *Y, int64_t n, int64_t nnz, int nrhs, int64_t ld,
-                 hipStream_t st) {
-    if (n <= 0) return;
+                 const double *X, const double *B, double *Y, double *Y2, int64_t n, int64_t nnz, int nrhs,
+                 int64_t ld, unsigned long long *zero, int64_t nzero, hipStream_t st) {
+    if (n <= 0 || nrhs <= 0) return;
     // lanes per row: the power of two (4..32) at or above the mean row length
     const int64_t avg = (nnz + n - 1) / n;
-    if (avg <= 4)
-        hipLaunchKernelGGL(k_spmv<4>, dim3(grid1(n * 4, 256)), dim3(256), 0, st, rowptr, colidx, valmap, values, X,
-                           B, Y, n, nrhs, ld);
-    else if (avg <= 8)
-        hipLaunchKernelGGL(k_spmv<8>, dim3(grid1(n * 8, 256)), dim3(256), 0, st, rowptr, colidx, valmap, values, X,
-                           B, Y, n, nrhs, ld);
-    else if (avg <= 16)
-        hipLaunchKernelGGL(k_spmv<16>, dim3(grid1(n * 16, 256)), dim3(256), 0, st, rowptr, colidx, valmap, values,
-                           X, B, Y, n, nrhs, ld);
-    else
-        hipLaunchKernelGGL(k_spmv<32>, dim3(grid1(n * 32, 256)), dim3(256), 0, st, rowptr, colidx, valmap, values,
-                           X, B, Y, n, nrhs, ld);
+    auto lanes = avg <= 4 ? launch_spmv_lanes<4>
+                 : avg <= 8 ? launch_spmv_lanes<8>
+                 : avg <= 16 ? launch_spmv_lanes<16> : launch_spmv_lanes<32>;
+    lanes(rowptr, colidx, valmap, values, X, B, Y, Y2, n, nrhs, ld, zero, nzero, st);
 }
 void launch_norm_inf_A(const int64_t *rowptr, const int64_t *valmap, const double *values, int64_t n, int64_t nnz,
                        unsigned long long *out, hipStream_t st) {
     if (n <= 0) return;
     const int64_t avg = (nnz + n - 1) / n;
-    const unsigned g4 = (unsigned)std::min<int64_t>(grid1(n * 4, 256), 1024);
+    const unsigned g4 = (unsigned)std::min<int64_t>(grid1(n * 4, 256), 512);
     const unsigned g32 = (unsigned)std::min<int64_t>(grid1(n * 32, 256), 1024);
     if (avg <= 8)
         hipLaunchKernelGGL(k_norm_inf_A<4>, dim3(g4), dim3(256), 0, st, rowptr, valmap, values, n, out);
@@ -3369,18 +3518,47 @@ static unsigned red_grid(int64_t n) {
     int64_t g = (n + 255) / 256;
     return (unsigned)(g < 1 ? 1 : (g > 1024 ? 1024 : g));
 }
-void launch_colmax(const double *V, int64_t n, int nrhs, int64_t ld, unsigned long long *out, hipStream_t st) {
-    if (n <= 0 || nrhs <= 0) return;
-    hipLaunchKernelGGL(k_colmax, dim3(std::min(red_grid(n), 128u), nrhs), dim3(256), 0, st, V, n, ld, out);
+// Workgroups a column of a reduction: every chunk its own in a batch; else 512
+// over the launch's columns, two a CU.  Each ends in an atomic and the slots of
+// all columns lie in a line or two, where an atomic takes about 7 ns: 125000
+// rows, 8 columns of r and x with one chunk each (1952 of them) 20.1 us, now
+// COLMAX.
+static unsigned red_chunks(const int32_t *seg, int64_t n, int columns) {
+    const int64_t c = (n + kRedRows - 1) / kRedRows;
+    return (unsigned)(seg ? c : std::min<int64_t>(c, std::max(1, 512 / columns)));
 }
-void launch_coldot(const double *U, const double *V, int64_t n, int nrhs, int64_t ld, double *out, hipStream_t st) {
+#define SPC_LAUNCH_SEG(kernel, grid, ...)                                                                   \
+    do {                                                                                                    \
+        if (seg) hipLaunchKernelGGL(kernel<true>, grid, dim3(256), 0, st, __VA_ARGS__);                     \
+        else hipLaunchKernelGGL(kernel<false>, grid, dim3(256), 0, st, __VA_ARGS__);                        \
+    } while (0)
+void launch_colmax(const double *V0, const double *V1, const int32_t *seg, int64_t n, int nrhs, int64_t ld, int nseg,
+                   unsigned long long *out, int64_t K, hipStream_t st) {
     if (n <= 0 || nrhs <= 0) return;
-    hipLaunchKernelGGL(k_coldot, dim3(std::min(red_grid(n), 128u), nrhs), dim3(256), 0, st, U, V, n, ld, out);
+    SPC_LAUNCH_SEG(k_colmax, dim3(red_chunks(seg, n, 2 * nrhs), nrhs, 2), V0, V1, seg, n, ld, nseg, (double *)out, K);
 }
-void launch_cg_coef(const double *dots, double *rho, const double *frozen, double *coef, int64_t K, bool alpha,
-                    hipStream_t st) {
+void launch_coldot(const double *U, const double *V, const int32_t *seg, int64_t n, int nrhs, int64_t ld, int nseg,
+                   double *out, hipStream_t st) {
+    if (n <= 0 || nrhs <= 0) return;
+    SPC_LAUNCH_SEG(k_coldot, dim3(red_chunks(seg, n, nrhs), nrhs), U, V, seg, n, ld, nseg, out);
+}
+void launch_refine_start(const double *B, int64_t ldb, double *Bw, double *Xw, const int32_t *seg, int64_t n,
+                         int nrhs, int nseg, unsigned long long *out, hipStream_t st) {
+    if (n <= 0 || nrhs <= 0) return;
+    SPC_LAUNCH_SEG(k_refine_start, dim3(red_chunks(seg, n, nrhs), nrhs), B, ldb, Bw, Xw, seg, n, nseg, (double *)out);
+}
+void launch_cg_update(const double *alpha, const double *Pv, const double *Qv, double *X, double *R, double *Z,
+                      const int32_t *seg, int64_t n, int nrhs, int nseg, unsigned long long *out, int64_t K,
+                      hipStream_t st) {
+    if (n <= 0 || nrhs <= 0) return;
+    SPC_LAUNCH_SEG(k_cg_update, dim3(red_chunks(seg, n, 2 * nrhs), nrhs), alpha, Pv, Qv, X, R, Z, seg, n, nseg, (double *)out,
+                   K);
+}
+#undef SPC_LAUNCH_SEG
+void launch_cg_coef(double *dots, double *rho, const double *frozen, double *coef, unsigned long long *umax, int64_t K,
+                    CgCoef mode, hipStream_t st) {
     if (K <= 0) return;
-    hipLaunchKernelGGL(k_cg_coef, dim3(grid1(K, 256)), dim3(256), 0, st, dots, rho, frozen, coef, K, alpha ? 1 : 0);
+    hipLaunchKernelGGL(k_cg_coef, dim3(grid1(K, 256)), dim3(256), 0, st, dots, rho, frozen, coef, umax, K, (int)mode);
 }
 void launch_axpby(const double *a, double a0, const double *X, const double *b, double b0, double *Y, int64_t n,
                   int nrhs, int64_t ld, hipStream_t st) {
@@ -3392,16 +3570,6 @@ void launch_seg_norm_inf_A(const int64_t *rowptr, const int64_t *valmap, const d
     if (n <= 0) return;
     hipLaunchKernelGGL(k_seg_norm_inf_A, dim3(grid1(n, 256)), dim3(256), 0, st, rowptr, valmap, values, seg, n,
                        out);
-}
-void launch_seg_colmax(const double *V, const int32_t *seg, int64_t n, int nrhs, int64_t ld, int nseg,
-                       unsigned long long *out, hipStream_t st) {
-    if (n <= 0 || nrhs <= 0) return;
-    hipLaunchKernelGGL(k_seg_colmax, dim3(grid1(n, kSegRows), nrhs), dim3(256), 0, st, V, seg, n, ld, nseg, out);
-}
-void launch_seg_coldot(const double *U, const double *V, const int32_t *seg, int64_t n, int nrhs, int64_t ld,
-                       int nseg, double *out, hipStream_t st) {
-    if (n <= 0 || nrhs <= 0) return;
-    hipLaunchKernelGGL(k_seg_coldot, dim3(grid1(n, kSegRows), nrhs), dim3(256), 0, st, U, V, seg, n, ld, nseg, out);
 }
 void launch_seg_axpby(const double *a, double a0, const double *X, const double *b, double b0, double *Y,
                       const int32_t *seg, int64_t n, int nrhs, int64_t ld, int nseg, hipStream_t st) {

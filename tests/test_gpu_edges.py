@@ -169,3 +169,48 @@ def test_default_groups_of_blocks(lib):
         err, eta, S = factor_and_solve(lib, matrix, tuning, nrhs=1)
         print(f"{tuning}: worst supernode {err:.2e}, eta {eta:.2e}", flush=True)
         assert S.nsuper == 65 and err <= 1e-10 and eta <= BAR["fp64"]
+
+
+def tridiag_errors(n, values, X, B):
+    """Backward error of each column for a tridiagonal matrix (lower CSC)."""
+    d, e = values[0::2], values[1::2]  # the columns hold (diagonal, below)
+    AX = d[:, None] * X
+    AX[1:] += e[:, None] * X[:-1]
+    AX[:-1] += e[:, None] * X[1:]
+    rows = np.abs(d)
+    rows[1:] += np.abs(e)
+    rows[:-1] += np.abs(e)
+    return np.abs(B - AX).max(0) / (rows.max() * np.abs(X).max(0) + np.abs(B).max(0))
+
+
+@pytest.mark.parametrize("maxit", [0, 4])
+@pytest.mark.parametrize("sizes", [(1,), (255,), (1023,), (1024,), (1025,), (2050,), (1, 1023), (700, 324, 1, 1024, 3),
+                                   (40, 1, 2, 61, 64, 1300)], ids=str)
+@pytest.mark.parametrize("nrhs", [1, 2, 3, 5, 8, 9, 17])
+def test_refinement_reductions(lib, sizes, nrhs, maxit):
+    """Refinement of one system and of batches whose systems end inside and
+    at the chunks of the reductions, over the column counts of the SpMV: the
+    reported backward error is the one taken on the host.  Both residuals are
+    of three products in FP64, so the two differ by at most a few units of
+    roundoff of |A||x| + |b|: 2e-15.  With tol = 0 the steps (refinement, then
+    conjugate gradients) only end at maxit."""
+    import torch
+    systems = [tridiag(n) if n > 1 else dense(1) for n in sizes]
+    rng = np.random.default_rng(nrhs)
+    Bh = [rng.standard_normal((nrhs, n)) * 10.0 ** rng.integers(-3, 4, (nrhs, 1)) for n in sizes]
+    syms = [lib.Symbolic(c, r, p, 0.0) for c, r, _, p in systems]
+    vals = [torch.from_numpy(v).cuda() for _, _, v, _ in systems]
+    Bs = [torch.from_numpy(b).cuda() for b in Bh]
+    Xs = [torch.zeros_like(b) for b in Bs]
+    if len(sizes) == 1:
+        F = lib.factorize(syms[0], vals[0], "fp32")
+        out = [F.solve_refined(vals[0], Bs[0], Xs[0], tol=0.0, maxit=maxit)]
+    else:
+        batch = lib.Batch(syms, "fp32")
+        batch.factorize(vals)
+        out = batch.solve_refined(Bs, Xs, tol=0.0, maxit=maxit)["systems"]
+    for n, (_, _, v, _), b, x, r in zip(sizes, systems, Bh, Xs, out):
+        eta = tridiag_errors(n, v, x.cpu().numpy().T, b.T).max()
+        print(f"n={n} nrhs={nrhs} maxit={maxit}: reported {r['berr']:.3e}, host {eta:.3e}", flush=True)
+        assert abs(r["berr"] - eta) <= 2e-15
+        assert eta <= (1e-5 if maxit == 0 else 1e-14)
