@@ -2876,9 +2876,10 @@ __device__ __forceinline__ int fold_first(int j) {
 // of the row, so a group's index and value loads are contiguous.  Q >= nrhs
 // values a lane, the columns past nrhs those of the last one again: a test
 // on each column made every one of an entry's gathers wait for the one
-// before.  Bound by the gathers' latency at these sizes (125000 rows of 7
-// entries, 8 columns: 50 MB); with the tests and a shuffle per column and
-// step 31 us, now SPMV8; 32 systems of 4096 rows, 16 columns: 137, now SPMV16.
+// before.  Bound by the gathers (125000 rows of 7 entries, 8 columns: 50 MB,
+// 10 us at the copy rate); with the tests and a shuffle per column and step
+// 31.3 us, now 20.2; 32 systems of 10000 rows, 16 columns 137, now 90; 24000
+// rows of 81 entries, 4 columns 19.5, now 13.4.
 template <int LPR, int Q>
 __global__ __launch_bounds__(256) void k_spmv(const int64_t *rowptr, const int32_t *colidx, const int64_t *valmap,
                                               const double *values, const double *X, const double *B, double *Y,
@@ -3176,8 +3177,8 @@ __global__ __launch_bounds__(256) void k_refine_start(const double *B, int64_t l
 // The end of a conjugate-gradient step in one pass: x += alpha p, r -= alpha
 // q, z = r (what the next preconditioner solve starts from), and the maxima
 // of r and x per slot (out, out + K; cleared by k_cg_coef).  As launches of
-// their own these were two updates, a copy, a clear and two reductions: 31 us
-// and their gaps on 24000 rows x 4 columns, now CGUPD us.
+// their own these were two updates, a copy, a clear and two reductions, 29 us
+// and five gaps on 24000 rows x 4 columns; now 5.1 us.
 template <bool SEG>
 __global__ __launch_bounds__(256) void k_cg_update(const double *alpha, const double *Pv, const double *Qv, double *X,
                                                    double *R, double *Z, const int32_t *seg, int64_t n, int nseg,
@@ -3507,6 +3508,8 @@ void launch_norm_inf_A(const int64_t *rowptr, const int64_t *valmap, const doubl
                        unsigned long long *out, hipStream_t st) {
     if (n <= 0) return;
     const int64_t avg = (nnz + n - 1) / n;
+    // (one atomic a workgroup, all on one word: 125000 rows of 7 entries 16.5
+    // us with 1024 workgroups, 13.3 with 512)
     const unsigned g4 = (unsigned)std::min<int64_t>(grid1(n * 4, 256), 512);
     const unsigned g32 = (unsigned)std::min<int64_t>(grid1(n * 32, 256), 1024);
     if (avg <= 8)
@@ -3522,7 +3525,7 @@ static unsigned red_grid(int64_t n) {
 // over the launch's columns, two a CU.  Each ends in an atomic and the slots of
 // all columns lie in a line or two, where an atomic takes about 7 ns: 125000
 // rows, 8 columns of r and x with one chunk each (1952 of them) 20.1 us, now
-// COLMAX.
+// 7.0.  (The maxima of one of the two took 14.2 us with 1024 workgroups.)
 static unsigned red_chunks(const int32_t *seg, int64_t n, int columns) {
     const int64_t c = (n + kRedRows - 1) / kRedRows;
     return (unsigned)(seg ? c : std::min<int64_t>(c, std::max(1, 512 / columns)));
