@@ -427,26 +427,17 @@ void enqueue_solve(const spc::Symbolic &S, const spc::DevPlan &P, const T *Lx, c
     // backward one
     const bool persist = split < S.nslevels;
     spc::launch_solve_init<T>(P, n, nrhs, B, ldb, Y, Acc, persist, nb, sy, st);
-    // below solve_split the tiny supernodes of a level have their own
-    // (one-wave) launch beside the level's task launch
-    const int32_t tsplit = S.solve_split;
-    for (int32_t l = 0; l < split; ++l) {
-        if (l < tsplit)
-            spc::launch_solve_tiny_fwd<T>(P, S.stiny_ptr[l], S.stiny_ptr[l + 1], Lx, Linv, Y, X, n, nrhs, st);
-        spc::launch_solve_fwd<T>(P, S.stask_ptr[l], S.stask_ptr[l + 1], Lx, Linv, Y, X, nullptr, n, nrhs, sy, false,
-                                 st);
-    }
+    for (int32_t l = 0; l < split; ++l)
+        spc::launch_solve_level_fwd<T>(P, S.stask_ptr[l], S.stask_ptr[l + 1], S.stiny_ptr[l], S.stiny_ptr[l + 1], Lx,
+                                       Linv, Y, X, n, nrhs, sy, st);
     if (persist) {
-        spc::launch_solve_fwd<T>(P, S.stask_ptr[split], nt, Lx, Linv, Y, X, Acc, n, nrhs, sy, true, st);
+        spc::launch_solve_fwd<T>(P, S.stask_ptr[split], nt, Lx, Linv, Y, X, Acc, n, nrhs, sy, st);
         spc::launch_solve_turn<T>(Y, Acc, n * nrhs, st);
-        spc::launch_solve_bwd<T>(P, S.stask_ptr[split], nt, Lx, Linv, X, Acc, Y, n, nrhs, sy, true, st);
+        spc::launch_solve_bwd<T>(P, S.stask_ptr[split], nt, Lx, Linv, X, Acc, Y, n, nrhs, sy, st);
     }
-    for (int32_t l = split - 1; l >= 0; --l) {
-        if (l < tsplit)
-            spc::launch_solve_tiny_bwd<T>(P, S.stiny_ptr[l], S.stiny_ptr[l + 1], Lx, Linv, X, n, nrhs, st);
-        spc::launch_solve_bwd<T>(P, S.stask_ptr[l], S.stask_ptr[l + 1], Lx, Linv, X, Acc, nullptr, n, nrhs, sy, false,
-                                 st);
-    }
+    for (int32_t l = split - 1; l >= 0; --l)
+        spc::launch_solve_level_bwd<T>(P, S.stask_ptr[l], S.stask_ptr[l + 1], S.stiny_ptr[l], S.stiny_ptr[l + 1], Lx,
+                                       Linv, X, Acc, n, nrhs, sy, st);
     spc::launch_perm_out<T>(P, n, nrhs, X, B, ldb, st);
 }
 

@@ -146,25 +146,24 @@ void launch_solve_turn(T *Y, T *Acc, int64_t count, hipStream_t st);
 template <typename T>
 void launch_perm_out(const DevPlan &P, int64_t n, int nrhs, const T *W, double *B, int64_t ldb,
                      hipStream_t st);
-// Solve sweeps over tasks t0..t1-1 (one block-tree level), or, with
-// persist, over the tasks of levels solve_split.. in one persistent launch
+// Solve sweeps over the tasks of levels solve_split.. in one persistent launch
 // (t0 = first task of that range, t1 = all tasks; needs launch_solve_init
 // first).
 // H (forward) and XB (backward): the persistent sweeps' hand-over buffers,
 // n x nrhs like Y, every entry unset before the sweep.
 template <typename T>
 void launch_solve_fwd(const DevPlan &P, int64_t t0, int64_t t1, const T *Lx, const T *Linv, T *Y, T *X, T *H,
-                      int64_t n, int nrhs, SolveSync sy, bool persist, hipStream_t st);
-// One-wave solve sweeps over the tiny supernodes t0..t1-1 of one level.
-template <typename T>
-void launch_solve_tiny_fwd(const DevPlan &P, int64_t t0, int64_t t1, const T *Lx, const T *Linv, T *Y, T *X,
-                           int64_t n, int nrhs, hipStream_t st);
-template <typename T>
-void launch_solve_tiny_bwd(const DevPlan &P, int64_t t0, int64_t t1, const T *Lx, const T *Linv, T *X, int64_t n,
-                           int nrhs, hipStream_t st);
+                      int64_t n, int nrhs, SolveSync sy, hipStream_t st);
 template <typename T>
 void launch_solve_bwd(const DevPlan &P, int64_t t0, int64_t t1, const T *Lx, const T *Linv, T *X, T *Acc, T *XB,
-                      int64_t n, int nrhs, SolveSync sy, bool persist, hipStream_t st);
+                      int64_t n, int nrhs, SolveSync sy, hipStream_t st);
+// One level below the sweeps: block tasks t0 .. t1, tiny supernodes s0 .. s1.
+template <typename T>
+void launch_solve_level_fwd(const DevPlan &P, int64_t t0, int64_t t1, int64_t s0, int64_t s1, const T *Lx,
+                            const T *Linv, T *Y, T *X, int64_t n, int nrhs, SolveSync sy, hipStream_t st);
+template <typename T>
+void launch_solve_level_bwd(const DevPlan &P, int64_t t0, int64_t t1, int64_t s0, int64_t s1, const T *Lx,
+                            const T *Linv, T *X, T *Acc, int64_t n, int nrhs, SolveSync sy, hipStream_t st);
 
 // refinement (FP64)
 void launch_spmv(const int64_t *rowptr, const int32_t *colidx, const int64_t *valmap, const double *values,

@@ -1954,6 +1954,224 @@ __device__ __forceinline__ int64_t next_task(int pass, const int32_t *order, int
     return order ? order[i] : i;
 }
 
+template <typename T>
+__device__ __forceinline__ T wave_sum(T v) {
+    v = pair_add<kRor8>(pair_add<kRor4>(pair_add<kXor2>(pair_add<kXor1>(v))));
+    return half_add<32>(half_add<16>(v));
+}
+
+// ---------------------------------------------------------------------------
+// One-wave solves of tiny supernodes (w <= kTinyW, m <= kTinyM), four per
+// workgroup, for the wide bottom levels where nearly every supernode is
+// tiny: a supernode costs one wave instead of a workgroup sized for a
+// 64-column block.  Right-hand sides are interleaved by row (entry (k, q) at
+// k * nrhs + q), so the values of one row sit together.
+// Forward: x = Linv y for the w diagonal rows, stored in X; then each row
+// i >= w below takes
+//   Y[rows[i]] -= sum_c L[i][c] x_c      (atomic, as in the block sweep).
+// One right-hand side: lane i holds row position i, y_c and x_c are
+// broadcast from lane c.  Several: x goes through LDS and the update is the
+// product (rows x w)(w x 16) on 16x16x4 MFMA (four row tiles, two steps of
+// the contraction), so the 16 lanes of one output row write its 16
+// consecutive values.
+// Bound by latency (a trip for the task, one for its rows and panel, one for
+// the values of the rows) and, in the bottom levels of a batch, by the
+// scattered rows.  Everything a wave reads is asked for ahead of its first
+// use, the inverse (at most 64 entries) by one load a lane and through LDS.
+// wg: the workgroup's place among those of the level's tiny tasks; lds:
+// kTinyLds values for each of its waves (several right-hand sides).
+// ---------------------------------------------------------------------------
+static_assert(kTinyW * kTinyW <= 64);
+constexpr int kTinyLds = 2 * kTinyW * (kMaxRhs + 1) + kTinyW * kTinyW;
+
+template <typename T, int NR>
+__device__ __forceinline__ void solve_tiny_fwd_body(int64_t wg, const SmallTask *tasks, int64_t ntasks,
+                                                    const int32_t *rows, const T *Lx, const T *Linv, T *Y, T *X,
+                                                    int nrhs, T *lds) {
+    constexpr int WT = kTinyW;
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    const int64_t ti = wg * 4 + wv;
+    if constexpr (NR == 1) {
+        if (ti >= ntasks) return;  // the whole wave
+        const SmallTask tk = tasks[ti];
+        const int m = tk.m, w = tk.w;
+        const T *P = Lx + tk.loff;
+        const T *Q = Linv + tk.ioff;
+        const int rc = min(lane, m - 1), dc = min(lane, w - 1);
+        T l[WT], vi[WT];
+#pragma unroll
+        for (int c = 0; c < WT; ++c) l[c] = P[(int64_t)min(c, w - 1) * m + rc];
+#pragma unroll
+        for (int c = 0; c < WT; ++c) vi[c] = Q[dc + min(c, w - 1) * w];  // (L^{-1})[dc][c]
+        const int64_t g = rows[tk.roff + rc];
+        const T y = Y[tk.g0 + dc];
+        T x = T(0), acc = T(0);
+#pragma unroll
+        for (int c = 0; c < WT; ++c)
+            if (c < w) x += (c <= lane ? vi[c] : T(0)) * lane_read(y, c);
+#pragma unroll
+        for (int c = 0; c < WT; ++c)
+            if (c < w) acc += l[c] * lane_read(x, c);
+        if (lane < w) X[tk.g0 + lane] = x;
+        else if (lane < m) atomicAdd(&Y[g], -acc);
+    } else {
+        using acc_t = typename Mfma<T>::acc;
+        T(*ys)[kMaxRhs + 1] = (T(*)[kMaxRhs + 1])(lds + wv * kTinyLds);
+        T(*xs)[kMaxRhs + 1] = ys + WT;
+        T *qs = lds + wv * kTinyLds + 2 * WT * (kMaxRhs + 1);
+        const bool active = ti < ntasks;
+        const SmallTask tk = tasks[active ? ti : ntasks - 1];  // idle waves mirror a task, store nothing
+        const int m = tk.m, w = tk.w;
+        const T *P = Lx + tk.loff;
+        const T *Q = Linv + tk.ioff;
+        const int kq = lane & 15, kr = lane >> 4;
+        const int64_t g = rows[tk.roff + min(lane, m - 1)];  // lane = row position
+        // A operands: row 16 tt + kq of the panel, columns 4 s + kr
+        T a[4][2];
+#pragma unroll
+        for (int tt = 0; tt < 4; ++tt)
+#pragma unroll
+            for (int s2 = 0; s2 < 2; ++s2)
+                a[tt][s2] = P[(int64_t)min(4 * s2 + kr, w - 1) * m + min(16 * tt + kq, m - 1)];
+        // y of the diagonal rows, two (c, q) slots per lane: c = kr + 4 h
+        const T ql = Q[min(lane, w * w - 1)];
+        T yv[2];
+#pragma unroll
+        for (int h = 0; h < 2; ++h) yv[h] = Y[(tk.g0 + min(kr + 4 * h, w - 1)) * nrhs + min(kq, nrhs - 1)];
+#pragma unroll
+        for (int h = 0; h < 2; ++h) ys[kr + 4 * h][kq] = (kr + 4 * h < w && kq < nrhs) ? yv[h] : T(0);
+        qs[lane] = ql;
+        wave_lds_sync();
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const int c = kr + 4 * h;
+            T xv = T(0);
+#pragma unroll
+            for (int j = 0; j < WT; ++j) {
+                const T vq = qs[min(c, w - 1) + min(j, w - 1) * w];  // (L^{-1})[c][j]
+                xv += (j <= c && c < w) ? vq * ys[j][kq] : T(0);
+            }
+            xs[c][kq] = xv;
+            if (active && c < w && kq < nrhs) X[(tk.g0 + c) * nrhs + kq] = xv;
+        }
+        wave_lds_sync();
+        // B operands: x[4 s + kr][kq] (zero beyond w)
+        const T b0 = xs[kr][kq], b1 = xs[4 + kr][kq];
+#pragma unroll
+        for (int tt = 0; tt < 4; ++tt) {
+            if (16 * tt >= m) break;  // uniform
+            acc_t acc = {0, 0, 0, 0};
+            acc = Mfma<T>::run(4 * 0 + kr < w ? a[tt][0] : T(0), b0, acc);
+            acc = Mfma<T>::run(4 + kr < w ? a[tt][1] : T(0), b1, acc);
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const int r = 16 * tt + Mfma<T>::row(lane, v);
+                const int64_t gr = __shfl(g, min(r, 63));
+                if (active && r >= w && r < m && kq < nrhs) atomicAdd(&Y[gr * nrhs + kq], -acc[v]);
+            }
+        }
+    }
+}
+
+// Backward: t_c = X[g0 + c] - sum_{i >= w} L[i][c] X[rows[i]] for the w
+// columns c (the rows below are ancestors, final already), then
+// x = Linv^T t.  One right-hand side: the sums are wave reductions.
+// Several: the sums form the product (L_below^T)(X_rows), w x 16 with up to
+// 64 rows of contraction, on 16x16x4 MFMA (A: lane l brings L[k][l%16],
+// B: X[rows[k]][l%16], k = 4 s + l/16); t goes through LDS for the final
+// small product with the inverse.
+template <typename T, int NR>
+__device__ __forceinline__ void solve_tiny_bwd_body(int64_t wg, const SmallTask *tasks, int64_t ntasks,
+                                                    const int32_t *rows, const T *Lx, const T *Linv, T *X, int nrhs,
+                                                    T *lds) {
+    constexpr int WT = kTinyW;
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    const int64_t tr = wg * 4 + wv;
+    const bool active = tr < ntasks;
+    const SmallTask tk = tasks[active ? tr : ntasks - 1];  // idle waves mirror a task, store nothing
+    const int m = tk.m, w = tk.w;
+    const T *P = Lx + tk.loff;
+    const T *Q = Linv + tk.ioff;
+    const int rc = min(lane, m - 1), dc = min(lane, w - 1);
+    const int64_t g = rows[tk.roff + rc];
+    if constexpr (NR == 1) {
+        T l[WT], vt[WT];
+#pragma unroll
+        for (int c = 0; c < WT; ++c) l[c] = P[(int64_t)min(c, w - 1) * m + rc];
+#pragma unroll
+        for (int i = 0; i < WT; ++i) vt[i] = Q[min(i, w - 1) + dc * w];  // (L^{-1})[i][dc]
+        const T xr = (lane >= w && lane < m) ? X[g] : T(0);
+        T t = X[tk.g0 + dc];
+#pragma unroll
+        for (int c = 0; c < WT; ++c)
+            if (c < w) {
+                const T sc = wave_sum(l[c] * xr);
+                if (lane == c) t -= sc;
+            }
+        T xv = T(0);
+#pragma unroll
+        for (int i = 0; i < WT; ++i)
+            if (i < w) xv += (i >= lane ? vt[i] : T(0)) * lane_read(t, i);
+        if (active && lane < w) X[tk.g0 + lane] = xv;
+    } else {
+        using acc_t = typename Mfma<T>::acc;
+        const int kq = lane & 15, kr = lane >> 4;
+        T(*ts)[kMaxRhs + 1] = (T(*)[kMaxRhs + 1])(lds + wv * kTinyLds);
+        T *qs = lds + wv * kTinyLds + WT * (kMaxRhs + 1);
+        T a[16], b[16], xo[4];
+        const T ql = Q[min(lane, w * w - 1)];
+#pragma unroll
+        for (int v = 0; v < 4; ++v)
+            xo[v] = X[(tk.g0 + min(Mfma<T>::row(lane, v), w - 1)) * nrhs + min(kq, nrhs - 1)];
+#pragma unroll
+        for (int s = 0; s < 16; ++s) {
+            const int k = 4 * s + kr, kc = min(k, m - 1);
+            const int64_t gk = __shfl(g, kc);
+            const bool row_ok = k >= w && k < m;
+            const T av = P[(int64_t)min(kq, w - 1) * m + kc];
+            const T bv = X[gk * nrhs + min(kq, nrhs - 1)];
+            a[s] = (row_ok && kq < w) ? av : T(0);
+            b[s] = (row_ok && kq < nrhs) ? bv : T(0);
+        }
+        acc_t acc = {0, 0, 0, 0};
+#pragma unroll
+        for (int s = 0; s < 16; ++s) acc = Mfma<T>::run(a[s], b[s], acc);
+        // element v of this lane: row c of (L_below^T X_rows), column kq
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            const int c = Mfma<T>::row(lane, v);
+            if (c < WT) ts[c][kq] = (c < w && kq < nrhs) ? xo[v] - acc[v] : T(0);
+        }
+        qs[lane] = ql;
+        wave_lds_sync();
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const int c = kr + 4 * h;
+            T xv = T(0);
+#pragma unroll
+            for (int i = 0; i < WT; ++i) {
+                const T vq = qs[min(i, w - 1) + min(c, w - 1) * w];  // (L^{-1})[i][c]
+                xv += (i >= c && i < w) ? vq * ts[i][kq] : T(0);
+            }
+            if (active && c < w && kq < nrhs) X[(tk.g0 + c) * nrhs + kq] = xv;
+        }
+    }
+}
+
+// Levels whose tiny supernodes are launched by themselves
+template <typename T, int NR>
+__global__ __launch_bounds__(256) void k_solve_tiny_fwd(const SmallTask *tasks, int64_t ntasks, const int32_t *rows,
+                                                        const T *Lx, const T *Linv, T *Y, T *X, int nrhs) {
+    __shared__ T lds[NR > 1 ? 4 * kTinyLds : 1];
+    solve_tiny_fwd_body<T, NR>(blockIdx.x, tasks, ntasks, rows, Lx, Linv, Y, X, nrhs, lds);
+}
+template <typename T, int NR>
+__global__ __launch_bounds__(256) void k_solve_tiny_bwd(const SmallTask *tasks, int64_t ntasks, const int32_t *rows,
+                                                        const T *Lx, const T *Linv, T *X, int nrhs) {
+    __shared__ T lds[NR > 1 ? 4 * kTinyLds : 1];
+    solve_tiny_bwd_body<T, NR>(blockIdx.x, tasks, ntasks, rows, Lx, Linv, X, nrhs, lds);
+}
+
 // Forward, one task = rows r0..r1-1 below block q:
 //   x_q = Linv_q y_q (every task; the first task stores it in X), then
 //   Y[rows[r]] -= sum_k L[r][c0+k] x_q[k] (atomic).
@@ -1970,7 +2188,11 @@ __device__ __forceinline__ int64_t next_task(int pass, const int32_t *order, int
 template <typename T, bool PERSIST>
 __global__ __launch_bounds__(256) void k_solve_fwd(const SolveTask *tasks, int64_t ntasks, const int32_t *rows,
                                                    const T *Lx, const T *Linv, T *Y, T *X, T *H, int64_t n,
-                                                   const int64_t *tgt_ptr, const int32_t *tgt, SolveSync sy) {
+                                                   const int64_t *tgt_ptr, const int32_t *tgt, SolveSync sy,
+                                                   const SmallTask *tiny, int64_t ntiny) {
+    if constexpr (!PERSIST)
+        if (blockIdx.x >= ntasks)
+            return solve_tiny_fwd_body<T, 1>(blockIdx.x - ntasks, tiny, ntiny, rows, Lx, Linv, Y, X, 1, nullptr);
     constexpr int NB = kNB, QW = NB / 4;
     __shared__ T yq[NB];
     __shared__ T xq[NB];
@@ -2064,11 +2286,18 @@ template <typename T, bool PERSIST>
 __global__ __launch_bounds__(256, 2) void k_solve_fwd_multi(const SolveTask *tasks, int64_t ntasks,
                                                          const int32_t *rows, const T *Lx, const T *Linv, T *Y,
                                                          T *X, T *H, int64_t n, int nrhs, const int64_t *tgt_ptr,
-                                                         const int32_t *tgt, SolveSync sy) {
+                                                         const int32_t *tgt, SolveSync sy,
+                                                         const SmallTask *tiny, int64_t ntiny) {
     constexpr int NB = kNB, NR = kMaxRhs, YPT = NB * NR / 256, KS = NB / 4;
     using acc_t = typename Mfma<T>::acc;
-    __shared__ T yq[NB][NR + 1];
-    __shared__ T xq[NB][NR + 1];
+    __shared__ T yx[2][NB][NR + 1];
+    auto &yq = yx[0], &xq = yx[1];
+    if constexpr (!PERSIST) {
+        static_assert(4 * kTinyLds <= 2 * NB * (NR + 1));
+        if (blockIdx.x >= ntasks)
+            return solve_tiny_fwd_body<T, NR>(blockIdx.x - ntasks, tiny, ntiny, rows, Lx, Linv, Y, X, nrhs,
+                                              &yx[0][0][0]);
+    }
     __shared__ int64_t grs[256];
     __shared__ int32_t slot;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -2435,7 +2664,7 @@ template <typename T, bool PERSIST>
 __global__ __launch_bounds__(256, 2) void k_solve_bwd_multi(const SolveTask *tasks, int64_t ntasks,
                                                             const int32_t *order, const int32_t *rows, const T *Lx,
                                                             const T *Linv, T *X, T *Acc, T *XB, int64_t n, int nrhs,
-                                                            SolveSync sy) {
+                                                            SolveSync sy, const SmallTask *tiny, int64_t ntiny) {
     constexpr int NB = kNB, NR = kMaxRhs, NT = NB / 16, EPT = NB * NR / 256;
     using M = Mfma<T>;
     using acc_t = typename M::acc;
@@ -2445,6 +2674,16 @@ __global__ __launch_bounds__(256, 2) void k_solve_bwd_multi(const SolveTask *tas
     __shared__ int32_t grs[256];
     __shared__ int last;
     __shared__ int32_t slot;
+    if constexpr (!PERSIST) {
+        static_assert(4 * kTinyLds <= 4 * NB * (NR + 1));
+        if (blockIdx.x >= ntasks) {
+            const int64_t wg = blockIdx.x - ntasks;
+            T *lds = &Sm[0][0][0];
+            if (nrhs == 1) solve_tiny_bwd_body<T, 1>(wg, tiny, ntiny, rows, Lx, Linv, X, 1, lds);
+            else solve_tiny_bwd_body<T, NR>(wg, tiny, ntiny, rows, Lx, Linv, X, nrhs, lds);
+            return;
+        }
+    }
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int kq = lane & 15, kg = lane >> 4;
@@ -2630,193 +2869,6 @@ __global__ __launch_bounds__(256, 2) void k_solve_bwd_multi(const SolveTask *tas
             }
         }
         __syncthreads();
-    }
-}
-
-// ---------------------------------------------------------------------------
-// One-wave solves of tiny supernodes (w <= kTinyW, m <= kTinyM), four per
-// workgroup, for the wide bottom levels where nearly every supernode is
-// tiny: a supernode costs one wave instead of a workgroup sized for a
-// 64-column block.  Right-hand sides are interleaved by row (entry (k, q) at
-// k * nrhs + q), so the values of one row sit together.
-// Forward: x = Linv y for the w diagonal rows, stored in X; then each row
-// i >= w below takes
-//   Y[rows[i]] -= sum_c L[i][c] x_c      (atomic, as in the block sweep).
-// One right-hand side: lane i holds row position i, y_c and x_c are
-// broadcast from lane c.  Several: x goes through LDS and the update is the
-// product (rows x w)(w x 16) on 16x16x4 MFMA (four row tiles, two steps of
-// the contraction), so the 16 lanes of one output row write its 16
-// consecutive values.
-// ---------------------------------------------------------------------------
-template <typename T, int NR>
-__global__ __launch_bounds__(256) void k_solve_tiny_fwd(const SmallTask *tasks, int64_t ntasks, const int32_t *rows,
-                                                        const T *Lx, const T *Linv, T *Y, T *X, int64_t n,
-                                                        int nrhs) {
-    constexpr int WT = kTinyW;
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    const int64_t ti = (int64_t)blockIdx.x * 4 + wv;
-    if constexpr (NR == 1) {
-        if (ti >= ntasks) return;  // the whole wave
-        const SmallTask tk = tasks[ti];
-        const int m = tk.m, w = tk.w;
-        const T *P = Lx + tk.loff;
-        const T *Q = Linv + tk.ioff;
-        const int rc = min(lane, m - 1), dc = min(lane, w - 1);
-        T l[WT], vi[WT];
-#pragma unroll
-        for (int c = 0; c < WT; ++c) l[c] = P[(int64_t)min(c, w - 1) * m + rc];
-#pragma unroll
-        for (int c = 0; c < WT; ++c) vi[c] = Q[dc + min(c, w - 1) * w];  // (L^{-1})[dc][c]
-        const int64_t g = rows[tk.roff + rc];
-        const T y = Y[tk.g0 + dc];
-        T x = T(0), acc = T(0);
-#pragma unroll
-        for (int c = 0; c < WT; ++c)
-            if (c < w) x += (c <= lane ? vi[c] : T(0)) * lane_read(y, c);
-#pragma unroll
-        for (int c = 0; c < WT; ++c)
-            if (c < w) acc += l[c] * lane_read(x, c);
-        if (lane < w) X[tk.g0 + lane] = x;
-        else if (lane < m) atomicAdd(&Y[g], -acc);
-    } else {
-        using acc_t = typename Mfma<T>::acc;
-        __shared__ T ys[4][WT][kMaxRhs + 1];
-        __shared__ T xs[4][WT][kMaxRhs + 1];
-        const bool active = ti < ntasks;
-        const SmallTask tk = tasks[active ? ti : ntasks - 1];  // idle waves mirror a task, store nothing
-        const int m = tk.m, w = tk.w;
-        const T *P = Lx + tk.loff;
-        const T *Q = Linv + tk.ioff;
-        const int kq = lane & 15, kr = lane >> 4;
-        const int64_t g = rows[tk.roff + min(lane, m - 1)];  // lane = row position
-        // A operands: row 16 tt + kq of the panel, columns 4 s + kr
-        T a[4][2];
-#pragma unroll
-        for (int tt = 0; tt < 4; ++tt)
-#pragma unroll
-            for (int s2 = 0; s2 < 2; ++s2)
-                a[tt][s2] = P[(int64_t)min(4 * s2 + kr, w - 1) * m + min(16 * tt + kq, m - 1)];
-        // y of the diagonal rows, two (c, q) slots per lane: c = kr + 4 h
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            const int c = kr + 4 * h;
-            const T yv = Y[(tk.g0 + min(c, w - 1)) * nrhs + min(kq, nrhs - 1)];
-            ys[wv][c][kq] = (c < w && kq < nrhs) ? yv : T(0);
-        }
-        __syncthreads();
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            const int c = kr + 4 * h;
-            T xv = T(0);
-#pragma unroll
-            for (int j = 0; j < WT; ++j) {
-                const T vq = Q[min(c, w - 1) + (int64_t)min(j, w - 1) * w];  // (L^{-1})[c][j]
-                xv += (j <= c && c < w) ? vq * ys[wv][j][kq] : T(0);
-            }
-            xs[wv][c][kq] = xv;
-            if (active && c < w && kq < nrhs) X[(tk.g0 + c) * nrhs + kq] = xv;
-        }
-        __syncthreads();
-        // B operands: x[4 s + kr][kq] (zero beyond w)
-        const T b0 = xs[wv][kr][kq], b1 = xs[wv][4 + kr][kq];
-#pragma unroll
-        for (int tt = 0; tt < 4; ++tt) {
-            if (16 * tt >= m) break;  // uniform
-            acc_t acc = {0, 0, 0, 0};
-            acc = Mfma<T>::run(4 * 0 + kr < w ? a[tt][0] : T(0), b0, acc);
-            acc = Mfma<T>::run(4 + kr < w ? a[tt][1] : T(0), b1, acc);
-#pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                const int r = 16 * tt + Mfma<T>::row(lane, v);
-                const int64_t gr = __shfl(g, min(r, 63));
-                if (active && r >= w && r < m && kq < nrhs) atomicAdd(&Y[gr * nrhs + kq], -acc[v]);
-            }
-        }
-    }
-}
-
-template <typename T>
-__device__ __forceinline__ T wave_sum(T v) {
-    v = pair_add<kRor8>(pair_add<kRor4>(pair_add<kXor2>(pair_add<kXor1>(v))));
-    return half_add<32>(half_add<16>(v));
-}
-
-// Backward: t_c = X[g0 + c] - sum_{i >= w} L[i][c] X[rows[i]] for the w
-// columns c (the rows below are ancestors, final already), then
-// x = Linv^T t.  One right-hand side: the sums are wave reductions.
-// Several: the sums form the product (L_below^T)(X_rows), w x 16 with up to
-// 64 rows of contraction, on 16x16x4 MFMA (A: lane l brings L[k][l%16],
-// B: X[rows[k]][l%16], k = 4 s + l/16); t goes through LDS for the final
-// small product with the inverse.
-template <typename T, int NR>
-__global__ __launch_bounds__(256) void k_solve_tiny_bwd(const SmallTask *tasks, int64_t ntasks, const int32_t *rows,
-                                                        const T *Lx, const T *Linv, T *X, int64_t n, int nrhs) {
-    constexpr int WT = kTinyW;
-    __shared__ T ts[4][WT][kMaxRhs + 1];
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    const int64_t tr = (int64_t)blockIdx.x * 4 + wv;
-    const bool active = tr < ntasks;
-    const SmallTask tk = tasks[active ? tr : ntasks - 1];  // idle waves mirror a task, store nothing
-    const int m = tk.m, w = tk.w;
-    const T *P = Lx + tk.loff;
-    const T *Q = Linv + tk.ioff;
-    const int rc = min(lane, m - 1), dc = min(lane, w - 1);
-    const int64_t g = rows[tk.roff + rc];
-    if constexpr (NR == 1) {
-        T l[WT], vt[WT];
-#pragma unroll
-        for (int c = 0; c < WT; ++c) l[c] = P[(int64_t)min(c, w - 1) * m + rc];
-#pragma unroll
-        for (int i = 0; i < WT; ++i) vt[i] = Q[min(i, w - 1) + dc * w];  // (L^{-1})[i][dc]
-        const T xr = (lane >= w && lane < m) ? X[g] : T(0);
-        T t = X[tk.g0 + dc];
-#pragma unroll
-        for (int c = 0; c < WT; ++c)
-            if (c < w) {
-                const T sc = wave_sum(l[c] * xr);
-                if (lane == c) t -= sc;
-            }
-        T xv = T(0);
-#pragma unroll
-        for (int i = 0; i < WT; ++i)
-            if (i < w) xv += (i >= lane ? vt[i] : T(0)) * lane_read(t, i);
-        if (active && lane < w) X[tk.g0 + lane] = xv;
-    } else {
-        using acc_t = typename Mfma<T>::acc;
-        const int kq = lane & 15, kr = lane >> 4;
-        T a[16], b[16];
-#pragma unroll
-        for (int s = 0; s < 16; ++s) {
-            const int k = 4 * s + kr, kc = min(k, m - 1);
-            const int64_t gk = __shfl(g, kc);
-            const bool row_ok = k >= w && k < m;
-            const T av = P[(int64_t)min(kq, w - 1) * m + kc];
-            const T bv = X[gk * nrhs + min(kq, nrhs - 1)];
-            a[s] = (row_ok && kq < w) ? av : T(0);
-            b[s] = (row_ok && kq < nrhs) ? bv : T(0);
-        }
-        acc_t acc = {0, 0, 0, 0};
-#pragma unroll
-        for (int s = 0; s < 16; ++s) acc = Mfma<T>::run(a[s], b[s], acc);
-        // element v of this lane: row c of (L_below^T X_rows), column kq
-#pragma unroll
-        for (int v = 0; v < 4; ++v) {
-            const int c = Mfma<T>::row(lane, v);
-            const T xo = X[(tk.g0 + min(c, w - 1)) * nrhs + min(kq, nrhs - 1)];
-            if (c < WT) ts[wv][c][kq] = (c < w && kq < nrhs) ? xo - acc[v] : T(0);
-        }
-        __syncthreads();
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            const int c = kr + 4 * h;
-            T xv = T(0);
-#pragma unroll
-            for (int i = 0; i < WT; ++i) {
-                const T vq = Q[min(i, w - 1) + (int64_t)min(c, w - 1) * w];  // (L^{-1})[i][c]
-                xv += (i >= c && i < w) ? vq * ts[wv][i][kq] : T(0);
-            }
-            if (active && c < w && kq < nrhs) X[(tk.g0 + c) * nrhs + kq] = xv;
-        }
     }
 }
 
@@ -3402,78 +3454,97 @@ inline unsigned persist_grid(int64_t ntasks) {
     return (unsigned)std::max<int64_t>(1, std::min<int64_t>(ntasks, 512));
 }
 
+// The persistent sweeps over the tasks t0 .. t1
 template <typename T>
 void launch_solve_fwd(const DevPlan &P, int64_t t0, int64_t t1, const T *Lx, const T *Linv, T *Y, T *X, T *H,
-                      int64_t n, int nrhs, SolveSync sy, bool persist, hipStream_t st) {
+                      int64_t n, int nrhs, SolveSync sy, hipStream_t st) {
     if (t1 <= t0) return;
     const int64_t nt = t1 - t0;
-    const dim3 g(persist ? persist_grid(nt) : (unsigned)nt), b(256);
+    const dim3 g(persist_grid(nt)), b(256);
     const SolveTask *tk = P.stasks + t0;
     const int64_t *tp = P.stgt_ptr + t0;
-    if (nrhs == 1) {
-        if (persist)
-            hipLaunchKernelGGL((k_solve_fwd<T, true>), g, b, 0, st, tk, nt, P.rows, Lx, Linv, Y, X, H, n, tp, P.stgt,
-                               sy);
-        else
-            hipLaunchKernelGGL((k_solve_fwd<T, false>), g, b, 0, st, tk, nt, P.rows, Lx, Linv, Y, X, H, n, tp, P.stgt,
-                               sy);
-    } else {
-        if (persist)
-            hipLaunchKernelGGL((k_solve_fwd_multi<T, true>), g, b, 0, st, tk, nt, P.rows, Lx, Linv, Y, X, H, n, nrhs,
-                               tp, P.stgt, sy);
-        else
-            hipLaunchKernelGGL((k_solve_fwd_multi<T, false>), g, b, 0, st, tk, nt, P.rows, Lx, Linv, Y, X, H, n, nrhs,
-                               tp, P.stgt, sy);
-    }
-}
-
-template <typename T>
-void launch_solve_tiny_fwd(const DevPlan &P, int64_t t0, int64_t t1, const T *Lx, const T *Linv, T *Y, T *X,
-                           int64_t n, int nrhs, hipStream_t st) {
-    if (t1 <= t0) return;
-    const dim3 g((unsigned)((t1 - t0 + 3) / 4)), b(256);
     if (nrhs == 1)
-        hipLaunchKernelGGL((k_solve_tiny_fwd<T, 1>), g, b, 0, st, P.stiny + t0, t1 - t0, P.rows, Lx, Linv, Y, X, n,
-                           nrhs);
+        hipLaunchKernelGGL((k_solve_fwd<T, true>), g, b, 0, st, tk, nt, P.rows, Lx, Linv, Y, X, H, n, tp, P.stgt, sy,
+                           nullptr, 0);
     else
-        hipLaunchKernelGGL((k_solve_tiny_fwd<T, kMaxRhs>), g, b, 0, st, P.stiny + t0, t1 - t0, P.rows, Lx, Linv, Y,
-                           X, n, nrhs);
-}
-
-template <typename T>
-void launch_solve_tiny_bwd(const DevPlan &P, int64_t t0, int64_t t1, const T *Lx, const T *Linv, T *X, int64_t n,
-                           int nrhs, hipStream_t st) {
-    if (t1 <= t0) return;
-    const dim3 g((unsigned)((t1 - t0 + 3) / 4)), b(256);
-    if (nrhs == 1)
-        hipLaunchKernelGGL((k_solve_tiny_bwd<T, 1>), g, b, 0, st, P.stiny + t0, t1 - t0, P.rows, Lx, Linv, X, n,
-                           nrhs);
-    else
-        hipLaunchKernelGGL((k_solve_tiny_bwd<T, kMaxRhs>), g, b, 0, st, P.stiny + t0, t1 - t0, P.rows, Lx, Linv, X,
-                           n, nrhs);
+        hipLaunchKernelGGL((k_solve_fwd_multi<T, true>), g, b, 0, st, tk, nt, P.rows, Lx, Linv, Y, X, H, n, nrhs, tp,
+                           P.stgt, sy, nullptr, 0);
 }
 
 template <typename T>
 void launch_solve_bwd(const DevPlan &P, int64_t t0, int64_t t1, const T *Lx, const T *Linv, T *X, T *Acc, T *XB,
-                      int64_t n, int nrhs, SolveSync sy, bool persist, hipStream_t st) {
+                      int64_t n, int nrhs, SolveSync sy, hipStream_t st) {
     if (t1 <= t0) return;
     const int64_t nt = t1 - t0;
-    const dim3 g(persist ? persist_grid(nt) : (unsigned)nt), b(256);
-    // the persistent sweep takes its tasks (global indices) from bwd_order
-    const SolveTask *tk = persist ? P.stasks : P.stasks + t0;
-    const int32_t *ord = persist ? P.bwd_order : nullptr;
-    // (level launches take the MFMA form for one right-hand side too: their
-    // tasks wait for nothing and only move the panel, 47 against 28 us a
-    // launch on the 60^3 grid; in the persistent sweep its longer path from
-    // block to block costs more, 657 against 444 us)
-    if (persist && nrhs == 1)
-        hipLaunchKernelGGL((k_solve_bwd<T>), g, b, 0, st, tk, nt, ord, P.rows, Lx, Linv, X, Acc, XB, sy);
-    else if (persist)
-        hipLaunchKernelGGL((k_solve_bwd_multi<T, true>), g, b, 0, st, tk, nt, ord, P.rows, Lx, Linv, X, Acc, XB, n,
-                           nrhs, sy);
+    const dim3 g(persist_grid(nt)), b(256);
+    // (tasks by their global indices, in the order of bwd_order)
+    if (nrhs == 1)
+        hipLaunchKernelGGL((k_solve_bwd<T>), g, b, 0, st, P.stasks, nt, P.bwd_order, P.rows, Lx, Linv, X, Acc, XB, sy);
     else
-        hipLaunchKernelGGL((k_solve_bwd_multi<T, false>), g, b, 0, st, tk, nt, ord, P.rows, Lx, Linv, X, Acc, XB, n,
-                           nrhs, sy);
+        hipLaunchKernelGGL((k_solve_bwd_multi<T, true>), g, b, 0, st, P.stasks, nt, P.bwd_order, P.rows, Lx, Linv, X,
+                           Acc, XB, n, nrhs, sy, nullptr, 0);
+}
+
+// One level: its block tasks t0 .. t1 and its tiny supernodes s0 .. s1, in one
+// launch.  A launch of either takes 5 to 8 us at the levels below the sweeps,
+// most of it start and end: a 50^3 refined re-solve (FP32, 8 columns) 2734 us
+// with two launches a level, 2641 with one where the tiny supernodes fill at
+// most 512 workgroups, 2593 at most 4096, 2601 always; 32 systems 21^3 (16
+// columns) 8443, 8200, 8102, 8118; 34^3 FP32 step 3242, 3208, 3216, 3236.
+// Beyond that the tiny ones' own kernel, with fewer registers and less LDS,
+// holds more of them in flight.
+constexpr int64_t kSolveMergeTiny = 4096;
+
+template <typename T>
+void launch_solve_level_fwd(const DevPlan &P, int64_t t0, int64_t t1, int64_t s0, int64_t s1, const T *Lx,
+                            const T *Linv, T *Y, T *X, int64_t n, int nrhs, SolveSync sy, hipStream_t st) {
+    const int64_t nt = t1 - t0, wgs = (s1 - s0 + 3) / 4;
+    const bool merge = nt > 0 && wgs <= kSolveMergeTiny;
+    const dim3 b(256);
+    const SmallTask *tiny = P.stiny + s0;
+    if (wgs > 0 && !merge) {
+        if (nrhs == 1)
+            hipLaunchKernelGGL((k_solve_tiny_fwd<T, 1>), dim3((unsigned)wgs), b, 0, st, tiny, s1 - s0, P.rows, Lx,
+                               Linv, Y, X, nrhs);
+        else
+            hipLaunchKernelGGL((k_solve_tiny_fwd<T, kMaxRhs>), dim3((unsigned)wgs), b, 0, st, tiny, s1 - s0, P.rows,
+                               Lx, Linv, Y, X, nrhs);
+    }
+    if (nt <= 0) return;
+    const dim3 g((unsigned)(nt + (merge ? wgs : 0)));
+    const SolveTask *tk = P.stasks + t0;
+    const int64_t *tp = P.stgt_ptr + t0;
+    if (nrhs == 1)
+        hipLaunchKernelGGL((k_solve_fwd<T, false>), g, b, 0, st, tk, nt, P.rows, Lx, Linv, Y, X, (T *)nullptr, n, tp,
+                           P.stgt, sy, tiny, s1 - s0);
+    else
+        hipLaunchKernelGGL((k_solve_fwd_multi<T, false>), g, b, 0, st, tk, nt, P.rows, Lx, Linv, Y, X, (T *)nullptr, n,
+                           nrhs, tp, P.stgt, sy, tiny, s1 - s0);
+}
+
+// (the blocks take the MFMA form for one right-hand side too: their tasks wait
+// for nothing and only move the panel, 47 against 28 us a launch on the 60^3
+// grid; in the persistent sweep its longer path from block to block costs
+// more, 657 against 444 us)
+template <typename T>
+void launch_solve_level_bwd(const DevPlan &P, int64_t t0, int64_t t1, int64_t s0, int64_t s1, const T *Lx,
+                            const T *Linv, T *X, T *Acc, int64_t n, int nrhs, SolveSync sy, hipStream_t st) {
+    const int64_t nt = t1 - t0, wgs = (s1 - s0 + 3) / 4;
+    const bool merge = nt > 0 && wgs <= kSolveMergeTiny;
+    const dim3 b(256);
+    const SmallTask *tiny = P.stiny + s0;
+    if (wgs > 0 && !merge) {
+        if (nrhs == 1)
+            hipLaunchKernelGGL((k_solve_tiny_bwd<T, 1>), dim3((unsigned)wgs), b, 0, st, tiny, s1 - s0, P.rows, Lx,
+                               Linv, X, nrhs);
+        else
+            hipLaunchKernelGGL((k_solve_tiny_bwd<T, kMaxRhs>), dim3((unsigned)wgs), b, 0, st, tiny, s1 - s0, P.rows,
+                               Lx, Linv, X, nrhs);
+    }
+    if (nt <= 0) return;
+    hipLaunchKernelGGL((k_solve_bwd_multi<T, false>), dim3((unsigned)(nt + (merge ? wgs : 0))), b, 0, st,
+                       P.stasks + t0, nt, (const int32_t *)nullptr, P.rows, Lx, Linv, X, Acc, (T *)nullptr, n, nrhs,
+                       sy, tiny, s1 - s0);
 }
 
 template <int LPR>
@@ -3610,13 +3681,13 @@ template void launch_zero<unsigned long long>(unsigned long long *, int64_t, hip
     template void launch_perm_out<T>(const DevPlan &, int64_t, int, const T *, double *, int64_t,           \
                                      hipStream_t);                                                          \
     template void launch_solve_fwd<T>(const DevPlan &, int64_t, int64_t, const T *, const T *, T *, T *, T *, \
-                                      int64_t, int, SolveSync, bool, hipStream_t);                          \
+                                      int64_t, int, SolveSync, hipStream_t);                                \
     template void launch_solve_bwd<T>(const DevPlan &, int64_t, int64_t, const T *, const T *, T *, T *, T *, \
-                                      int64_t, int, SolveSync, bool, hipStream_t);                          \
-    template void launch_solve_tiny_fwd<T>(const DevPlan &, int64_t, int64_t, const T *, const T *, T *, T *, \
-                                           int64_t, int, hipStream_t);                                      \
-    template void launch_solve_tiny_bwd<T>(const DevPlan &, int64_t, int64_t, const T *, const T *, T *,     \
-                                           int64_t, int, hipStream_t);
+                                      int64_t, int, SolveSync, hipStream_t);                                \
+    template void launch_solve_level_fwd<T>(const DevPlan &, int64_t, int64_t, int64_t, int64_t, const T *, \
+                                            const T *, T *, T *, int64_t, int, SolveSync, hipStream_t);     \
+    template void launch_solve_level_bwd<T>(const DevPlan &, int64_t, int64_t, int64_t, int64_t, const T *, \
+                                            const T *, T *, T *, int64_t, int, SolveSync, hipStream_t);
 SPC_INSTANTIATE(double)
 SPC_INSTANTIATE(float)
 

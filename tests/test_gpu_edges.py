@@ -214,3 +214,35 @@ def test_refinement_reductions(lib, sizes, nrhs, maxit):
         print(f"n={n} nrhs={nrhs} maxit={maxit}: reported {r['berr']:.3e}, host {eta:.3e}", flush=True)
         assert abs(r["berr"] - eta) <= 2e-15
         assert eta <= (1e-5 if maxit == 0 else 1e-14)
+
+
+@pytest.mark.parametrize("precision", ["fp64", "fp32"])
+@pytest.mark.parametrize("tiny", [1, 3, 6, 16380, 16388])
+def test_solve_levels_of_tiny_and_wide_supernodes(lib, tiny, precision):
+    """A solve level that holds both kinds: its tiny supernodes share the
+    block tasks' launch up to 4096 workgroups of four and have one of their
+    own beyond, with ragged last workgroups in both."""
+    import torch
+    w, b, wide_w, wide_blocks = 3, 20, 40, 3
+    n = tiny * w + wide_blocks * wide_w + b
+    rows, cols, c0 = [], [], 0
+    for width in [w] * tiny + [wide_w] * wide_blocks + [b]:
+        r, c = np.tril_indices(width, -1)
+        rows.append(c0 + r)
+        cols.append(c0 + c)
+        if c0 + width < n:  # coupled to the last b columns
+            rows.append(n - b + np.repeat(np.arange(b), width))
+            cols.append(c0 + np.tile(np.arange(width), b))
+        c0 += width
+    colptr, rowidx, values, perm = spd(n, (np.concatenate(rows), np.concatenate(cols)))
+    sym = lib.Symbolic(colptr, rowidx, perm, -1.0, {"solve_persist_max": -1})
+    F = lib.factorize(sym, torch.from_numpy(values).cuda(), precision)
+    F.sync()
+    B = np.random.default_rng(5).uniform(-1, 1, (n, 16))
+    for q in (1, 3, 16):
+        X = torch.from_numpy(np.ascontiguousarray(B[:, :q].T)).cuda()
+        F.solve(X)
+        F.sync()
+        eta = oracle.backward_error(n, colptr, rowidx, values, X.cpu().numpy().T, B[:, :q])
+        print(f"tiny={tiny} {precision} nrhs={q}: eta={eta:.2e}", flush=True)
+        assert eta <= BAR[precision]
