@@ -3050,13 +3050,15 @@ __global__ void k_copy_cols(const double *X, int64_t ldx, double *Y, int64_t ldy
 
 // Batched right-hand sides: system i's n_i x nrhs block (leading dimension
 // ld[i]) <-> rows off[i].. of the merged n x nrhs array (leading dimension
-// n).  grid.x = systems, grid.y = right-hand sides.
+// n).  grid.x = systems, grid.y = right-hand sides, grid.z shares a column's
+// rows: 32 systems of 10000 rows, 16 columns took 70 us with one workgroup a
+// column (a fifth of the copy rate), now 31.
 __global__ void k_batch_move(double *const *ptrs, const int64_t *lds, const int64_t *offs, double *M, int64_t n,
                              int to_merged) {
     const int i = blockIdx.x, q = blockIdx.y;
     const int64_t o = offs[i], ni = offs[i + 1] - o, ld = lds[i];
     double *X = ptrs[i];
-    for (int64_t r = threadIdx.x; r < ni; r += blockDim.x) {
+    for (int64_t r = (int64_t)blockIdx.z * blockDim.x + threadIdx.x; r < ni; r += (int64_t)gridDim.z * blockDim.x) {
         if (to_merged) M[o + r + q * n] = X[r + q * ld];
         else X[r + q * ld] = M[o + r + q * n];
     }
@@ -3654,7 +3656,10 @@ void launch_seg_axpby(const double *a, double a0, const double *X, const double 
 void launch_batch_move(double *const *ptrs, const int64_t *lds, const int64_t *offs, double *M, int64_t n,
                        int count, int nrhs, bool to_merged, hipStream_t st) {
     if (count <= 0 || nrhs <= 0) return;
-    hipLaunchKernelGGL(k_batch_move, dim3(count, nrhs), dim3(256), 0, st, ptrs, lds, offs, M, n, to_merged ? 1 : 0);
+    // (by the mean size: a larger system's workgroups go on at the grid's stride)
+    const unsigned z = (unsigned)std::min<int64_t>(std::max<int64_t>(n / count / 512, 1), 64);
+    hipLaunchKernelGGL(k_batch_move, dim3(count, nrhs, z), dim3(256), 0, st, ptrs, lds, offs, M, n,
+                       to_merged ? 1 : 0);
 }
 void launch_copy_cols(const double *X, int64_t ldx, double *Y, int64_t ldy, int64_t n, int nrhs, hipStream_t st) {
     if (n <= 0 || nrhs <= 0) return;

@@ -185,7 +185,7 @@ def tridiag_errors(n, values, X, B):
 
 @pytest.mark.parametrize("maxit", [0, 4])
 @pytest.mark.parametrize("sizes", [(1,), (255,), (1023,), (1024,), (1025,), (2050,), (1, 1023), (700, 324, 1, 1024, 3),
-                                   (40, 1, 2, 61, 64, 1300)], ids=str)
+                                   (40, 1, 2, 61, 64, 1300), (3000, 1, 5000)], ids=str)
 @pytest.mark.parametrize("nrhs", [1, 2, 3, 5, 8, 9, 17])
 def test_refinement_reductions(lib, sizes, nrhs, maxit):
     """Refinement of one system and of batches whose systems end inside and
