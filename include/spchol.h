@@ -418,7 +418,9 @@ int spc_factor_last_ms(spc_factor f, float *ms);
 
 /* Kernel classes of the numeric phase, for spc_factor_kernel_stats; each
  * class is one kernel (the assemble class: the zero fill and the scatter
- * of A), so per-launch figures of a class are those of its kernel. */
+ * of A), so per-launch figures of a class are those of its kernel.  The
+ * POTRF, small and tiny classes are parts of one launch per level; a profiled
+ * factorization launches them one by one, so its total is a little longer. */
 enum spc_kernel_class {
     SPC_K_ASSEMBLE = 0,       /* zero the panels, scatter A into them */
     SPC_K_POTRF = 1,          /* POTRF of 64-column diagonal blocks, with their inverses */

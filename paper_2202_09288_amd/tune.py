@@ -31,7 +31,8 @@ from . import workloads as W
 CACHE = os.path.join(os.path.dirname(os.path.abspath(__file__)), "tuned.json")
 
 # candidate values per group of cut-offs (the first entry of each group is
-# the library default); negative turns a path off
+# the library default; of big and delay, which the default chooses by the
+# level's size, the fixed value below its limits); negative turns a path off
 GROUPS = [
     ("tiny", ("tiny_w", "tiny_m"), [(8, 64), (4, 32), (-1, -1)]),
     ("small", ("small_w", "small_m"), [(32, 128), (16, 64), (32, 64), (-1, -1)]),
