@@ -257,18 +257,28 @@ __device__ __forceinline__ float rcp_nr(float d) {
     const float y = __builtin_amdgcn_rcpf(d);
     return fmaf(y, fmaf(-d, y, 1.0f), y);
 }
-// Diagonals above `big` are scaled by `down` before an elimination that
-// takes 1/d, which would be subnormal near the top of the range.
+// Diagonals of an elimination that takes 1/d: beyond these 1/d would be
+// subnormal or overflow (the pivots themselves can be smaller than the
+// diagonal by its rounding), and the tile is scaled first, each row and column
+// by its own power of two (pivot_exponent: 2^e times 2^e is about d).
 template <typename T>
 struct PivotRange;
 template <>
 struct PivotRange<double> {
-    static constexpr double big = 0x1p1000, down = 0x1p-512, root = 0x1p-256;
+    static constexpr double big = 0x1p1000, small = 0x1p-960;
 };
 template <>
 struct PivotRange<float> {
-    static constexpr float big = 0x1p100f, down = 0x1p-64f, root = 0x1p-32f;
+    static constexpr float big = 0x1p100f, small = 0x1p-100f;
 };
+template <typename T>
+__device__ __forceinline__ bool pivot_far(T d) {
+    return d > PivotRange<T>::big || (d > T(0) && d < PivotRange<T>::small);
+}
+__device__ __forceinline__ int pivot_exponent(double d) { return __builtin_amdgcn_frexp_exp(d) >> 1; }
+__device__ __forceinline__ int pivot_exponent(float d) { return __builtin_amdgcn_frexp_expf(d) >> 1; }
+__device__ __forceinline__ double pow2(double, int e) { return __builtin_amdgcn_ldexp(1.0, e); }
+__device__ __forceinline__ float pow2(float, int e) { return __builtin_amdgcn_ldexpf(1.0f, e); }
 
 // Elimination steps C.. of a 16x16 diagonal tile, by one wave.  Every row of
 // 16 lanes holds the whole symmetric tile: t[k] of lane c is entry (k, c).
@@ -385,7 +395,6 @@ __device__ __forceinline__ void potrf_lds(T (*A)[kNB + 1], PotrfLds<T> &W, int n
     constexpr int PW = 16;
     using M = Mfma<T>;
     using acc_t = typename M::acc;
-    using R = PivotRange<T>;
     const int t = threadIdx.x;
     int lane = t & 63, l16 = lane & 15, lg = lane >> 4;
     // hides the lane's indices from the optimizer, so that the addresses of
@@ -446,23 +455,27 @@ __device__ __forceinline__ void potrf_lds(T (*A)[kNB + 1], PotrfLds<T> &W, int n
             dmax = A[l16][l16];
         }
         T flo = BOOST ? (p0 + l16 < nb ? pfl.v[g0 + p0 + l16] : T(0)) : T(0);
-        T up = T(1), dn = T(1);
-        if (__any(dmax > R::big)) {  // near the top of the type's range
+        // near the ends of the type's range the tile D becomes S D S, the
+        // tile below X becomes X S, and the identity S: the tile below and
+        // the inverse come out as they are, the tile itself as S L
+        const bool far = __any(pivot_far(dmax));
+        const int se = far ? pivot_exponent(dmax) : 0;
+        const T sc = pow2(T(), -se);
+        if (far) {
 #pragma unroll
-            for (int k = 0; k < 16; ++k) tt[k] *= R::down;
+            for (int k = 0; k < 16; ++k) tt[k] *= sc;
+            scale_rows16<T, 0>(tt, sc);
 #pragma unroll
-            for (int e = 0; e < 4 * NX; ++e) x[e] *= R::down;
-            flo *= R::down;
-            up = T(1) / R::root;
-            dn = R::root;
+            for (int e = 0; e < 4 * NX; ++e) x[e] *= sc;
+            flo = flo * sc * sc;
         }
         if constexpr (INV)
 #pragma unroll
-            for (int k = 0; k < 16; ++k) z[k] = k == l16 ? T(1) : T(0);
+            for (int k = 0; k < 16; ++k) z[k] = k == l16 ? sc : T(0);
         eliminate16<T, NX, INV, BOOST, 0>(tt, x, z, flo, dl, boosted, l16);
         const T rs = rsqrt_nr(dl);
         if constexpr (INV) {
-            scale_rows16<T, 0>(z, rs * dn);
+            scale_rows16<T, 0>(z, rs);
             if (lane < 16)
 #pragma unroll
                 for (int k = 0; k < 16; ++k) D[k][l16] = z[k];
@@ -475,21 +488,26 @@ __device__ __forceinline__ void potrf_lds(T (*A)[kNB + 1], PotrfLds<T> &W, int n
                 }
             }
         } else {
-            const T ls = rs * up;
             if constexpr (NX > 0)
 #pragma unroll
-                for (int v = 0; v < 4; ++v) A[16 * ti + M::row(lane, v)][p0 + l16] = x[v] * ls;
+                for (int v = 0; v < 4; ++v) A[16 * ti + M::row(lane, v)][p0 + l16] = x[v] * rs;
             if (wv == 0) {
                 const unsigned long long fail = __ballot(!finite_pos(dl) && lane < 16 && p0 + lane < nb);
                 if (fail && bad < 0) bad = p0 + __builtin_ctzll(fail);
                 // L of the diagonal tile, transposed, above the diagonal, and
                 // its diagonal apart: another wave may still have to read the
                 // tile's values before the elimination
+                T ld = dl * rs;
+                if (far) {
+                    const T up = pow2(T(), se);
+                    scale_rows16<T, 0>(tt, up);
+                    ld *= up;
+                }
                 if (lane < 16) {
-                    W.dg[p0 + l16] = dl * ls;
+                    W.dg[p0 + l16] = ld;
 #pragma unroll
                     for (int k = 1; k < 16; ++k)
-                        if (k > l16) A[p0 + l16][p0 + k] = tt[k] * ls;
+                        if (k > l16) A[p0 + l16][p0 + k] = tt[k] * rs;
                 }
             }
         }

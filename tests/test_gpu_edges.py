@@ -246,3 +246,56 @@ def test_solve_levels_of_tiny_and_wide_supernodes(lib, tiny, precision):
         eta = oracle.backward_error(n, colptr, rowidx, values, X.cpu().numpy().T, B[:, :q])
         print(f"tiny={tiny} {precision} nrhs={q}: eta={eta:.2e}", flush=True)
         assert eta <= BAR[precision]
+
+
+def exponents(kind, n, precision):
+    """Powers of two for the rows and columns: `ends` mixes diagonals near both
+    ends of the precision's range in every tile, `one` puts a single large one
+    among small ones, `random` spreads them, `subnormal` puts all of them below
+    the normal numbers."""
+    top = 505 if precision == "fp64" else 59
+    i = np.arange(n)
+    return {"ends": np.where(i % 2, top - 4, 4 - top), "one": np.where(i == 3, top, -3 * top // 4),
+            "random": np.random.default_rng(n).integers(5 - top, top - 5, n),
+            "subnormal": np.full(n, -515 if precision == "fp64" else -66)}[kind]
+
+
+def scaled_factor_error(lib, n, kind, precision, tuning):
+    """Largest error of a row of the factor of S B S, relative to the row, S
+    powers of two and B well conditioned (of a few bits, so that S B S is
+    exact down into the subnormal numbers): the factor is S times that of B."""
+    import torch
+    B = np.tril(np.random.default_rng(n).integers(-8, 9, (n, n)) / 16.0, -1)
+    B = B + B.T
+    B[np.diag_indices(n)] = np.ceil(np.abs(B).sum(1)) + 1
+    s = np.exp2(exponents(kind, n, precision))
+    r, c = np.tril_indices(n)
+    colptr, rowidx, values = W.lower_csc(n, r, c, B[r, c] * s[r] * s[c])
+    sym = lib.Symbolic(colptr, rowidx, np.arange(n, dtype=np.int32), 0.05, tuning)
+    F = lib.factorize(sym, torch.from_numpy(values).cuda(), precision)
+    F.sync()
+    ref = np.linalg.cholesky(B)
+    L = np.tril(F.export().reshape(n, n).T) / s[:, None]
+    b = np.random.default_rng(7).uniform(-1, 1, n)
+    X = torch.from_numpy((b * s)[None, :].copy()).cuda()
+    F.solve(X)
+    F.sync()
+    x = X.cpu().numpy()[0] * s
+    return float((np.linalg.norm(L - ref, axis=1) / np.linalg.norm(ref, axis=1)).max()), \
+        float(np.abs(B @ x - b).max() / (np.abs(B).sum(1).max() * np.abs(x).max() + np.abs(b).max()))
+
+
+@pytest.mark.parametrize("precision,kind", [("fp64", "ends"), ("fp64", "one"), ("fp64", "random"),
+                                            ("fp64", "subnormal"), ("fp32", "ends"), ("fp32", "one"),
+                                            ("fp32", "random"), ("bf16upd", "ends"), ("bf16upd", "one")])
+@pytest.mark.parametrize("n", [8, 24, 40, 193])
+def test_blocks_of_pivots_of_different_magnitude(lib, n, kind, precision):
+    """Diagonals of one 16-column tile far apart, and near the ends of the
+    range: the 64-column blocks' factorization loses nothing by it.  (With BF16
+    updates the blocks after the first are only good to the rounding of their
+    operands, 2^-8.)"""
+    err, eta = scaled_factor_error(lib, n, kind, precision, BLOCKED)
+    print(f"n={n} {kind} {precision}: worst row {err:.2e}, eta {eta:.2e}", flush=True)
+    rough = precision == "bf16upd" and n > 64
+    assert err <= (1e-2 if rough else 1e-10 if precision == "fp64" else 1e-4)
+    assert eta <= (1e-2 if rough else BAR["fp64" if precision == "fp64" else "fp32"])
