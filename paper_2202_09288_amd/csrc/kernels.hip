@@ -1116,10 +1116,22 @@ __device__ __forceinline__ void small_body(const SmallTask &tk, SmallLds<T> &L, 
             const T a = A[p0 + c][min(i, m - 1)];
             r[c] = real ? a : (c == lane ? T(1) : T(0));
         }
+        // FP32: the hardware's 1/sqrt takes no subnormal number, so a panel
+        // with diagonals near one is scaled as in potrf_lds, each column and
+        // each diagonal row by its own power of two
+        const T dmax = sizeof(T) == 4 && p0 + l16 < w ? A[p0 + l16][p0 + l16] : T(1);
+        const bool far = sizeof(T) == 4 && __any(pivot_far(dmax));
+        const int se = far ? pivot_exponent(dmax) : 0;
         __syncthreads();  // every wave has read the diagonal rows that wave 0 stores below
         if (wv < 3 && (wv == 0 || b0 + RW * wv < m)) {
             T mine = T(0);
-            const T flo = pfl.v ? pfl.v[tk.g0 + min(p0 + l16, w - 1)] : T(0);
+            T flo = pfl.v ? pfl.v[tk.g0 + min(p0 + l16, w - 1)] : T(0);
+            if (far) {
+                const T sc = pow2(T(), -se);
+#pragma unroll
+                for (int c = 0; c < PW; ++c) r[c] = r[c] * lane_read(sc, c) * (dg ? sc : T(1));
+                flo = flo * sc * sc;
+            }
 #pragma unroll
             for (int c = 0; c < PW; ++c) {
                 if ((c & 3) == 0 && p0 + c >= w) break;
@@ -1143,6 +1155,12 @@ __device__ __forceinline__ void small_body(const SmallTask &tk, SmallLds<T> &L, 
                 r[c] = lic;
 #pragma unroll
                 for (int c2 = c + 1; c2 < PW; ++c2) r[c2] -= lic * lane_read(lic, c2);
+            }
+            if (far) {
+                mine *= pow2(T(), -se);
+                if (dg)
+#pragma unroll
+                    for (int c = 0; c < PW; ++c) r[c] *= pow2(T(), se);
             }
             if (wv == 0 && dg) L.rdg[p0 + lane] = mine;
             if (real && (wv == 0 || !dg))

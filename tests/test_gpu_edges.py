@@ -299,3 +299,13 @@ def test_blocks_of_pivots_of_different_magnitude(lib, n, kind, precision):
     rough = precision == "bf16upd" and n > 64
     assert err <= (1e-2 if rough else 1e-10 if precision == "fp64" else 1e-4)
     assert eta <= (1e-2 if rough else BAR["fp64" if precision == "fp64" else "fp32"])
+
+
+@pytest.mark.parametrize("kind", ["ends", "one", "random", "subnormal"])
+@pytest.mark.parametrize("precision", ["fp64", "fp32"])
+@pytest.mark.parametrize("n,persist", [(9, -1), (17, 1), (32, -1)])
+def test_small_supernodes_of_pivots_of_different_magnitude(lib, n, persist, precision, kind):
+    """The same for the one-workgroup path."""
+    err, eta = scaled_factor_error(lib, n, kind, precision, {"tiny_w": -1, "tiny_m": -1, "persist": persist})
+    print(f"n={n} {kind} {precision} persist={persist}: worst row {err:.2e}, eta {eta:.2e}", flush=True)
+    assert err <= (1e-10 if precision == "fp64" else 1e-4) and eta <= BAR[precision]
