@@ -97,15 +97,16 @@ typedef struct spc_options {
      *                     (eight or more supernodes, or the waiting tiles at
      *                     most 1.5 of a launch's mean share per XCD beside
      *                     the step's other tiles), the others get a TRSM
-     *                     launch.  Default 1.
+     *                     launch.  Default: 1, and 2 in the steps that the
+     *                     default `delay` groups.
      *   delay             column blocks per bulk trailing update inside a wide
      *                     supernode: the columns beyond a group of `delay`
      *                     64-column blocks receive the group's update once,
      *                     with K = 64 * delay, while each next block inside
      *                     the group is brought up to date on its own; at most
-     *                     8; a negative value keeps 1.  Default: 4 with
-     *                     lookahead and hand-over rule 2 where a level has at
-     *                     least 3500 64x64 tiles beyond the step's block, else 1
+     *                     8; a negative value keeps 1.  Default: 4 where a
+     *                     level has at least 3500 64x64 tiles beyond the step's
+     *                     block, else 1
      *   persist           1: every small subtree (a supernode whose whole
      *                     subtree is within the one-wave or one-workgroup
      *                     limits), of every system of a batch, is factored by

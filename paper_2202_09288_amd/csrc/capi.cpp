@@ -896,6 +896,7 @@ int spc_analyze(int64_t n, const int64_t *h_colptr, const int32_t *h_rowidx, con
                         pick(opts->bulk128, 0, 1, 0, &tu.bulk128) &&
                         pick(opts->lookahead, opts->delay == 0 ? 1 : 0, 1, 0, &tu.lookahead);
         tu.delay_auto = opts->delay == 0;
+        tu.handover_auto = opts->handover == 0;
         tu.big_fill = opts->big_min == 0 && opts->big_min_k == 0 ? spc::kBigFill : 0;
         if (!ok) {
             delete s;

@@ -74,6 +74,7 @@ struct Tuning {
     int32_t big_min = kBigMin, big_min_k = kBigMinK;
     int32_t solve_persist_max = kSolvePersistMax;
     int32_t handover = 1;  // fused TRSM with in-launch waits (0: off, 2: only where few tiles wait)
+    bool handover_auto = true;  // instead of 1: 2 in the steps that delay_auto groups
     int32_t delay = kDelay;  // column blocks per bulk trailing update
     bool delay_auto = true;  // instead: kDelayAuto or one, by the rule at kDelayTiles
     int32_t persist = 0;     // small subtrees in one persistent launch (0: per level)

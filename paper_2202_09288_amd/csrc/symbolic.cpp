@@ -550,8 +550,9 @@ int build_schedule(Symbolic &S) {
                 b = e;
             }
         }
-        // (a group that delay_auto made takes the hand-over by rule 2)
-        auto grouped = [&](int64_t b) { return tu.delay_auto && glast[b] > gfirst[b]; };
+        // (a group that delay_auto made takes the hand-over by rule 2, unless
+        // another was asked for)
+        auto grouped = [&](int64_t b) { return tu.handover_auto && tu.delay_auto && glast[b] > gfirst[b]; };
         // handover 2: a step takes the hand-over only where few of its
         // tiles wait (they hold their CUs while the block is factored):
         // eight or more supernodes get one, or the waiting tiles are at most

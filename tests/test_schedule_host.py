@@ -68,3 +68,19 @@ def test_solve_handovers_counted():
     every.verify()
     assert every.info["nsuper"] == 1 and every.info["solve_handovers"] == 9
     assert spchol.Symbolic(colptr, rowidx, perm, 0.05, {"solve_persist_max": -1}).info["solve_handovers"] == 0
+
+
+def test_given_handover_rule_holds_in_default_groups():
+    """A hand-over rule that is asked for is kept where the library groups
+    column blocks by itself (the root of a 64^3 grid), where its own choice is
+    another: the task lists (part of the reported bytes) differ, and the
+    groups' other options do not change them."""
+    s = W.laplacian((64, 64, 64), "7pt", 88, 0, unit=False, shift=1e-2, nrhs=1)
+
+    def size(**tuning):
+        sym = spchol.Symbolic(s.colptr, s.rowidx, s.perm, 0.05, tuning or None)
+        sym.verify()
+        return sym.info["factor_bytes_fp64"]
+    default, one, two = size(), size(handover=1), size(handover=2)
+    assert len({default, one, two, size(handover=-1), size(delay=1)}) == 5
+    assert size(handover=1, lookahead=1) == one and size(lookahead=1) == default
