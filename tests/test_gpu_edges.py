@@ -11,6 +11,7 @@ import pytest
 
 import oracle
 from paper_2202_09288_amd import workloads as W
+from tests.wide_levels import BORDER, WIDTHS, uneven_arrow
 
 pytestmark = pytest.mark.gpu
 
@@ -309,3 +310,69 @@ def test_small_supernodes_of_pivots_of_different_magnitude(lib, n, persist, prec
     err, eta = scaled_factor_error(lib, n, kind, precision, {"tiny_w": -1, "tiny_m": -1, "persist": persist})
     print(f"n={n} {kind} {precision} persist={persist}: worst row {err:.2e}, eta {eta:.2e}", flush=True)
     assert err <= (1e-10 if precision == "fp64" else 1e-4) and eta <= BAR[precision]
+
+
+@pytest.fixture(scope="module")
+def uneven():
+    """The wide level of tests/wide_levels.py as one system and as two."""
+    return uneven_arrow(sum(WIDTHS, []), BORDER), [uneven_arrow(w, BORDER, i) for i, w in enumerate(WIDTHS)]
+
+
+def csc_backward_error(matrix, X, B):
+    """Normwise backward error (largest column) of a lower CSC system."""
+    import scipy.sparse as sp
+    colptr, rowidx, values, _ = matrix
+    n = colptr.size - 1
+    A = sp.csc_matrix((values, rowidx, colptr), shape=(n, n))
+    A = A + sp.tril(A, -1).T
+    r = np.abs(B - A @ X).max(0)
+    return float((r / (abs(A).sum(1).max() * np.abs(X).max(0) + np.abs(B).max(0))).max())
+
+
+@pytest.mark.parametrize("precision", ["fp64", "fp32", "bf16upd"])
+def test_default_groups_follow_each_other(lib, uneven, precision):
+    """Two default groups of four blocks in a row with supernodes that end
+    raggedly inside them: the factor is that of one block a group, to the
+    rounding of the updates (BF16 operands: 2^-8), with the update beyond the
+    next group spread over its steps or not and under every hand-over rule."""
+    import torch
+    colptr, rowidx, values, perm = uneven[0]
+    n = colptr.size - 1
+    dv = torch.from_numpy(values).cuda()
+    B = np.random.default_rng(9).uniform(-1, 1, (n, 3))
+    bar = {"fp64": (1e-10, 1e-12), "fp32": (1e-4, 1e-5), "bf16upd": (1e-2, 1e-2)}[precision]
+    ref = None
+    for tuning in ({"delay": 1}, {}, {"lookahead": -1}, {"handover": 1}, {"handover": -1}):
+        sym = lib.Symbolic(colptr, rowidx, perm, -1.0, tuning)
+        F = lib.factorize(sym, dv, precision)
+        F.sync()
+        L = F.export()
+        if ref is None:
+            ref, lptr = L, oracle.Symbolic(colptr, rowidx, perm, -1.0).lptr
+        err = float(oracle.supernode_rel_errors(L, ref, lptr).max())
+        X = torch.from_numpy(np.ascontiguousarray(B.T)).cuda()
+        F.solve(X)
+        F.sync()
+        eta = csc_backward_error(uneven[0], X.cpu().numpy().T, B)
+        print(f"{precision} {tuning}: worst supernode {err:.2e}, eta {eta:.2e}", flush=True)
+        assert err <= bar[0] and eta <= bar[1]
+
+
+@pytest.mark.parametrize("precision", ["fp64", "fp32", "bf16upd"])
+def test_default_groups_of_a_batch(lib, uneven, precision):
+    """Two systems whose merged level reaches the groups' limit, which neither
+    reaches alone, also when factored again."""
+    import torch
+    systems = uneven[1]
+    vals = [torch.from_numpy(v).cuda() for _, _, v, _ in systems]
+    Bs = [np.random.default_rng(i).uniform(-1, 1, (2, c.size - 1)) for i, (c, _, _, _) in enumerate(systems)]
+    batch = lib.Batch([lib.Symbolic(c, r, p, -1.0) for c, r, _, p in systems], precision)
+    for _ in range(2):
+        batch.factorize(vals)
+        Xs = [torch.from_numpy(b).cuda() for b in Bs]
+        batch.solve(Xs)
+        batch.sync()
+        for matrix, x, b in zip(systems, Xs, Bs):
+            eta = csc_backward_error(matrix, x.cpu().numpy().T, b.T)
+            print(f"{precision} n={b.shape[1]}: eta {eta:.2e}", flush=True)
+            assert eta <= {"fp64": 1e-12, "fp32": 1e-5, "bf16upd": 1e-2}[precision]

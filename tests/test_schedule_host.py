@@ -9,6 +9,7 @@ import numpy as np
 import pytest
 
 from paper_2202_09288_amd import workloads as W
+from tests.wide_levels import BORDER, WIDTHS, uneven_arrow
 
 from paper_2202_09288_amd import spchol  # noqa: E402  (conftest builds it when missing)
 
@@ -84,3 +85,17 @@ def test_given_handover_rule_holds_in_default_groups():
     default, one, two = size(), size(handover=1), size(handover=2)
     assert len({default, one, two, size(handover=-1), size(delay=1)}) == 5
     assert size(handover=1, lookahead=1) == one and size(lookahead=1) == default
+
+
+def test_schedule_invariants_default_groups():
+    """Groups of four blocks made by default, two in a row, with supernodes
+    that end inside them, and at one block a group, with the update beyond the
+    next group spread over its steps or not: all valid, and different."""
+    colptr, rowidx, _, perm = uneven_arrow(sum(WIDTHS, []), BORDER)
+    sizes = set()
+    for tuning in (None, {"lookahead": -1}, {"handover": 1}, {"handover": -1}, {"delay": 1}):
+        sym = spchol.Symbolic(colptr, rowidx, perm, -1.0, tuning)
+        sym.verify()
+        assert sym.info["nsuper"] == 6
+        sizes.add(sym.info["factor_bytes_fp64"])
+    assert len(sizes) == 5
