@@ -30,17 +30,19 @@ from . import workloads as W
 
 CACHE = os.path.join(os.path.dirname(os.path.abspath(__file__)), "tuned.json")
 
-# candidate values per group of cut-offs (the first entry of each group is
-# the library default; of big and delay, which the default chooses by the
-# level's size, the fixed value below its limits); negative turns a path off
+# candidate values per group of cut-offs; negative turns a path off.  The
+# first entry of each group is the library default, or, for big, delay,
+# handover and lookahead, where the default goes by the level's size, the
+# fixed value below its limits; their 0 leaves the choice to the library
+# again, so that a later pass can come back to it.
 GROUPS = [
     ("tiny", ("tiny_w", "tiny_m"), [(8, 64), (4, 32), (-1, -1)]),
     ("small", ("small_w", "small_m"), [(32, 128), (16, 64), (32, 64), (-1, -1)]),
-    ("big", ("big_min", "big_min_k"), [(256, 128), (128, 64), (512, 128), (256, 256), (-1, -1)]),
+    ("big", ("big_min", "big_min_k"), [(256, 128), (128, 64), (512, 128), (256, 256), (-1, -1), (0, 0)]),
     ("persist", ("solve_persist_max",), [(1024,), (256,), (4096,)]),
-    ("delay", ("delay",), [(1,), (2,), (3,), (4,)]),
-    ("handover", ("handover",), [(1,), (-1,), (2,)]),
-    ("lookahead", ("lookahead",), [(-1,), (1,)]),
+    ("delay", ("delay",), [(1,), (2,), (3,), (4,), (0,)]),
+    ("handover", ("handover",), [(1,), (-1,), (2,), (0,)]),
+    ("lookahead", ("lookahead",), [(-1,), (1,), (0,)]),
     ("persist", ("persist",), [(-1,), (1,)]),
     ("group", ("group",), [(1,), (-1,)]),
     ("bulk128", ("bulk128",), [(-1,), (1,)]),
@@ -167,6 +169,7 @@ def tune(systems, nrhs: int, precision: str = "fp64", reps: int = 5, log=print, 
             for vals in cands:
                 trial = dict(best)
                 trial.update(dict(zip(fields, vals)))
+                trial = {f: v for f, v in trial.items() if v != 0}
                 key = json.dumps(trial, sort_keys=True)
                 if key in tried:
                     continue

@@ -63,3 +63,20 @@ def test_second_pass_finds_settings_that_pay_together(monkeypatch):
     keys = [json.dumps(t["tuning"], sort_keys=True) for t in res["trials"]]
     assert len(keys) == len(set(keys))
     assert any(not t["ok"] for t in res["trials"])
+
+
+def test_second_pass_can_return_to_the_default_choice(monkeypatch):
+    """A fixed bulk depth that pays alone, but less than the library's own
+    choice once the hand-over rule has changed: the tuner comes back to it,
+    and never times the defaults twice by spelling them out as 0."""
+    import torch
+
+    def cost(t):
+        return {(None, None): 10.0, (2, None): 9.0, (2, 2): 8.0, (None, 2): 5.0}.get(
+            (t.get("delay"), t.get("handover")), 11.0)
+
+    monkeypatch.setattr(tune, "measure", lambda s, nrhs, tuning, *_: (cost(tuning), 0.0, 1e-16))
+    monkeypatch.setattr(torch.cuda, "set_device", lambda *_: None)
+    res = tune.tune([None], 1, "fp64", log=lambda *_: None)
+    assert {k: v for k, v in res["tuning"].items() if k in ("delay", "handover")} == {"handover": 2}
+    assert all(0 not in t["tuning"].values() for t in res["trials"])
