@@ -361,9 +361,9 @@ __device__ __forceinline__ void fill_last_inverse(T *Vi) {
 // Factor the block in A (nb <= 64; rows and columns >= nb hold the identity;
 // only the lower triangle is read, what is above the diagonal is scratch),
 // write L into P (columns c0.., leading dimension m, lower triangle only) and
-// the inverse into Vi; a failed pivot lowers *status to g0 + its column.  Called by all 256 threads of the workgroup.  With pflags (a full
-// block, nb = 64), each panel p is also handed to workgroups of the same
-// launch: its L and the inverse of its 16x16 diagonal triangle go out with
+// the inverse into Vi; a failed pivot lowers *status to g0 + its column.
+// Called by all 256 threads of the workgroup.  With pflags (a full block,
+// nb = 64), each panel p is also handed to workgroups of the same launch: its L and the inverse of its 16x16 diagonal triangle go out with
 // device-scope atomic stores, and each of waves 2 and 3 adds 1 to pflags[p]
 // once its part has completed (kPanelParts when the panel is out; the last
 // panel by its values, above).  next_full: the supernode's next block is a
@@ -382,12 +382,15 @@ __device__ __forceinline__ void fill_last_inverse(T *Vi) {
 // with S_ij, later X_ij, in the tile (j, i) of A.  Only the last row's three
 // products remain after the last panel.
 // L^{-1} is stored column-major: Vi[k * nb + i] = (L^{-1})_ik.
-// Bound by the chain of 64 pivots.  The form before kept a panel's 16
-// columns in the registers of lane = row of one wave, its multipliers read
-// lane by lane into scalar registers, had a reciprocal square root in the
-// chain and the inverse after it; one block alone took 19.6 us (FP64) and
-// 16.9 (FP32) a launch, this one 12.6 and 11.3; the trailing launches of a
-// 34^3 grid's top levels (FP32) 21.7 and 18.4 on average.
+// Bound by the 64 pivots, 125 to 170 cycles each: a chain of a reciprocal and
+// four dependent multiply-adds, and a move and a multiply-add to issue for
+// every row of the tile and of the one beside it (FP64: 90 to 120 cycles on
+// average).  The form before kept a panel's 16 columns in the registers of
+// lane = row of one wave, its multipliers read lane by lane into scalar
+// registers, had a reciprocal square root in the chain and the inverse after
+// it; one block alone took 19.6 us (FP64) and 16.9 (FP32) a launch, this one
+// 12.6 and 11.3; the trailing launches of a 34^3 grid's top levels (FP32) 21.7
+// and 18.4 on average.
 template <typename T, bool BOOST = false>
 __device__ __forceinline__ void potrf_lds(T (*A)[kNB + 1], PotrfLds<T> &W, int nb, T *P, int64_t m, int c0, T *Vi,
                                           unsigned long long *status, int64_t g0, int32_t *pflags, bool next_full,

@@ -45,11 +45,24 @@ constexpr int kBigFill = 256;
 // chain of dependent steps.  So by default a group has one block, and
 // kDelayAuto where the level has at least kDelayTiles 64x64 tiles beyond the
 // step's block: those move about 130 KB each at K = 64, which 3,500 take 90 us
-// for, several times a step of the chain.  Measured at thresholds 1000, 2000,
-// 3000, 4500, 9000 and none: 48^3 elasticity FP64 52.9, 53.0, 52.9, 53.2,
-// 55.4, 59.4 ms; 60^3 12.21, 12.00, 12.03, 11.99, 12.06, 12.05; 30x29x27
-// elasticity 5.52, 5.41, 5.39, 5.37, 5.40, 5.37.  Groups of 2, 3, 4, 6, 8:
-// 48^3 elasticity 55.7, 54.3, 53.8, 54.4, 54.8.
+// for, several times a step of the chain.  FP32, whose tiles move half as
+// much, gains from groups only at a higher limit than FP64.  Factorization in
+// ms at limits of 2000, 2750, 3500, 4500 and none (spread 0.05 to 0.2):
+//   64^3 grid        FP64 19.05, 19.06, 19.11, 19.22, 19.23
+//                    FP32 13.26, 13.17, 13.16, 13.19, 13.17
+//   68x66x64 grid    FP64 19.63, 19.52, 19.57, 19.69, 19.74
+//                    FP32 13.45, 13.32, 13.25, 13.24, 13.23
+//   38^3 elasticity  FP64 18.51, 18.42, 18.50, 18.63, 18.77
+//                    FP32 12.42, 12.28, 12.26, 12.23, 12.24
+//   42^3 elasticity  FP64 29.26, 29.10, 29.22, 29.45, 30.30
+//                    FP32 18.82, 18.68, 18.65, 18.59, 18.83
+//   48^3 elasticity  FP64 53.27, 53.32, 53.35, 53.58, 59.77
+//                    FP32 32.61, 32.59, 32.56, 32.51, 34.37
+// The 56^3 and 60^3 grids and 30x29x27 and 34^3 elasticity do not move (60^3,
+// whose root has 3,486 tiles: FP64 11.94, 11.96, 12.00, 12.01, 12.03).  The
+// limit is where FP32 loses nothing yet and FP64 is within half a percent of
+// its best.  Groups of 2, 3, 4, 6, 8: 48^3 elasticity 55.7, 54.3, 53.8, 54.4,
+// 54.8.
 constexpr int kDelay = 1;
 constexpr int kDelayMax = 8;
 constexpr int kDelayAuto = 4;
