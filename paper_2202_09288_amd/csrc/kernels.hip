@@ -362,12 +362,13 @@ __device__ __forceinline__ void fill_last_inverse(T *Vi) {
 // only the lower triangle is read, what is above the diagonal is scratch),
 // write L into P (columns c0.., leading dimension m, lower triangle only) and
 // the inverse into Vi; a failed pivot lowers *status to g0 + its column.
-// Called by all 256 threads of the workgroup.  With pflags (a full block,
-// nb = 64), each panel p is also handed to workgroups of the same launch: its L and the inverse of its 16x16 diagonal triangle go out with
-// device-scope atomic stores, and each of waves 2 and 3 adds 1 to pflags[p]
-// once its part has completed (kPanelParts when the panel is out; the last
-// panel by its values, above).  next_full: the supernode's next block is a
-// full one, whose last tile of the inverse is unset here.
+// Called by all 256 threads of the workgroup.  With pflags (a full block, nb =
+// 64), each panel p is also handed to workgroups of the same launch: its L and
+// the inverse of its 16x16 diagonal triangle go out with device-scope atomic
+// stores, and each of waves 2 and 3 adds 1 to pflags[p] once its part has
+// completed (kPanelParts when the panel is out; the last panel by its values,
+// above).  next_full: the supernode's next block is a full one, whose last
+// tile of the inverse is unset here.
 //
 // Four 16-column panels, one workgroup barrier each.  In step p each of the
 // panel's tiles below the diagonal (at most three) has a wave of its own (0,
