@@ -259,8 +259,8 @@ __device__ __forceinline__ float rcp_nr(float d) {
 }
 // Diagonals of an elimination that takes 1/d: beyond these 1/d would be
 // subnormal or overflow (the pivots themselves can be smaller than the
-// diagonal by its rounding), and the tile is scaled first, each row and column
-// by its own power of two (pivot_exponent: 2^e times 2^e is about d).
+// diagonal by its rounding), and the tile is scaled first, each column by its
+// own power of two (pivot_exponent: 2^e times 2^e is about d).
 template <typename T>
 struct PivotRange;
 template <>
@@ -459,27 +459,26 @@ __device__ __forceinline__ void potrf_lds(T (*A)[kNB + 1], PotrfLds<T> &W, int n
             dmax = A[l16][l16];
         }
         T flo = BOOST ? (p0 + l16 < nb ? pfl.v[g0 + p0 + l16] : T(0)) : T(0);
-        // near the ends of the type's range the tile D becomes S D S, the
-        // tile below X becomes X S, and the identity S: the tile below and
-        // the inverse come out as they are, the tile itself as S L
-        const bool far = __any(pivot_far(dmax));
-        const int se = far ? pivot_exponent(dmax) : 0;
-        const T sc = pow2(T(), -se);
-        if (far) {
+        // near the ends of the type's range the columns are scaled, S powers
+        // of two: the elimination keeps the scale of each column (u becomes
+        // u S, d becomes d s), about the root of the diagonal, and d s s is
+        // about 1
+        T sc = T(1);
+        if (__any(pivot_far(dmax))) {
+            sc = pow2(T(), -pivot_exponent(dmax));
 #pragma unroll
             for (int k = 0; k < 16; ++k) tt[k] *= sc;
-            scale_rows16<T, 0>(tt, sc);
 #pragma unroll
             for (int e = 0; e < 4 * NX; ++e) x[e] *= sc;
-            flo = flo * sc * sc;
+            flo *= sc;
         }
         if constexpr (INV)
 #pragma unroll
-            for (int k = 0; k < 16; ++k) z[k] = k == l16 ? sc : T(0);
+            for (int k = 0; k < 16; ++k) z[k] = k == l16 ? T(1) : T(0);
         eliminate16<T, NX, INV, BOOST, 0>(tt, x, z, flo, dl, boosted, l16);
-        const T rs = rsqrt_nr(dl);
+        const T rs = rsqrt_nr(dl * sc);  // 1 / (s sqrt(d))
         if constexpr (INV) {
-            scale_rows16<T, 0>(z, rs);
+            scale_rows16<T, 0>(z, rs * sc);
             if (lane < 16)
 #pragma unroll
                 for (int k = 0; k < 16; ++k) D[k][l16] = z[k];
@@ -501,14 +500,8 @@ __device__ __forceinline__ void potrf_lds(T (*A)[kNB + 1], PotrfLds<T> &W, int n
                 // L of the diagonal tile, transposed, above the diagonal, and
                 // its diagonal apart: another wave may still have to read the
                 // tile's values before the elimination
-                T ld = dl * rs;
-                if (far) {
-                    const T up = pow2(T(), se);
-                    scale_rows16<T, 0>(tt, up);
-                    ld *= up;
-                }
                 if (lane < 16) {
-                    W.dg[p0 + l16] = ld;
+                    W.dg[p0 + l16] = dl * rs;
 #pragma unroll
                     for (int k = 1; k < 16; ++k)
                         if (k > l16) A[p0 + l16][p0 + k] = tt[k] * rs;
