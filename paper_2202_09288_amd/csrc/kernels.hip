@@ -1114,8 +1114,8 @@ __device__ __forceinline__ void small_body(const SmallTask &tk, SmallLds<T> &L, 
             r[c] = real ? a : (c == lane ? T(1) : T(0));
         }
         // FP32: the hardware's 1/sqrt takes no subnormal number, so a panel
-        // with diagonals near one is scaled as in potrf_lds, each column and
-        // each diagonal row by its own power of two
+        // with diagonals near them is scaled by powers of two, each column
+        // and each diagonal row by its own
         const T dmax = sizeof(T) == 4 && p0 + l16 < w ? A[p0 + l16][p0 + l16] : T(1);
         const bool far = sizeof(T) == 4 && __any(pivot_far(dmax));
         const int se = far ? pivot_exponent(dmax) : 0;
