@@ -334,7 +334,8 @@ def test_default_groups_follow_each_other(lib, uneven, precision):
     """Two default groups of four blocks in a row with supernodes that end
     raggedly inside them: the factor is that of one block a group, to the
     rounding of the updates (BF16 operands: 2^-8), with the update beyond the
-    next group spread over its steps or not and under every hand-over rule."""
+    next group spread over its steps or not, on 128x128 tiles, and under every
+    hand-over rule."""
     import torch
     colptr, rowidx, values, perm = uneven[0]
     n = colptr.size - 1
@@ -342,7 +343,7 @@ def test_default_groups_follow_each_other(lib, uneven, precision):
     B = np.random.default_rng(9).uniform(-1, 1, (n, 3))
     bar = {"fp64": (1e-10, 1e-12), "fp32": (1e-4, 1e-5), "bf16upd": (1e-2, 1e-2)}[precision]
     ref = None
-    for tuning in ({"delay": 1}, {}, {"lookahead": -1}, {"handover": 1}, {"handover": -1}):
+    for tuning in ({"delay": 1}, {}, {"lookahead": -1}, {"handover": 1}, {"handover": -1}, {"bulk128": 1}):
         sym = lib.Symbolic(colptr, rowidx, perm, -1.0, tuning)
         F = lib.factorize(sym, dv, precision)
         F.sync()
